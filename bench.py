@@ -96,11 +96,12 @@ def copy_calibration(nbytes=1 << 30):
     print(json.dumps({"copy_bytes_read": nbytes, "copy_bytes_written": nbytes, "launches": 3}), flush=True)
 
 
-def kernel_names(rtype, cfg, multi, ke=False):
+def kernel_names(rtype, cfg, multi, ke=False, sparse=False):
     """Names of the two particle kernels as the profiler lists them (cfg: launch shapes; ke:
-    the gas has internal degrees of freedom)."""
-    return {"stream": f"k_stream<{rtype}, {cfg[0]}, {'true' if multi else 'false'}, {cfg[1]}>",
-            "gather": f"k_gather<{rtype}, 1, {'true' if ke else 'false'}>"}
+    the gas has internal degrees of freedom; sparse: fewer than 320 particles per cell on a
+    large mesh)."""
+    return {"stream": f"k_stream{'_e' if ke else ''}<{rtype}, {cfg[0]}, {'true' if multi else 'false'}, {cfg[1]}>",
+            "gather": f"k_gather{'_sparse' if sparse else ''}<{rtype}, 1, {'true' if ke else 'false'}>"}
 
 
 def timed_steps(s, steps):
@@ -246,7 +247,7 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
     s.profile(False)
     el, moves, kms, st0, st1 = timed_steps(s, steps)
     done_steps = int(st1["step"])
-    names = kernel_names("float", cfg, True)
+    names = kernel_names("float", cfg, True, sparse=True)
     workload = "batch64"
     dom, kr = kernel_roofline(kms, moves / steps, st1, "float", names, workload)
     faces = sum((6 * w.mesh.n_cells + int(w.mesh.bface_nodes.shape[0])) // 2 for w in ws)

@@ -215,7 +215,6 @@ size_t carve(const HostMesh &H, int n_inst, long long cap, int prec, bool recon,
     D.injoff = C.take<long long>(nff + 1);
     D.W = C.take<double>(5 * nc);
     D.P = C.take<double>(5 * nc);
-    D.nleft = C.take<int32_t>(nc);
     D.tau = C.take<double>(nc);
     D.ec = C.take<double>(nc);
     D.rhoh = C.take<double>(nc);
@@ -224,16 +223,16 @@ size_t carve(const HostMesh &H, int n_inst, long long cap, int prec, bool recon,
     D.nsam = C.take<long long>(nc);
     D.samoff = C.take<long long>(nc + 1);
     D.scan64 = C.take<long long>((size_t)ugkwp::scan_partials_needed((long long)(nc > nff ? nc : nff)));
-    D.off = C.take<int32_t>(2 * nc + 1);
-    D.scan32 = C.take<int32_t>((size_t)ugkwp::scan_partials_needed(2 * (long long)nc));
-    D.spart = C.take<unsigned long long>(128);
+    D.lrun = reinterpret_cast<unsigned long long *>(D.nsam);  // (N_sam is not read after the sampling)
+    D.off = C.take<unsigned long long>(2 * nc + 1);
+    D.scan32 = C.take<unsigned long long>((size_t)ugkwp::scan_partials_needed(2 * (long long)nc));
+    D.spart = C.take<unsigned long long>(2 * ugkwp::kWallSeg);
     D.cnt64 = C.take<unsigned long long>(2 * nc);
-    D.rank = C.take<int32_t>((size_t)(cap + ugkwp::kWallSlack));
-    D.wallq = C.take<unsigned int>(ugkwp::kWallSeg);
-    D.segoff[0] = C.take<int32_t>(nc + 1);
-    D.segoff[1] = C.take<int32_t>(nc + 1);
-    D.key = C.take<int32_t>((size_t)cap);
-    D.perm = C.take<int32_t>((size_t)cap);
+    D.v0[0] = C.take<int32_t>(nc + 1);
+    D.v0[1] = C.take<int32_t>(nc + 1);
+    D.lkey = C.take<int32_t>((size_t)cap);
+    D.lsrc = C.take<uint32_t>((size_t)cap);
+    D.perm = C.take<unsigned long long>((size_t)cap);
     D.big = C.take<int32_t>(nc);
     for (int b = 0; b < 2; ++b) {
         ugkwp::Particles &P = D.pa[b];
@@ -250,7 +249,6 @@ size_t carve(const HostMesh &H, int n_inst, long long cap, int prec, bool recon,
             P.rec = C.take<ugkwp::PRec>((size_t)cap);
             if (K > 0) P.e64 = C.take<double>((size_t)cap);
         }
-        P.cell = C.take<int32_t>((size_t)cap);
     }
     D.sc = C.take<Scalars>(1);
     D.avgA = C.take<double>(5 * nc);
@@ -491,14 +489,13 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
     D.any_diffuse = 0;
     for (const auto &bc : ctx->H.bcs) D.any_diffuse |= bc.type == 1 ? 1 : 0;
     D.all_box = D.nfar != nullptr ? 1 : 0;
+    D.all_tet = 1;
+    for (uint8_t t : H.ctype) D.all_tet = D.all_tet && t == 4;
     {
-        // sparsely filled cells (the tetrahedral runs, ~50 particles each) give a block of the
-        // bucket count many distinct keys: smaller blocks and a higher occupancy pay there;
-        // dense cells keep the larger blocks (fewer global atomics per key)
         double per_cell = 0.0;
         for (int k = 0; k < n_inst; ++k)
             per_cell += (double)(ctx->ranges[k].cell1 - ctx->ranges[k].cell0) * std::max(p[k].n_ref, p[k].n_min);
-        D.count_ch = per_cell < 128.0 * (double)H.nc ? 4 : 8;
+        D.list_sparse = H.nc >= 16384 && per_cell < 320.0 * (double)H.nc ? 1 : 0;
     }
     D.cap = cap;
     D.prec = p[0].precision;
@@ -629,9 +626,9 @@ int32_t ugkwp_init_state(ugkwp_ctx *ctx, const double *W0) {
     sc.dtmin_bits = 0x7FF0000000000000ULL;
     HIPCHK(ctx, up(D.W, Wt, s));
     ugkwp::launch_fill_f64(D.P, 5 * (long long)nc, 0.0, s);
-    ugkwp::launch_fill_i32(D.nleft, (long long)nc, 0, s);
-    ugkwp::launch_fill_i32(D.segoff[0], (long long)nc + 1, 0, s);
-    ugkwp::launch_fill_i32(D.segoff[1], (long long)nc + 1, 0, s);
+    ugkwp::launch_fill_i32(D.v0[0], (long long)nc + 1, 0, s);
+    ugkwp::launch_fill_i32(D.v0[1], (long long)nc + 1, 0, s);
+    ugkwp::launch_fill_f64(reinterpret_cast<double *>(D.off), 2 * (long long)nc + 1, 0.0, s);
     ugkwp::launch_fill_f64(D.avgA, 5 * (long long)nc, 0.0, s);
     ugkwp::launch_heat(D, 0, s);  // no particle yet: zero heat fluxes
     HIPCHK(ctx, hipGetLastError());
@@ -822,7 +819,21 @@ int32_t ugkwp_export_particles(ugkwp_ctx *ctx, double *x, double *u, double *m, 
     int64_t n = 0;
     int32_t st = ugkwp_particle_count(ctx, &n);
     if (st != UGKWP_OK) return st;
-    const ugkwp::Particles &P = ctx->D.pa[ctx->buf];
+    // in their order into the other buffer, which holds nothing between two steps
+    const ugkwp::Particles &P = ctx->D.pa[ctx->buf ^ 1];
+    if (n > 0) {
+        ugkwp::launch_pack(ctx->D, ctx->buf, ctx->stream);
+        HIPCHK(ctx, hipGetLastError());
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    }
+    std::vector<unsigned long long> off;  // per cell: its first particle in the high word
+    if (n > 0 && cell) {
+        const size_t nc = (size_t)ctx->D.nc;
+        off.resize(nc + 1);
+        HIPCHK(ctx, hipMemcpy(off.data(), ctx->D.off, (nc + 1) * sizeof(off[0]), hipMemcpyDeviceToHost));
+        for (size_t c = 0; c < nc; ++c)
+            for (int64_t i = (int64_t)(off[c] >> 32); i < (int64_t)(off[c + 1] >> 32); ++i) cell[i] = (int32_t)c;
+    }
     if (n > 0 && ctx->D.prec == 1) {
         std::vector<ugkwp::PRec32> rec((size_t)n);
         std::vector<float> mm((size_t)n);
@@ -836,7 +847,6 @@ int32_t ugkwp_export_particles(ugkwp_ctx *ctx, double *x, double *u, double *m, 
             if (m) m[i] = mm[i];
             if (uid) uid[i] = rec[i].uid;
         }
-        if (cell) HIPCHK(ctx, hipMemcpy(cell, P.cell, n * sizeof(int32_t), hipMemcpyDeviceToHost));
         if (e && P.e32) {
             std::vector<float> ee((size_t)n);
             HIPCHK(ctx, hipMemcpy(ee.data(), P.e32, n * sizeof(float), hipMemcpyDeviceToHost));
@@ -855,7 +865,6 @@ int32_t ugkwp_export_particles(ugkwp_ctx *ctx, double *x, double *u, double *m, 
             if (m) m[i] = rec[i].m;
             if (uid) uid[i] = rec[i].uid;
         }
-        if (cell) HIPCHK(ctx, hipMemcpy(cell, P.cell, n * sizeof(int32_t), hipMemcpyDeviceToHost));
         if (e && P.e64) {
             HIPCHK(ctx, hipMemcpy(e, P.e64, n * sizeof(double), hipMemcpyDeviceToHost));
         } else if (e) {
@@ -934,8 +943,11 @@ int32_t ugkwp_import_state(ugkwp_ctx *ctx, const double *W, const double *P, int
         }
     HIPCHK(ctx, up(D.W, Wt, s));
     HIPCHK(ctx, up(D.P, Pt, s));
-    HIPCHK(ctx, up(D.nleft, cnt, s));
-    HIPCHK(ctx, up(D.segoff[b], seg, s));
+    // every particle in its cell's region, no arrivals
+    std::vector<unsigned long long> off(nc + 1);
+    for (size_t c = 0; c <= nc; ++c) off[c] = (unsigned long long)(uint32_t)seg[c] << 32;
+    HIPCHK(ctx, up(D.off, off, s));
+    HIPCHK(ctx, up(D.v0[b], seg, s));
     std::vector<ugkwp::PRec> rec;
     std::vector<ugkwp::PRec32> rec32;
     std::vector<float> m32;
@@ -975,7 +987,6 @@ int32_t ugkwp_import_state(ugkwp_ctx *ctx, const double *W, const double *P, int
                 HIPCHK(ctx, up(pa.e64, e64, s));
             }
         }
-        HIPCHK(ctx, hipMemcpyAsync(pa.cell, cell, (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice, s));
     }
     // step bookkeeping as after a step: the particles are the old ones of the next step
     Scalars sc;
@@ -983,6 +994,7 @@ int32_t ugkwp_import_state(ugkwp_ctx *ctx, const double *W, const double *P, int
     sc.dtmin_bits = 0x7FF0000000000000ULL;
     sc.n_old = n;
     sc.n_alive = n;
+    sc.span[b] = n;
     sc.step = step[0];
     sc.t = t[0];
     HIPCHK(ctx, hipMemcpyAsync(D.sc, &sc, sizeof(sc), hipMemcpyHostToDevice, s));

@@ -20,9 +20,11 @@ enum : int { kTagTF = 1, kTagPos = 2, kTagVel = 3, kTagWall = 4, kTagInject = 5,
 // internal degrees of freedom supported: gamma = (K + 5)/(K + 3), 0 <= K <= kMaxK
 constexpr int kMaxK = 8;
 
-// bucket key flag: the particle flew collisionless for the whole step without meeting a face
-// (so it ends in the cell it started in, at x + u dt; its record is not rewritten)
-constexpr int32_t kStayBit = 1 << 30;
+// flag of a leaver's source slot: the particle is not one of the step's old ones (it was sampled
+// or entered in this step), so it sorts after every old particle of its bucket
+constexpr uint32_t kNewBit = 1u << 31;
+// flag of an entry's slot in perm: the first of a piece of its bucket that is in order already
+constexpr uint32_t kHeadBit = 1u << 31;
 
 // the neighbour's local face of a slot whose face is periodic: the neighbour's local face lf2
 // and the face's boundary condition b (whose shift a crossing particle takes) as
@@ -69,24 +71,23 @@ struct InstS {
     double avg_res;
 };
 
-// Step scalars of the whole batch, resident in device memory: the host never reads them
-// inside a step.  dt, t and step mirror instance 0.
-// wall queue: segment s takes the particles stopped at diffuse walls by the transport
-// blocks b with b % kWallSeg == s (one counter per segment, not one for the whole grid);
-// a segment holds ceil(blocks / kWallSeg) x (particles per block) entries, so the segments
-// need at most kWallSlack entries beyond the capacity
+// slots over which the blocks spread their counts of crossings and of wall hits (one address for
+// all blocks would make them queue there)
+constexpr int kWallSeg = 64;
+
 // blocks per instance of the averaging kernel (each a contiguous run of its cells)
 constexpr int kAvgBlocks = 64;
 
-constexpr int kWallSeg = 64;
-constexpr long long kWallSlack = (long long)kWallSeg * 1024;
-
+// Step scalars of the whole batch, resident in device memory: the host never reads them
+// inside a step.  dt, t and step mirror instance 0.
 struct Scalars {
     unsigned long long dtmin_bits;  // bit pattern of min Omega/Lambda (positive doubles order as integers)
     double dt;
     double t;
     long long step;
-    long long n_old;      // particles at the start of the step (grouped by cell)
+    long long n_old;      // particles at the start of the step
+    long long n_mov;      // of these, the arrivals of the step before (see Particles)
+    long long span[2];    // slots of the cells' regions in each particle buffer
     long long n_new;      // particles sampled in the step (0 if the capacity check failed)
     long long n_inj;      // free-stream particles entering in the step, stored after the sampled ones
     long long n_alive;    // particles after the step
@@ -95,11 +96,11 @@ struct Scalars {
     unsigned int err;
     unsigned int max_cross;  // the most face crossings of one particle in the step
     unsigned int n_big;      // cells with more than 64 new particles this step (k_sample_big's list)
-    unsigned int pad;
+    unsigned int none;       // the step has no particle anywhere (old, sampled or entering)
 };
 
 // One particle: position, velocity, mass and id in a 64-byte record, so that a particle
-// read from anywhere costs one memory transaction; the cell index lives in its own array.
+// read from anywhere costs one memory transaction.
 struct alignas(64) PRec {
     double x[3];
     double u[3];
@@ -115,11 +116,21 @@ struct alignas(32) PRec32 {
     uint64_t uid;
 };
 
+// Layout of a particle buffer between two steps.  The particles of cell c are, in this order,
+//   its arrivals   places moff(c) .. of the buffer's second part (see below), sorted by source
+//   its stayers    slots v0[c] .. v0[c] + stayers - 1, in the order they had
+// The first part of the buffer, slots [0, span), is cut into one region per cell: v0[c] is the
+// prefix sum of the particles the cells held when the step began (old and sampled), so a stayer
+// can be written there at once, before anything is known about the other cells.  A region's
+// end stays empty where particles left.  The second part holds, one after the other, the
+// arrivals of all cells, then the next step's sampled and entering particles: place a is slot
+// span + a, and when these run past the capacity, the empty slots of the regions in order
+// (slot_of).  The empty slots are as many as the particles that left, so everything fits as
+// long as the particles themselves do.
 struct Particles {
     PRec *rec;      // FP64 form
     PRec32 *rec32;  // FP32 form
     float *m32;     // FP32 form
-    int32_t *cell;
     double *e64;    // internal energy variable |xi|^2 of each particle (K > 0; FP64 form)
     float *e32;     // the same in the FP32 form
 };
@@ -162,9 +173,10 @@ struct Dev {
     int32_t all_box;        // every cell is an axis-aligned box and interior neighbours share whole
                             // faces: tracking needs no cell type, and the box of the cell across a
                             // face is this one's with the bounds along the face's axis moved
+    int32_t all_tet;        // every cell is a tetrahedron
+    int32_t list_sparse;    // the kernels over the cells' lists take more cells per wave
     int32_t recon_any, recon_all;  // some / every instance reconstructs to second order
     int32_t any_diffuse;           // the mesh has a diffuse wall (the wall kernel runs)
-    int32_t count_ch;              // runs of 64 particles per wave of the bucket count (4 or 8)
     const InstP *ip;        // [n_inst]
     InstS *is;              // [n_inst]
     const int32_t *cinst;   // [nc] instance of each cell (n_inst > 1 only)
@@ -172,7 +184,6 @@ struct Dev {
     // state
     double *W;              // [5][nc]
     double *P;              // [5][nc] raw particle sums (W^p = P / Omega)
-    int32_t *nleft;         // [nc]
     // per-step scratch
     double *tau;            // [nc]
     double *ec;             // [nc] exp(-dt/tau)
@@ -187,16 +198,18 @@ struct Dev {
     long long *scan64;      // scan partials
     long long *ninj;        // [nff] particles entering through each far-field face
     long long *injoff;      // [nff+1]
-    int32_t *off;           // [2nc+1]
-    int32_t *scan32;        // scan partials
-    unsigned long long *spart; // [2][64] crossings and wall hits, spread over 64 slots
-    unsigned long long *cnt64; // [2nc] per bucket: stayers << 32 | movers (or collided)
-    int32_t *rank;          // [cap + kWallSlack] slot of a mover / collided particle inside its
-                            // bucket; during transport, the wall queue (kWallSeg segments)
-    unsigned int *wallq;    // [kWallSeg] particles queued in each wall-queue segment
-    int32_t *segoff[2];     // [nc+1] each: survivor segments per cell in pa[0] / pa[1]
-    int32_t *key;           // [cap]
-    int32_t *perm;          // [cap]
+    unsigned long long *off;   // [2nc+1] prefix of the buckets: high word all their particles, low
+                               // word those listed in perm (arrivals, collided from elsewhere)
+    unsigned long long *scan32; // scan partials
+    unsigned long long *spart; // [2][kWallSeg] crossings and wall hits
+    unsigned long long *cnt64; // [2nc] per bucket (survivors ending in c, collided ending in c):
+                               // particles that never left c << 32 | listed ones
+    int32_t *v0[2];         // [nc+1] each: the cells' regions in pa[0] / pa[1]
+    unsigned long long *lrun; // [nc] (aliases nsam) first entry << 32 | length of the cell's list of leavers
+    int32_t *lkey;          // [cap] leavers, per cell from its region's first slot on: end bucket
+    uint32_t *lsrc;         // [cap] the leaver's slot | kNewBit
+    unsigned long long *perm; // [cap] leavers by end bucket: order << 32 | slot; during transport,
+                              // the flight times of the lists' particles
     int32_t *big;           // [nc] cells with more than 64 new particles (listed by k_sample)
     Particles pa[2];
     Scalars *sc;

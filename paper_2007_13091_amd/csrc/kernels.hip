@@ -9,13 +9,14 @@
 //   k_flux(2)      S2  wave flux F^eq + F^{fr,wave} per face                    (Sec. 2.2, 2.4)
 //   k_sample       S3  antithetic Maxwellian pairs, uniform positions; start sums S
 //   k_inject       S5  free-stream particles entering through far-field faces
-//   k_stream       S4+S5 free-flight time and face-to-face transport; end-cell keys;
-//                  particles meeting a diffuse wall stop there and are queued
-//   k_stream_wall  S5  diffuse re-emission of the queued particles, rest of their flight
-//   k_count        bucket sizes (survivors and collided per end cell), slots of movers
+//   k_stream         S4+S5 free-flight times and the flights that meet no face, cell by cell:
+//                  stayers are written to their cell's region of the next buffer and summed,
+//                  the others listed
+//   k_stream_in      S5  flights of the particles entering through far-field faces
+//   k_track        S5  the listed flights, face to face; bucket sizes
 //   scan           exclusive prefix of the bucket sizes
-//   k_scatter      bucket the movers and collided particles by end cell
-//   k_gather       S6  deterministic order per cell, sums E and W^p, update of W
+//   k_scatter      the leavers by end cell
+//   k_gather       S6  arrivals in a fixed order, sums E and W^p, update of W
 //   k_finalize     step bookkeeping
 //   k_avg_cells,   time averaging for steady states, when turned on        (Sec. 2.4(c))
 //   k_avg_fin
@@ -46,10 +47,9 @@ __device__ __forceinline__ void st_nt(uint4 *p, const uint4 &v) {
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4_nt *>(p));
 }
 constexpr int kWave = 64;
-constexpr int kScatterChunks = 8;  // particles per thread in k_scatter
+constexpr int kGatherWaves = 1;    // waves per block in k_gather
 constexpr int kSampleCells = 8;     // consecutive cells per wave in k_sample (meshes of 32768 cells or more)
 constexpr int kSampleCellsMin = 32768;
-constexpr int kGatherWaves = 1;    // cells (waves) per block in k_gather (2 and 4 are slower in FP32)
 
 // ---------------------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror & Shaw, SC'11); counter = (uid, step, tag<<32|sub, 0),
@@ -331,6 +331,36 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
     return v;
 }
 
+// ---------------------------------------------------------------------------------------
+// slots of a particle buffer (layout: see Particles)
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ int hi32(unsigned long long v) { return (int)(v >> 32); }
+__device__ __forceinline__ int lo32(unsigned long long v) { return (int)(v & 0xFFFFFFFFULL); }
+
+// empty slots in the regions of the cells before c
+__device__ __forceinline__ int empty_before(const Dev &D, int b, int c) {
+    const unsigned long long o = D.off[c];
+    return D.v0[b][c] - (hi32(o) - lo32(o));
+}
+// slot of place a >= D.cap - span of the second part of buffer b: the regions' empty slots in order
+__device__ __forceinline__ int empty_slot(const Dev &D, int b, int h) {
+    int lo = 0, hi = D.nc;
+    while (hi - lo > 1) {
+        const int mid = lo + (hi - lo) / 2;
+        if (empty_before(D, b, mid) <= h)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    const unsigned long long o0 = D.off[lo], o1 = D.off[lo + 1];
+    const int stay = (hi32(o1) - lo32(o1)) - (hi32(o0) - lo32(o0));
+    return D.v0[b][lo] + stay + (h - empty_before(D, b, lo));
+}
+// slot of place a of the second part
+__device__ __forceinline__ int slot_of(const Dev &D, int b, long long span, long long a) {
+    return a < D.cap - span ? (int)(span + a) : empty_slot(D, b, (int)(a - (D.cap - span)));
+}
+
 // the step's most crossings of one particle: a block's maximum raises the step's (reset by
 // k_prim_dt); the atomic is issued only when it would change it (the value read first only
 // grows during the step, so a stale read costs at most an extra atomic)
@@ -397,9 +427,8 @@ __global__ void __launch_bounds__(256) k_prim_dt(Dev D) {
         s->max_cross = 0u;
         s->n_big = 0u;
     }
-    if (blockIdx.x == 0 && threadIdx.x < kWallSeg) D.wallq[threadIdx.x] = 0u;
     // partial sums of crossings and wall hits of this step's transport
-    if (blockIdx.x == 0 && threadIdx.x < 128) D.spart[threadIdx.x] = 0ULL;
+    if (blockIdx.x == 0 && threadIdx.x < 2 * kWallSeg) D.spart[threadIdx.x] = 0ULL;
     double r = INFINITY;
     int inst = 0;
     if (c < D.nc) {
@@ -462,7 +491,7 @@ __global__ void __launch_bounds__(256) k_cell_prep(Dev D) {
     const double Pm = D.P[c];
     const double rho = D.W[c];
     const double tau = D.tau[c];
-    const int nleft = D.nleft[c];
+    const int nleft = hi32(D.off[c + 1]) - hi32(D.off[c]);
     // bucket counters of this step's transport (survivors ending in c, collided ending in c)
     D.cnt64[c] = 0ULL;
     D.cnt64[D.nc + c] = 0ULL;
@@ -503,7 +532,7 @@ __global__ void __launch_bounds__(256) k_cell_prep(Dev D) {
 }
 
 // capacity check of the step: old + sampled + entering must fit
-__global__ void k_sample_setup(Dev D) {
+__global__ void k_sample_setup(Dev D, int buf) {
     Scalars *s = D.sc;
     const long long nn = D.samoff[D.nc];
     const long long ni = D.nff > 0 ? D.injoff[D.nff] : 0;
@@ -515,8 +544,12 @@ __global__ void k_sample_setup(Dev D) {
         s->n_new = nn;
         s->n_inj = ni;
     }
+    s->none = s->n_old + s->n_new + s->n_inj == 0 ? 1u : 0u;
     s->n_sampled = (unsigned long long)s->n_new;
     s->n_injected = (unsigned long long)s->n_inj;
+    // the next buffer's regions: a cell's is as long as its old and new particles are many
+    s->span[buf ^ 1] = s->n_old + s->n_new;
+    D.v0[buf ^ 1][D.nc] = (int32_t)(s->n_old + s->n_new);
 }
 
 // Diffuse isothermal wall (Sec. 2.4(e)), first order at the state l (n out of the domain):
@@ -1197,10 +1230,8 @@ __device__ __forceinline__ void store_e(const Particles &pa, long long i, float 
 __device__ __forceinline__ double load_e(const Particles &pa, long long i, double) { return pa.e64[i]; }
 __device__ __forceinline__ float load_e(const Particles &pa, long long i, float) { return pa.e32[i]; }
 
-// Shakhov model (SH): the survivors' raw moments sum m u_i |u|^2 and sum m u_i u_j as well, so
-// that the cell's heat flux for the next step, q = (1/Omega) sum m c |c|^2 / 2 with c = u - U
-// and U from W^{n+1}, follows from them and P^{n+1} by expanding c = u - U (the particles and
-// the state the next step starts from are exactly these)
+// Shakhov model: raw moments sum m u_i |u|^2 and sum m u_i u_j of a cell's particles, from which
+// the cell's heat flux q = (1/Omega) sum m c |c|^2 / 2 with c = u - U follows by expanding c
 template <bool SH>
 __device__ __forceinline__ void add_heat(double m, double u0, double u1, double u2, double H[9]) {
     if constexpr (SH) {
@@ -1241,10 +1272,10 @@ __device__ __forceinline__ double heat_of(const double H[9], const double Wn[5],
 // Shakhov model: the heat flux of the gas in each cell at the start of the step,
 //   q = (1/Omega) sum_k m_k c_k |c_k|^2 / 2,  c_k = u_k - U,  U = (W_1, W_2, W_3) / W_0,
 // over the particles the cell holds (the hydro part, a Maxwellian at the cell's U and T,
-// carries none).  The gather of every step leaves it for the next one; this kernel computes it
-// after the state is set (init_state, import_state), from the raw moments sum m u_i |u|^2 and
-// sum m u_i u_j summed exactly as the gather sums them (lane l the particles s0 + l + 64 k, in
-// increasing k), so that both give the same bits.  One wave per cell.
+// carries none), from the raw moments sum m u_i |u|^2 and sum m u_i u_j: lane l sums the cell's
+// particles l + 64 k in increasing k, arrivals first, so the bits do not depend on where the
+// particles lie (a state that was exported and imported gives the same ones).  One wave per
+// cell, at the end of every step and after the state is set.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void load_um(const Particles &pa, long long i, double u[3], double &m, double) {
     const double2 *r = reinterpret_cast<const double2 *>(pa.rec + i);
@@ -1273,11 +1304,13 @@ __global__ void __launch_bounds__(256) k_heat(Dev D, int buf) {
     const bool sh = D.ip[inst_of(D, c)].pr != 1.0;
     double H[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     if (sh) {
-        const long long s0 = D.segoff[buf][c], s1 = D.segoff[buf][c + 1];
+        const unsigned long long o0 = D.off[c], o1 = D.off[c + 1];
+        const int n = hi32(o1) - hi32(o0), nm = lo32(o1) - lo32(o0), m0 = lo32(o0), v0 = D.v0[buf][c];
+        const long long span = D.sc->span[buf];
         const Particles pa = D.pa[buf];
-        for (long long i = s0 + lane; i < s1; i += kWave) {
+        for (int k = lane; k < n; k += kWave) {
             double u[3], m;
-            load_um(pa, i, u, m, R(0));
+            load_um(pa, k < nm ? slot_of(D, buf, span, m0 + k) : v0 + (k - nm), u, m, R(0));
             add_heat<true>(m, u[0], u[1], u[2], H);
         }
 #pragma unroll
@@ -1354,7 +1387,7 @@ __device__ __forceinline__ void sample_cell(const Dev &D, int buf, int c, long l
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     {
         const Particles pa = D.pa[buf];
-        const long long base = sc->n_old + D.samoff[c];
+        const long long span = sc->span[buf], base = sc->n_mov + D.samoff[c];
         const int inst = inst_of(D, c);
         const InstP &P = D.ip[inst];
         const long long step = D.is[inst].step;
@@ -1411,7 +1444,7 @@ __device__ __forceinline__ void sample_cell(const Dev &D, int buf, int c, long l
             if ((k0 > 0 || !exact) && k < ns) half_normal<R>(seed, make_uid(step, cl, k & ~1LL), step, inst, odd, h0, h1);
             const R X0 = __shfl(h0, lane & ~1), X1 = __shfl(h1, lane & ~1), X2 = __shfl(h0, lane | 1);
             if (k < ns) {
-                const long long i = base + k;
+                const long long i = slot_of(D, buf, span, base + k);
                 const uint64_t uid = make_uid(step, cl, k);
                 const R sg = odd ? -one : one;
                 const R X[3] = {X0, X1, X2};
@@ -1421,7 +1454,6 @@ __device__ __forceinline__ void sample_cell(const Dev &D, int buf, int c, long l
                 R x[3];
                 cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
                 store_new(pa, i, x, u, msam, uid);
-                pa.cell[i] = c;
                 R e = (R)0;
                 if (K > 0) {
                     e = internal_energy<R>(seed, uid, step, kTagInt, 0, inst, K, T);
@@ -1465,9 +1497,9 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int c0 = (blockIdx.x * WPB + wave) * G;
-    if (c0 >= D.nc) return;
-    const int nc = D.nc;
     const Scalars *sc = D.sc;
+    if (c0 >= D.nc || sc->none) return;
+    const int nc = D.nc;
     // new particles of the group's cells; -1 marks a lane without a cell of its own (past the
     // mesh) and a cell of an instance that samples one by one (k_sample_gp's, which also writes
     // its S): neither is sampled nor has S written here
@@ -1571,14 +1603,14 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
             }
             const R X0 = __shfl(h0, lane & ~1), X1 = __shfl(h1, lane & ~1), X2 = __shfl(h0, lane | 1);
             if (act) {
-                const long long base = sc->n_old + D.samoff[c];
+                const long long span = sc->span[buf], base = sc->n_mov + D.samoff[c];
                 const R msam = (R)(D.ec[c] * D.rhoh[c] * D.vol[c] / (double)nsj);
                 const R org[3] = {(R)D.orig[c], (R)D.orig[nc + c], (R)D.orig[2 * nc + c]};
                 R Ed[9];
 #pragma unroll
                 for (int q = 0; q < 9; ++q) Ed[q] = (R)D.edge[q * nc + c];
                 const bool tet = D.ctype[c] == 4;
-                const long long i = base + k;
+                const long long i = slot_of(D, buf, span, base + k);
                 const uint64_t uid = make_uid(step, cl, k);
                 const R sg = odd ? (R)-1 : (R)1;
                 const R X[3] = {X0, X1, X2};
@@ -1588,7 +1620,6 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
                 R x[3];
                 cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
                 store_new(pa, i, x, u, msam, uid);
-                pa.cell[i] = c;
                 R e = (R)0;
                 if (K > 0) {
                     e = internal_energy<R>(seed, uid, step, kTagInt, 0, inst, K, T);
@@ -1653,7 +1684,7 @@ __global__ void __launch_bounds__(256) k_sample_gp(Dev D, int buf) {
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int c = blockIdx.x * 4 + wave;
-    if (c >= D.nc) return;
+    if (c >= D.nc || D.sc->none) return;
     const int nc = D.nc;
     const int inst = inst_of(D, c);
     const InstP &P = D.ip[inst];
@@ -1664,7 +1695,7 @@ __global__ void __launch_bounds__(256) k_sample_gp(Dev D, int buf) {
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (ns > 0) {
         const Particles pa = D.pa[buf];
-        const long long base = sc->n_old + D.samoff[c];
+        const long long span = sc->span[buf], base = sc->n_mov + D.samoff[c];
         const long long step = D.is[inst].step;
         const unsigned long long seed = P.seed;
         const int cl = c - P.cell0;
@@ -1760,11 +1791,10 @@ __global__ void __launch_bounds__(256) k_sample_gp(Dev D, int buf) {
         // particle k: its id, position, record and sums
         auto put = [&](long long k, const R u[3], R e) {
             const uint64_t uid = make_uid(step, cl, k);
-            const long long i = base + k;
+            const long long i = slot_of(D, buf, span, base + k);
             R x[3];
             cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
             store_new(pa, i, x, u, msam, uid);
-            pa.cell[i] = c;
             if (KE) store_e(pa, i, e);
             add_phi<R>(acc, msam, u, e);
         };
@@ -1901,7 +1931,8 @@ __global__ void __launch_bounds__(64) k_inject(Dev D, int buf) {
     const long long n = D.ninj[j];
     if (n <= 0) return;
     const Inflow q = inflow_face(D, j);
-    const long long base = sc->n_old + sc->n_new + D.injoff[j];
+    const long long span = sc->span[buf], base = sc->n_mov + sc->n_new + D.injoff[j];
+    const long long list = sc->n_old + sc->n_new + D.injoff[j];
     const long long step = D.is[q.inst].step;
     const unsigned long long seed = D.ip[q.inst].seed;
     const Particles pa = D.pa[buf];
@@ -1927,9 +1958,10 @@ __global__ void __launch_bounds__(64) k_inject(Dev D, int buf) {
             u[d] = (R)(vn * q.nin[d] + w1 * q.t1[d] + w2 * q.t2[d]);
             x[d] = (R)(g[d] + p1 * g[3 + d] + p2 * g[6 + d]);
         }
-        store_new(pa, base + k, x, u, (R)q.m, uid);
-        pa.cell[base + k] = q.c;
-        if (D.K > 0) store_e(pa, base + k, (R)internal_energy<double>(seed, uid, step, kTagInt, 0, q.inst, D.K, q.T));
+        const long long i = slot_of(D, buf, span, base + k);
+        store_new(pa, i, x, u, (R)q.m, uid);
+        D.lkey[list + k] = q.c;  // its start cell, for k_stream_in
+        if (D.K > 0) store_e(pa, i, (R)internal_energy<double>(seed, uid, step, kTagInt, 0, q.inst, D.K, q.T));
     }
 }
 
@@ -1939,7 +1971,7 @@ __global__ void __launch_bounds__(64) k_inject(Dev D, int buf) {
 // face on a tie; an exit time >= the remaining time keeps the particle in the cell.
 // Box hexes take a path that evaluates only the three candidate faces; its arithmetic is
 // the plane formula (d - n.x) / (n.u) with n = +-e_d, term by term, so both paths give the
-// same bits.  Returns 0 inside (cell updated), 1 escaped through a far-field face, -1 lost.
+// same bits.
 // ---------------------------------------------------------------------------------------
 template <typename R>
 __device__ __forceinline__ const R *cell_box(const Dev &D, int c);
@@ -1997,36 +2029,78 @@ __device__ __forceinline__ void reemit_diffuse(const DevBC &b, const R n[3], R u
     if (e) *e = internal_energy<R>(sx.seed, uid, sx.step, kTagWallInt, 2u * (uint32_t)bounce, sx.inst, K, Tw);
 }
 
+// Decisions on exit times without a division.  The time to a face is tt = max(a, 0) / un (a its
+// distance, un > 0 the speed towards it).  Products decide comparisons of such quotients by a
+// relative margin well above the rounding of either; only values within the margin (or so small
+// that a product could lose precision) are divided, so every decision is the formula's own.
+template <typename R>
+struct Margin;
+template <>
+struct Margin<double> {
+    static constexpr double up = 1.0 + 1e-12, dn = 1.0 - 1e-12, tiny = 1e-280;
+};
+template <>
+struct Margin<float> {
+    static constexpr float up = 1.0f + 1e-5f, dn = 1.0f - 1e-5f, tiny = 1e-30f;
+};
+// whether a flight of time ts meets the face (tt < ts)
+template <typename R>
+__device__ __forceinline__ bool meets_face(R a, R un, R ts) {
+    const R reach = un * ts;
+    if (reach > Margin<R>::tiny) {
+        if (a >= reach * Margin<R>::up) return false;
+        if (a < reach * Margin<R>::dn) return true;
+    }
+    R tt = a / un;
+    if (tt < (R)0) tt = (R)0;
+    return tt < ts;
+}
+// the face with the smallest exit time (the lowest local face on a tie): its distance over speed
+template <typename R>
+struct Exit {
+    R a, un;
+    int lf;
+};
+template <typename R>
+__device__ __forceinline__ void nearer(Exit<R> &b, R a, R un, R reach, int lf) {
+    // a face at distance a >= un trem (1 + margin) has a computed exit time >= trem, so it can
+    // be neither the smallest nor a crossing
+    if (!(un > (R)0) || !(a < reach * Margin<R>::up || reach <= Margin<R>::tiny) || a != a) return;
+    const R ac = a > (R)0 ? a : (R)0;
+    bool take = b.lf < 0;
+    if (!take) {
+        const R l = ac * b.un, r = b.a * un;
+        if (fmax(l, r) > Margin<R>::tiny && (l < r * Margin<R>::dn || l > r * Margin<R>::up))
+            take = l < r;
+        else
+            take = ac / un < b.a / b.un;
+    }
+    b.a = take ? ac : b.a;
+    b.un = take ? un : b.un;
+    b.lf = take ? lf : b.lf;
+}
+
 // Flight of one particle for the time ts from cell `cell`, entered through its local face
 // `entry` (-1: none).  Returns 0 (ends inside the domain), 1 (left through a far-field face)
 // or -1 (more than max_cross crossings); ncross, nwall and bounce (diffuse re-emissions so
-// far, which keys the wall draws) carry on from their values at the call.  With STOP, a
-// diffuse wall ends the call with 2: x is then the wall point, u the incoming velocity,
-// cell the cell at the wall, entry the wall face and ts the time still to fly; the
-// re-emission and the rest of the flight are left to a later call (the wall kernel).
-// ct0 >= 0: the start cell's type and, for a box cell, its bounds B0 (loaded by the caller
-// together with the particle's other start-cell data, so that the first pass does not
-// wait for them).
-template <typename R, bool STOP>
+// far, which keys the wall draws) carry on from their values at the call.  MESH 1: every cell
+// a box and neighbours share whole faces; 2: every cell a tetrahedron; 0: any mesh.  What a
+// crossing costs is the dependent loads of the next cell: one round with MESH 1 (the neighbour
+// and its far bound) and 2 (the neighbour, then its planes with its own neighbours), three
+// with MESH 0.
+template <typename R, int MESH>
 __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry, uint64_t uid, const StepCtx &sx,
-                     int &ncross, int &nwall, int &bounce, int ct0 = -1, const R *B0 = nullptr, R *e = nullptr) {
-    // margin of the exact division skip below: well above the rounding of the products
-    const R skip = sizeof(R) == 8 ? (R)(1.0 + 1e-12) : (R)(1.0f + 1e-5f);
+                     int &ncross, int &nwall, int &bounce, R *e = nullptr) {
     int c = cell;
     R trem = ts;
-    bool first = ct0 >= 0;
     // bounds of box cell c; on conforming boxes a crossing builds them for the next cell
     R B[6];
-    bool haveB = first;
-    if (first) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) B[q] = B0[q];
-    }
+    bool haveB = false;
     for (;;) {
-        R best = (R)INFINITY;
-        int bf = -1;
-        const int ctc = first ? ct0 : (D.all_box ? 8 : (int)D.ctype[c]);
-        if (ctc == 8) {
+        Exit<R> ex{(R)0, (R)1, -1};
+        int2 nb = make_int2(0, 0);
+        const bool box = MESH == 1 || (MESH == 0 && D.ctype[c] == 8);
+        if (box) {
             if (!haveB) {
                 const R *Bg = cell_box<R>(D, c);
 #pragma unroll
@@ -2035,49 +2109,30 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
             }
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                // a face at distance a >= |u_d| trem (1 + margin) has a computed exit time
-                // >= trem, so it can be neither the minimum nor a crossing: no division
-                const R ud = u[d];
-                if (ud > (R)0) {
-                    const R a = B[3 + d] - x[d];
-                    if (2 * d + 1 != entry && !(a >= ud * trem * skip)) {
-                        R tt = a / ud;
-                        if (tt < (R)0) tt = (R)0;
-                        if (tt < best) {
-                            best = tt;
-                            bf = 2 * d + 1;
-                        }
-                    }
-                } else if (ud < (R)0) {
-                    const R a = x[d] - B[d];
-                    if (2 * d != entry && !(a >= (-ud) * trem * skip)) {
-                        R tt = a / (-ud);
-                        if (tt < (R)0) tt = (R)0;
-                        if (tt < best) {
-                            best = tt;
-                            bf = 2 * d;
-                        }
-                    }
-                }
+                const bool up = u[d] > (R)0;
+                const R au = fabs(u[d]), a = up ? B[3 + d] - x[d] : x[d] - B[d];
+                const int lf = 2 * d + (up ? 1 : 0);
+                if (lf != entry) nearer<R>(ex, a, au, au * trem, lf);
             }
         } else {
-            const int nfc = D.nfc[c];
-            for (int lf = 0; lf < nfc; ++lf) {
-                if (lf == entry) continue;
-                R p[4];
-                cell_plane(D, c * 6 + lf, p);
+            R pl[4][4];
+            int2 nbs[4];
+#pragma unroll
+            for (int lf = 0; lf < 4; ++lf) {
+                cell_plane(D, c * 6 + lf, pl[lf]);
+                nbs[lf] = D.nbl[c * 6 + lf];
+            }
+#pragma unroll
+            for (int lf = 0; lf < 4; ++lf) {
+                const R *p = pl[lf];
                 const R un = p[0] * u[0] + p[1] * u[1] + p[2] * u[2];
-                if (un > (R)0) {
-                    R tt = (p[3] - (p[0] * x[0] + p[1] * x[1] + p[2] * x[2])) / un;
-                    if (tt < (R)0) tt = (R)0;
-                    if (tt < best) {
-                        best = tt;
-                        bf = lf;
-                    }
-                }
+                const R a = p[3] - (p[0] * x[0] + p[1] * x[1] + p[2] * x[2]);
+                if (lf != entry) nearer<R>(ex, a, un, un * trem, lf);
+                if (ex.lf == lf) nb = nbs[lf];
             }
         }
-        first = false;
+        const int bf = ex.lf;
+        const R best = ex.a / ex.un;
         if (bf < 0 || best >= trem) {
             x[0] = x[0] + u[0] * trem;
             x[1] = x[1] + u[1] * trem;
@@ -2093,9 +2148,12 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
             cell = c;
             return -1;
         }
-        const int2 nb = D.nbl[c * 6 + bf];
         // the far bound of the next box, loaded together with the neighbour
-        const R far = D.all_box ? face_far<R>(D, c * 6 + bf) : (R)0;
+        R far = (R)0;
+        if (box) {
+            nb = D.nbl[c * 6 + bf];
+            if (MESH == 1) far = face_far<R>(D, c * 6 + bf);
+        }
         if (nb.x >= 0) {
             int ent = nb.y;
             if (ent >= kPeriodicEntry) {
@@ -2106,16 +2164,17 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
                 x[2] = x[2] + (R)pb.shift[2];
                 ent = ent % kPeriodicEntry;
                 haveB = false;
-            } else if (D.all_box) {
+            } else if (MESH == 1) {
                 // the neighbour shares the whole face: its bounds along the face's axis are
                 // this cell's bound at the face and the far one
+                // (selects: an array indexed at run time would live in scratch memory)
                 const int d = bf >> 1;
-                if (bf & 1) {
-                    B[d] = B[3 + d];
-                    B[3 + d] = far;
-                } else {
-                    B[3 + d] = B[d];
-                    B[d] = far;
+                const bool up = (bf & 1) != 0;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const R lo = B[k], hi = B[3 + k];
+                    B[k] = k == d ? (up ? hi : far) : lo;
+                    B[3 + k] = k == d ? (up ? far : lo) : hi;
                 }
             } else {
                 haveB = false;
@@ -2126,10 +2185,11 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
         }
         const DevBC &b = D.bc[-1 - nb.x];
         if (b.type == 0) {
-            if (ctc == 8) {
+            if (box) {
                 // u - 2 (u.n) n with n = +-e_d flips exactly component d
                 const int d = bf >> 1;
-                u[d] = -u[d];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) u[k] = k == d ? -u[k] : u[k];
             } else {
                 R p[4];
                 cell_plane(D, c * 6 + bf, p);
@@ -2140,12 +2200,6 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
             }
             entry = bf;
         } else if (b.type == 1) {
-            if (STOP) {
-                cell = c;
-                ts = trem;
-                entry = bf;
-                return 2;
-            }
             R p[4];
             cell_plane(D, c * 6 + bf, p);
             const R n[3] = {p[0], p[1], p[2]};
@@ -2198,111 +2252,28 @@ __device__ __forceinline__ void store_state(const Particles &pa, long long i, co
     q[0] = make_float2(u[1], u[2]);
 }
 
-// Free flight and transport of the particles, ILP particles per thread (their loads are all
-// issued before the first is tracked, so that each thread keeps ILP memory chains in flight);
-// blocks past the live particles exit at once.  The free-flight time of an old particle is
-// t_f = -tau ln eta with tau of its start cell; it collides iff t_f < dt.  Since t_f < dt <=>
-// eta > exp(-dt/tau), eta below exp(-dt/tau) by a relative margin decides the comparison
-// without the logarithm (the same decision as the formula, which is evaluated near the
-// threshold and for every collided particle).
-// Key of the end bucket: end cell (stays collisionless), nc + end cell (collided), -1
-// (escaped); stayers (collisionless, no face met) carry kStayBit and their records are not
-// stored (the gather advances them), nor are those of escaped particles.
-// A particle that meets a diffuse wall stops there (its state at the wall is stored) and is
-// queued with what its flight still needs (WallCont, kept in the next step's buffer, which
-// is free until the gather); the wall kernel re-emits it and finishes the flight with the
-// same draws and arithmetic.  The re-emission (logarithm, sine, cosine) is thereby kept out
-// of the transport kernel's registers.
-template <typename R>
-struct WallCont {
-    R trem;                   // flight time left at the wall
-    int ncross, bounce;       // crossings so far (the wall included), re-emissions so far
-    int entry, c0, collided;  // wall face, start cell (-1: entered this step), collided flag
-    int cell;                 // cell at the wall
-};
-static_assert(sizeof(WallCont<double>) <= sizeof(PRec) && sizeof(WallCont<float>) <= sizeof(PRec32),
-              "a continuation fits in a particle record");
-template <typename R>
-__device__ __forceinline__ WallCont<R> *wall_cont(const Particles &p, long long i);
-template <>
-__device__ __forceinline__ WallCont<double> *wall_cont<double>(const Particles &p, long long i) {
-    return reinterpret_cast<WallCont<double> *>(p.rec + i);
-}
-template <>
-__device__ __forceinline__ WallCont<float> *wall_cont<float>(const Particles &p, long long i) {
-    return reinterpret_cast<WallCont<float> *>(p.rec32 + i);
-}
-
-// end of a flight: state (unless the caller stores it) and bucket key of particle i (the key
-// carries the end cell; the cell array of this buffer is not read again, the gather writes
-// the next one).  A stayer (kStayBit) flew collisionless for the whole step without meeting
-// any face: its state is x + u dt of its record, which the gather forms itself, so its record
-// is not rewritten here.  Returns whether the record must be stored (every particle that is
-// neither a stayer nor escaped).
-template <typename R, bool STORE>
-__device__ __forceinline__ bool finish_flight(const Dev &D, const Particles &pa, long long i, const R x[3],
-                                              const R u[3], int c, int rc, bool collided, int c0, int ncross,
-                                              bool &lost) {
-    if (STORE) store_state(pa, i, x, u);
-    int key = -1;
-    bool stay = false;
-    if (rc != 1) {
-        lost = lost || rc < 0;
-        key = collided ? D.nc + c : c;
-        stay = !collided && c == c0 && ncross == 0;
-    }
-    D.key[i] = stay ? (key | kStayBit) : key;
-    return rc != 1 && !stay;
-}
-
-template <typename R, bool MULTI, bool STORE>
-__device__ __forceinline__ void stream_one(const Dev &D, const Particles &pa, const Particles &pc, long long i,
-                                           long long n_old, long long n_smp, int c, R x[3], R u[3], uint64_t uid,
-                                           R e, R tauc, unsigned long long &nx_, unsigned &mx_, bool &lost,
-                                           bool &queued, bool &wr, int ct0, const R *B0, int inst_c) {
-    const R lmargin = sizeof(R) == 8 ? (R)(1.0 - 1e-12) : (R)(1.0f - 1e-5f);
-    int c0 = c;
-    // a single instance reads its values through uniform addresses
-    const int inst = MULTI ? inst_c : 0;
-    const InstP &P = D.ip[inst];
-    const double dt64 = D.is[inst].dt;
-    const R dt = (R)dt64;
-    const StepCtx sx{P.seed, D.is[inst].step, inst, P.max_cross};
-    R ts = dt;
-    int entry0 = -1;
-    bool collided = false;
-    if (i >= n_smp) {
-        // entering through a far-field face: from its entry time to the end of the step,
-        // starting on that face; never a stayer (it did not start in a cell)
-        const U4 r = draw(sx.seed, uid, sx.step, kTagInject, 0, inst);
-        ts = (R)(unif<double>(r.v[3]) * dt64);
-        entry0 = D.bflf[P.bf0 + (long long)((uid >> 20) & 0xFFFFFFULL)];
-        c0 = -1;
-    } else if (i < n_old) {
-        const U4 r = draw(sx.seed, uid, sx.step, kTagTF, 0, inst);
-        const R eta = unif<R>(r.v[0]);
-        if (!(eta < e * lmargin)) {
-            const R tf = -tauc * log(eta);
-            if (tf < dt) {
-                ts = tf;
-                collided = true;
-            }
-        }
-    }
-    int nx = 0, nw = 0, bounce = 0;
-    int entry = entry0;
-    const int rc = track<R, true>(D, x, u, c, ts, entry, uid, sx, nx, nw, bounce, ct0, B0);
-    nx_ += (unsigned long long)nx;
-    if (rc == 2) {  // its count goes on in k_stream_wall
-        if (STORE) store_state(pa, i, x, u);
-        *wall_cont<R>(pc, i) = WallCont<R>{ts, nx, bounce, entry, c0, collided ? 1 : 0, c};
-        queued = true;
-        wr = true;
-        return;
-    }
-    mx_ = max(mx_, (unsigned)nx);
-    wr = finish_flight<R, STORE>(D, pa, i, x, u, c, rc, collided, c0, nx, lost);
-}
+// Free flight of a cell's particles by one wave, 64 at a time in the cell's order (arrivals,
+// stayers, new ones).  The free-flight time of an old particle is t_f = -tau ln eta with tau of
+// its start cell; it collides iff t_f < dt.  Since t_f < dt <=> eta > exp(-dt/tau), eta below
+// exp(-dt/tau) by a relative margin decides the comparison without the logarithm (the same
+// decision as the formula, which is evaluated near the threshold and for every collided
+// particle).
+//
+// Every particle is read once here.  A stayer (collisionless, no face met) is written at once,
+// moved by u dt, to its cell's region of the next buffer, whose start is known beforehand
+// (Particles), and summed into P^{n+1}; a particle that collided before it met a face is summed
+// into the cell's part of E and dropped.  The others meet a face: they are put on the cell's
+// list with their slot and flight time, and k_track follows them.
+//
+// What bounds it: the vector ALU (a wave64 instruction holds its SIMD for four cycles), about
+// half of it the Philox draw.  So a face is decided without a division: it is met iff its
+// distance over the normal speed is below the flight time, which the product of speed and time
+// decides by a relative margin well above the rounding; only a particle within the margin takes
+// the quotient itself (the same decision as k_track's formula).  And the tracking loop, which
+// one lane in seven needs, is left to a kernel whose lanes all need it.  One wave per cell: the
+// cell's data (faces, tau, exp(-dt/tau), the instance's constants) are read once, into scalar
+// registers, and the first rounds of the draw, on counter words that do not change within
+// the instance, are scalar too.
 
 // a record as 16-byte chunks
 template <typename R>
@@ -2322,195 +2293,240 @@ __device__ __forceinline__ uint4 *rec_chunks(const Particles &p, long long i, fl
     return reinterpret_cast<uint4 *>(p.rec32 + i);
 }
 
-// the transported state of a lane's particle into its slot of the wave's stage: position and
-// velocity with the mass and id chunk (FP64) or id words (FP32) as loaded
-__device__ __forceinline__ void stage_state(uint4 *slot, const double x[3], const double u[3], const uint4 &tail) {
+// a whole record in registers
+template <typename R>
+struct Part {
+    R x[3], u[3], m, e;
+    uint64_t uid;
+};
+template <bool KE>
+__device__ __forceinline__ void load_part(const Particles &pa, long long i, Part<double> &q) {
+    const double2 *a = reinterpret_cast<const double2 *>(pa.rec + i);
+    const double2 r0 = a[0], r1 = a[1], r2 = a[2], r3 = a[3];
+    q.x[0] = r0.x;
+    q.x[1] = r0.y;
+    q.x[2] = r1.x;
+    q.u[0] = r1.y;
+    q.u[1] = r2.x;
+    q.u[2] = r2.y;
+    q.m = r3.x;
+    q.uid = (uint64_t)__double_as_longlong(r3.y);
+    q.e = KE ? pa.e64[i] : 0.0;
+}
+template <bool KE>
+__device__ __forceinline__ void load_part(const Particles &pa, long long i, Part<float> &q) {
+    const float4 *a = reinterpret_cast<const float4 *>(pa.rec32 + i);
+    const float4 r0 = a[0], r1 = a[1];
+    q.x[0] = r0.x;
+    q.x[1] = r0.y;
+    q.x[2] = r0.z;
+    q.u[0] = r0.w;
+    q.u[1] = r1.x;
+    q.u[2] = r1.y;
+    q.uid = (uint64_t)__float_as_uint(r1.z) | ((uint64_t)__float_as_uint(r1.w) << 32);
+    q.m = pa.m32[i];
+    q.e = KE ? pa.e32[i] : 0.0f;
+}
+// a record into its place in a wave's LDS stage
+__device__ __forceinline__ void stage_part(uint4 *slot, const Part<double> &q) {
     double2 *d = reinterpret_cast<double2 *>(slot);
-    d[0] = make_double2(x[0], x[1]);
-    d[1] = make_double2(x[2], u[0]);
-    d[2] = make_double2(u[1], u[2]);
-    slot[3] = tail;
+    d[0] = make_double2(q.x[0], q.x[1]);
+    d[1] = make_double2(q.x[2], q.u[0]);
+    d[2] = make_double2(q.u[1], q.u[2]);
+    d[3] = make_double2(q.m, __longlong_as_double((long long)q.uid));
 }
-__device__ __forceinline__ void stage_state(uint4 *slot, const float x[3], const float u[3], const uint4 &tail) {
+__device__ __forceinline__ void stage_part(uint4 *slot, const Part<float> &q) {
     float4 *f = reinterpret_cast<float4 *>(slot);
-    f[0] = make_float4(x[0], x[1], x[2], u[0]);
-    f[1] = make_float4(u[1], u[2], __uint_as_float(tail.z), __uint_as_float(tail.w));
+    f[0] = make_float4(q.x[0], q.x[1], q.x[2], q.u[0]);
+    f[1] = make_float4(q.u[1], q.u[2], __uint_as_float((uint32_t)q.uid), __uint_as_float((uint32_t)(q.uid >> 32)));
 }
-// the last 16 bytes of a record as loaded (FP64: mass and id; FP32: u1 u2 and the id words)
-__device__ __forceinline__ uint4 rec_tail(const Particles &pa, long long i, double) {
-    return reinterpret_cast<const uint4 *>(pa.rec + i)[3];
+// the arrays beside the records: mass (FP32 form) and internal energy
+template <bool KE>
+__device__ __forceinline__ void store_side(const Particles &pa, long long i, const Part<double> &q) {
+    if constexpr (KE) pa.e64[i] = q.e;
 }
-__device__ __forceinline__ uint4 rec_tail(const Particles &pa, long long i, float) {
-    return reinterpret_cast<const uint4 *>(pa.rec32 + i)[1];
+template <bool KE>
+__device__ __forceinline__ void store_side(const Particles &pa, long long i, const Part<float> &q) {
+    pa.m32[i] = q.m;
+    if constexpr (KE) pa.e32[i] = q.e;
 }
 
-template <typename R, int BS, bool MULTI, int ILP>
-__global__ void __launch_bounds__(BS) k_stream(Dev D, int buf, long long qseg) {
-    constexpr int NW = BS / 64;
-    constexpr int CPR = RecChunks<R>::N;
-    __shared__ unsigned long long red[2][NW];
-    // output stage: the records of each wave's run, stored whole and coalesced at the end
-    __shared__ uint4 stage[NW][ILP][kWave * CPR];
-    const Scalars *sc = D.sc;
-    const long long n_old = sc->n_old;
-    const long long n_smp = n_old + sc->n_new;
-    const long long n_tot = n_smp + sc->n_inj;
-    const long long i0 = (long long)blockIdx.x * (BS * ILP);
-    if (i0 >= n_tot) return;
-    const Particles pa = D.pa[buf], pc = D.pa[buf ^ 1];
-    unsigned long long nx_ = 0;
-    unsigned mx_ = 0;  // most crossings of one of this lane's particles
-    bool lost = false;
-    long long ii[ILP];
-    int cc[ILP];
-    bool qq[ILP], wr[ILP];
-    uint4 tl[ILP];
-    R xx[ILP][3], uu[ILP][3], ee[ILP], tt[ILP], bx[ILP][6];
-    int ct[ILP], ins[ILP];
-    uint64_t id[ILP];
-#pragma unroll
-    for (int j = 0; j < ILP; ++j) {
-        ii[j] = i0 + j * BS + threadIdx.x;
-        if (ii[j] < n_tot) {
-            cc[j] = pa.cell[ii[j]];
-            load_state(pa, ii[j], xx[j], uu[j], id[j]);
-            tl[j] = rec_tail(pa, ii[j], R(0));
-        }
-    }
-    // start-cell data (e, tau, cell type, box bounds, instance), loaded before the generators
-    // run, all in one round
-#pragma unroll
-    for (int j = 0; j < ILP; ++j)
-        if (ii[j] < n_tot) {
-            ee[j] = (R)D.ec[cc[j]];
-            tt[j] = (R)D.tau[cc[j]];
-            ct[j] = D.all_box ? 8 : (int)D.ctype[cc[j]];
-            ins[j] = MULTI ? D.cinst[cc[j]] : 0;
-            const R *Bg = cell_box<R>(D, cc[j]);
-#pragma unroll
-            for (int q = 0; q < 6; ++q) bx[j][q] = Bg[q];
-        }
-    unsigned long long wm[ILP];
-#pragma unroll
-    for (int j = 0; j < ILP; ++j) {
-        qq[j] = false;
-        wr[j] = false;
-        if (ii[j] < n_tot) {
-            stream_one<R, MULTI, false>(D, pa, pc, ii[j], n_old, n_smp, cc[j], xx[j], uu[j], id[j], ee[j], tt[j], nx_,
-                                        mx_, lost, qq[j], wr[j], ct[j], bx[j], ins[j]);
-            stage_state(&stage[threadIdx.x / kWave][j][lane_id() * CPR], xx[j], uu[j], tl[j]);
-        }
-        wm[j] = __ballot(wr[j]);
-    }
-    // each wave stores the records of its runs that changed (stayers and escaped particles
-    // are skipped), consecutive lanes on consecutive chunks
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-#pragma unroll
-    for (int j = 0; j < ILP; ++j) {
-        const long long wb = i0 + j * BS + (threadIdx.x / kWave) * kWave;  // the run's first record
-        const long long nr = n_tot - wb;
-        const int nch = (nr <= 0 ? 0 : (nr >= kWave ? kWave : (int)nr)) * CPR;
-        uint4 *g = rec_chunks(pa, wb, R(0));
-        for (int k = lane_id(); k < nch; k += kWave)
-            if ((wm[j] >> (k / CPR)) & 1ULL) st_nt(&g[k], stage[threadIdx.x / kWave][j][k]);
-    }
-    // wall queue (held in the rank array, which the bucket count fills only later): this
-    // block's segment, qseg entries from seg * qseg
-    const int lane = lane_id();
-    const unsigned long long below = (lane == 0) ? 0ULL : (~0ULL >> (64 - lane));
-    const int seg = (int)(blockIdx.x % kWallSeg);
-#pragma unroll
-    for (int j = 0; j < ILP; ++j) {
-        const unsigned long long m = __ballot(qq[j]);
-        if (m) {
-            const int first = __ffsll((long long)m) - 1;
-            unsigned int base = 0;
-            if (lane == first) base = atomicAdd(&D.wallq[seg], (unsigned int)__popcll(m));
-            base = __shfl(base, first);
-            if (qq[j]) D.rank[seg * qseg + base + __popcll(m & below)] = (int32_t)ii[j];
-        }
-    }
+// the crossing counts of a block's waves into the step's (called by the whole block)
+template <int NW>
+__device__ __forceinline__ void block_counts(const Dev &D, unsigned long long nx, unsigned long long nw, unsigned mx,
+                                             bool lost, unsigned long long red[3][NW]) {
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
     if (__ballot(lost) && lane == 0) atomicOr(&D.sc->err, kErrLost);
-    nx_ = wave_sum_u64(nx_);
-    mx_ = wave_max_u32(mx_);
-    const int wave = threadIdx.x / kWave;
+    nx = wave_sum_u64(nx);
+    nw = wave_sum_u64(nw);
+    mx = wave_max_u32(mx);
     if (lane == 0) {
-        red[0][wave] = nx_;
-        red[1][wave] = mx_;
+        red[0][wave] = nx;
+        red[1][wave] = nw;
+        red[2][wave] = mx;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long a = 0, m = 0;
+        unsigned long long a = 0, b = 0, m = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             a += red[0][w];
-            m = max(m, red[1][w]);
+            b += red[1][w];
+            m = max(m, red[2][w]);
         }
-        if (a) atomicAdd(&D.spart[blockIdx.x & 63], a);
+        if (a) atomicAdd(&D.spart[blockIdx.x & (kWallSeg - 1)], a);
+        if (b) atomicAdd(&D.spart[kWallSeg + (blockIdx.x & (kWallSeg - 1))], b);
         raise_max_cross(D, (unsigned)m);
     }
 }
 
-// The diffuse re-emissions queued by k_stream and the rest of those flights (further walls
-// re-emitted here directly).  Block b serves queue segment b % kWallSeg in a block-stride
-// loop together with the other gridDim / kWallSeg blocks of that segment.
-template <typename R, bool MULTI, bool KE>
-__global__ void __launch_bounds__(256) k_stream_wall(Dev D, int buf, long long qseg) {
-    __shared__ unsigned long long red[2][4];
-    __shared__ unsigned redm[4];
-    const int seg = (int)(blockIdx.x % kWallSeg);
-    const long long nq = (long long)D.wallq[seg];
-    const long long per = (long long)(gridDim.x / kWallSeg) * 256;
-    const Particles pa = D.pa[buf], pc = D.pa[buf ^ 1];
-    unsigned long long nx_ = 0, nw_ = 0;
-    unsigned mx_ = 0;
-    bool lost = false;
-    for (long long q = (long long)(blockIdx.x / kWallSeg) * 256 + threadIdx.x; q < nq; q += per) {
-        const long long i = D.rank[seg * qseg + q];
-        R x[3], u[3];
-        uint64_t uid;
-        load_state(pa, i, x, u, uid);
-        const WallCont<R> w = *wall_cont<R>(pc, i);
-        int c = w.cell;
-        const int inst = MULTI ? D.cinst[c] : 0;
-        const InstP &P = D.ip[inst];
-        const StepCtx sx{P.seed, D.is[inst].step, inst, P.max_cross};
-        const DevBC &b = D.bc[-1 - D.nbl[c * 6 + w.entry].x];
-        R p[4];
-        cell_plane(D, c * 6 + w.entry, p);
-        const R n[3] = {p[0], p[1], p[2]};
-        R ev = (R)0;
-        R *ep = KE ? &ev : nullptr;
-        reemit_diffuse<R>(b, n, u, uid, sx, w.bounce, ep, KE ? D.K : 0);
-        int nx = w.ncross, nw = 1, bounce = w.bounce + 1;
-        int entry = w.entry;
-        R ts = w.trem;
-        const int rc = track<R, false>(D, x, u, c, ts, entry, uid, sx, nx, nw, bounce, -1, nullptr, ep);
-        if (ep) store_e(pa, i, ev);
-        nx_ += (unsigned long long)(nx - w.ncross);
-        nw_ += (unsigned long long)nw;
-        mx_ = max(mx_, (unsigned)nx);
-        (void)finish_flight<R, true>(D, pa, i, x, u, c, rc, w.collided != 0, w.c0, nx, lost);
+// BS threads per block (a wave per cell), ILP runs of 64 particles loaded together
+template <typename R, int BS, bool MULTI, int ILP, bool KE>
+__device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
+    constexpr int CPR = RecChunks<R>::N, WPB = BS / kWave;
+    __shared__ uint4 stage[WPB][kWave * CPR];  // output stage of each wave
+    const Scalars *sc = D.sc;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    const int c = blockIdx.x * WPB + wave;
+    const int nc = D.nc;
+    if (c >= nc || sc->none) return;
+    const Particles pa = D.pa[buf], pb = D.pa[buf ^ 1];
+    const long long n_new = sc->n_new, span = sc->span[buf], n_mov = sc->n_mov;
+    const unsigned long long o0 = D.off[c], o1 = D.off[c + 1];
+    const long long so = n_new > 0 ? D.samoff[c] : 0;
+    const int ns = n_new > 0 ? (int)(D.samoff[c + 1] - so) : 0;
+    const int nold = hi32(o1) - hi32(o0), nm = lo32(o1) - lo32(o0);
+    const int n = nold + ns;
+    const int v0 = hi32(o0) + (int)so;  // this cell's region of the next buffer
+    const int vs = D.v0[buf][c] - nm;   // slot of an old particle k >= nm: vs + k
+    // places of its arrivals and of its new particles in the second part of this buffer: am + k
+    // for k < nm, an + k for k >= nold
+    const long long am = lo32(o0), an = n_mov + so - nold;
+    const bool wrap = n_mov + n_new > D.cap - span;
+    const int inst = MULTI ? D.cinst[c] : 0;
+    const InstP &P = D.ip[inst];
+    const unsigned long long seed = P.seed;
+    const long long step = D.is[inst].step;
+    const R dt = (R)D.is[inst].dt;
+    const R e = (R)D.ec[c], tauc = (R)D.tau[c];
+    const bool box = D.all_box || D.ctype[c] == 8;
+    // the cell's faces: the bounds of a box, or the planes of a tetrahedron
+    R F[16];
+    if (box) {
+        const R *Bg = cell_box<R>(D, c);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) F[q] = Bg[q];
+    } else {
+#pragma unroll
+        for (int lf = 0; lf < 4; ++lf) cell_plane(D, c * 6 + lf, F + 4 * lf);
     }
-    if (__ballot(lost) && lane_id() == 0) atomicOr(&D.sc->err, kErrLost);
-    nx_ = wave_sum_u64(nx_);
-    nw_ = wave_sum_u64(nw_);
-    mx_ = wave_max_u32(mx_);
-    const int wave = threadIdx.x / kWave;
-    if (lane_id() == 0) {
-        red[0][wave] = nx_;
-        red[1][wave] = nw_;
-        redm[wave] = mx_;
+    const R elow = e * (sizeof(R) == 8 ? (R)(1.0 - 1e-12) : (R)(1.0f - 1e-5f));
+    const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
+    uint4 *st = stage[wave];
+    double Pn[5] = {0, 0, 0, 0, 0}, Cn[5] = {0, 0, 0, 0, 0};
+    int nst = 0, nlv = 0, nco = 0;  // stayers, particles that meet a face, collided here
+    for (int k0 = 0; k0 < n; k0 += ILP * kWave) {
+        Part<R> q[ILP];
+        int slot[ILP];
+#pragma unroll
+        for (int j = 0; j < ILP; ++j) {
+            const int k = k0 + j * kWave + lane;
+            slot[j] = 0;
+            if (k < n) {
+                slot[j] = vs + k;
+                if (k < nm || k >= nold) {
+                    const long long a = (k < nm ? am : an) + k;
+                    slot[j] = wrap ? slot_of(D, buf, span, a) : (int)(span + a);
+                }
+                load_part<KE>(pa, slot[j], q[j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < ILP; ++j) {
+            const int k = k0 + j * kWave + lane;
+            bool meets = false, collided = false;
+            R ts = dt;
+            if (k < n) {
+                if (k < nold) {
+                    const U4 r = draw(seed, q[j].uid, step, kTagTF, 0, inst);
+                    const R eta = unif<R>(r.v[0]);
+                    if (!(eta < elow)) {
+                        const R tf = -tauc * log(eta);
+                        if (tf < dt) {
+                            ts = tf;
+                            collided = true;
+                        }
+                    }
+                }
+                if (box) {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const R ud = q[j].u[d], au = fabs(ud);
+                        const R a = ud > (R)0 ? F[3 + d] - q[j].x[d] : q[j].x[d] - F[d];
+                        if (au > (R)0) meets = meets || meets_face<R>(a, au, ts);
+                    }
+                } else {
+#pragma unroll
+                    for (int lf = 0; lf < 4; ++lf) {
+                        const R *p = F + 4 * lf;
+                        const R un = p[0] * q[j].u[0] + p[1] * q[j].u[1] + p[2] * q[j].u[2];
+                        const R a = p[3] - (p[0] * q[j].x[0] + p[1] * q[j].x[1] + p[2] * q[j].x[2]);
+                        if (un > (R)0) meets = meets || meets_face<R>(a, un, ts);
+                    }
+                }
+            }
+            const bool stay = k < n && !meets && !collided, own = k < n && !meets && collided;
+            const unsigned long long ms = __ballot(stay), ml = __ballot(meets), mo = __ballot(own);
+            const int cs = (int)__popcll(ms);
+            if (stay) {
+                // the transport's last move of a flight that meets no face
+#pragma unroll
+                for (int d = 0; d < 3; ++d) q[j].x[d] = q[j].x[d] + q[j].u[d] * dt;
+                add_phi<R>(Pn, q[j].m, q[j].u, q[j].e);
+                const int rs = (int)__popcll(ms & below);
+                stage_part(st + rs * CPR, q[j]);
+                store_side<KE>(pb, v0 + nst + rs, q[j]);
+            }
+            if (mo && own) add_phi<R>(Cn, q[j].m, q[j].u, q[j].e);
+            if (meets) {
+                const int li = v0 + nlv + (int)__popcll(ml & below);
+                D.lsrc[li] = (uint32_t)slot[j] | (k < nold ? 0u : kNewBit);
+                reinterpret_cast<R *>(D.perm + li)[0] = collided ? -ts : ts;  // (ts > 0)
+            }
+            // the wave's LDS accesses stay in order; consecutive lanes on consecutive chunks
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            uint4 *g = rec_chunks(pb, v0 + nst, R(0));
+            for (int i = lane; i < cs * CPR; i += kWave) st_nt(&g[i], st[i]);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            nst += cs;
+            nlv += (int)__popcll(ml);
+            nco += (int)__popcll(mo);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long a = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        const unsigned long long bw = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-        const int slot64 = blockIdx.x & 63;
-        if (a) atomicAdd(&D.spart[slot64], a);
-        if (bw) atomicAdd(&D.spart[64 + slot64], bw);
-        raise_max_cross(D, max(max(redm[0], redm[1]), max(redm[2], redm[3])));
+    // the stayers' part of P^{n+1}; the gather's E - S is P^{n+1} + (collided elsewhere) - S, so
+    // what collided here comes off S
+    double Pk, Ck;
+    wave_sum_pc(Pn, Cn, Pk, Ck);
+    if (lane < 5) {
+        if (nco) D.S[lane * nc + c] = D.S[lane * nc + c] - Ck;
+        D.P[lane * nc + c] = Pk;
     }
+    if (lane == 0) {
+        D.v0[buf ^ 1][c] = v0;
+        D.lrun[c] = ((unsigned long long)(unsigned)v0 << 32) | (unsigned)nlv;
+        D.cnt64[c] = (unsigned long long)(unsigned)nst << 32;
+        D.cnt64[nc + c] = (unsigned long long)(unsigned)nco << 32;
+    }
+}
+
+template <typename R, int BS, bool MULTI, int ILP>
+__global__ void __launch_bounds__(BS) k_stream(Dev D, int buf) {
+    stream_cells<R, BS, MULTI, ILP, false>(D, buf);
+}
+// the same for a gas with internal degrees of freedom
+template <typename R, int BS, bool MULTI, int ILP>
+__global__ void __launch_bounds__(BS) k_stream_e(Dev D, int buf) {
+    stream_cells<R, BS, MULTI, ILP, true>(D, buf);
 }
 
 // Lanes of a wave grouped by key with ballots only: mine = the lanes that share this lane's
@@ -2519,162 +2535,226 @@ __device__ __forceinline__ unsigned long long key_group(int key) {
     unsigned long long todo = __ballot(key >= 0);
     unsigned long long mine = 0;
     while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int lkey = __shfl(key, leader);
-        const unsigned long long same = __ballot(key == lkey) & todo;
+        const int lkey = __builtin_amdgcn_readlane(key, __ffsll((long long)todo) - 1);
+        const unsigned long long same = __ballot(key == lkey);
         if (key == lkey) mine = same;
         todo &= ~same;
     }
     return mine;
 }
 
-// bucket counts: stayers are only counted, movers and collided particles get their slot in
-// the bucket (the order of those slots is fixed later by sorting in the gather).  A block
-// takes 4 waves x CH runs of 64 consecutive particles and counts them in an LDS
-// hash table keyed by bucket (open addressing, as many entries as the block has particles,
-// so it cannot fill up; entry = stayers << 32 | movers).  Stayers are grouped by ballots
-// (one LDS atomic per group); a mover or collided particle adds itself, and the returned
-// count is its place among the block's particles of that key.  Then one global 64-bit
-// atomic per distinct key of the block adds the block's count to the bucket counter and
-// returns the block's base.  Particles are sorted by start cell, so a block holds a few
-// dozen distinct keys.
-template <int CH>
-__global__ void __launch_bounds__(256) k_count(Dev D) {
-    constexpr int TS = 256 * CH;
-    constexpr int LOG_TS = __builtin_ctz(TS);
-    static_assert((TS & (TS - 1)) == 0, "hash table size must be a power of two");
-    __shared__ int tkey[TS];
-    __shared__ unsigned long long tcnt[TS];
+// bucket counts: one atomic per end bucket of a run (the particles of a run end in a handful of
+// cells; an atomic per particle queues at those few addresses: 129 against 33 us in the scatter
+// of a cavity of 32^3 cells with 400 particles each)
+__device__ __forceinline__ void count_run(const Dev &D, int key) {
+    const unsigned long long mine = key_group(key);
+    if (mine && lane_id() == __ffsll((long long)mine) - 1) atomicAdd(&D.cnt64[key], (unsigned long long)__popcll(mine));
+}
+
+// Lists of G consecutive cells taken by one wave as if they were one: lane j < G holds cell j's
+// first entry and length; entry t of all of them is entry k of cell j.
+template <int G>
+struct Runs {
+    int first[G], pre[G + 1];
+    __device__ __forceinline__ Runs(int my_first, int my_len) {
+        pre[0] = 0;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            first[j] = __builtin_amdgcn_readlane(my_first, j);
+            pre[j + 1] = pre[j] + __builtin_amdgcn_readlane(my_len, j);
+        }
+    }
+    // cell j of entry t < pre[G] and where its list entry lies
+    __device__ __forceinline__ int find(int t, int &j) const {
+        int l = first[0] + t;
+        j = 0;
+#pragma unroll
+        for (int i = 1; i < G; ++i)
+            if (t >= pre[i]) {
+                j = i;
+                l = first[i] + (t - pre[i]);
+            }
+        return l;
+    }
+};
+// Cells per wave of the kernels over the lists and buckets (host: list_cells).  A list holds
+// some 15% of a box cell's particles and some 30% of a tetrahedron's, so with tens of particles
+// per cell eight lists fill the lanes that one leaves idle (tetrahedra, N_ref 50: 178 against
+// 742 us in k_track, 106 against 291 us in the gather), while with hundreds two lists are
+// enough and eight leave too few waves (box cells, N_ref 400: 216 against 261 us).  A small mesh
+// has few waves anyway and takes two.
+constexpr int kListCellsSparse = 8, kListCellsDense = 2;
+
+// S5: the flights that meet a face: the moved state goes back to the particle's slot, its end
+// bucket (end cell, or nc + end cell for a collided one, -1 for one that left through a
+// far-field face) to its cell's list and into the bucket counts.  Diffuse walls re-emit here.
+// One wave takes the lists of G consecutive cells.  What bounds it: the chain of dependent
+// loads at each crossing, so the lanes are kept full.
+template <typename R, bool KE, int MESH, int G>
+__global__ void __launch_bounds__(256) k_track(Dev D, int buf) {
+    constexpr int CPR = RecChunks<R>::N;
+    __shared__ unsigned long long red[3][4];
+    __shared__ uint4 stage[4][kWave * CPR];
+    __shared__ int lslot[4][kWave];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    const int c0 = (blockIdx.x * 4 + wave) * G;
+    const Particles pa = D.pa[buf];
+    unsigned long long nx_ = 0, nw_ = 0;
+    unsigned mx_ = 0;
+    bool lost = false;
+    if (c0 < D.nc && !D.sc->none) {
+        const unsigned long long run = lane < G && c0 + lane < D.nc ? D.lrun[c0 + lane] : 0ULL;
+        const Runs<G> L(hi32(run), lo32(run));
+        const int n = L.pre[G];
+        uint4 *st = stage[wave];
+        int *ls = lslot[wave];
+        for (int k0 = 0; k0 < n; k0 += kWave) {
+            const int k = k0 + lane, nr = min(kWave, n - k0);
+            int key = -1, li = 0;
+            if (k < n) {
+                int j;
+                li = L.find(k, j);
+                const int slot = (int)(D.lsrc[li] & ~kNewBit);
+                R ts = reinterpret_cast<const R *>(D.perm + li)[0];
+                int ec = c0 + j;
+                const int inst = inst_of(D, ec);
+                Part<R> q;
+                load_part<KE>(pa, slot, q);
+                const InstP &P = D.ip[inst];
+                const StepCtx sx{P.seed, D.is[inst].step, inst, P.max_cross};
+                const bool collided = ts < (R)0;  // the sign carries it
+                ts = fabs(ts);
+                int entry = -1, nx = 0, nw = 0, bounce = 0;
+                const int rc = track<R, MESH>(D, q.x, q.u, ec, ts, entry, q.uid, sx, nx, nw, bounce, KE ? &q.e : nullptr);
+                nx_ += (unsigned long long)nx;
+                nw_ += (unsigned long long)nw;
+                mx_ = max(mx_, (unsigned)nx);
+                lost = lost || rc < 0;
+                if (rc != 1) key = collided ? D.nc + ec : ec;
+                if (KE && nw > 0) store_e(pa, slot, q.e);
+                ls[lane] = slot;
+                stage_part(st + lane * CPR, q);
+            }
+            // whole records, consecutive lanes on consecutive chunks
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            for (int i = lane; i < nr * CPR; i += kWave) rec_chunks(pa, ls[i / CPR], R(0))[i % CPR] = st[i];
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            if (k < n) D.lkey[li] = key;
+            count_run(D, key);
+        }
+    }
+    block_counts<4>(D, nx_, nw_, mx_, lost, red);
+}
+
+// The particles entering through far-field faces, one per thread: from its entry time to the
+// end of the step, starting on that face; never a stayer (it did not start in a cell) and
+// never collided.  Diffuse walls re-emit here directly.  Their list is one for all of them,
+// after the cells' lists.
+template <typename R, bool KE, int MESH>
+__global__ void __launch_bounds__(256) k_stream_in(Dev D, int buf) {
+    __shared__ unsigned long long red[3][4];
     const Scalars *sc = D.sc;
-    const long long n_tot = sc->n_old + sc->n_new + sc->n_inj;
-    const long long b0 = (long long)blockIdx.x * TS;
-    if (b0 >= n_tot) return;
+    const long long n = sc->n_inj, l0 = sc->n_old + sc->n_new, a0 = sc->n_mov + sc->n_new, span = sc->span[buf];
+    const Particles pa = D.pa[buf];
+    unsigned long long nx_ = 0, nw_ = 0;
+    unsigned mx_ = 0;
+    bool lost = false;
+    for (long long i0 = (long long)blockIdx.x * 256; i0 < n; i0 += (long long)gridDim.x * 256) {
+        const long long i = i0 + threadIdx.x;
+        int key = -1;
+        if (i < n) {
+            const int slot = slot_of(D, buf, span, a0 + i);
+            int c = D.lkey[l0 + i];
+            const int inst = inst_of(D, c);
+            const InstP &P = D.ip[inst];
+            const StepCtx sx{P.seed, D.is[inst].step, inst, P.max_cross};
+            Part<R> q;
+            load_part<KE>(pa, slot, q);
+            const U4 r = draw(sx.seed, q.uid, sx.step, kTagInject, 0, inst);
+            R ts = (R)(unif<double>(r.v[3]) * D.is[inst].dt);
+            int entry = D.bflf[P.bf0 + (long long)((q.uid >> 20) & 0xFFFFFFULL)];
+            int nx = 0, nw = 0, bounce = 0;
+            const int rc = track<R, MESH>(D, q.x, q.u, c, ts, entry, q.uid, sx, nx, nw, bounce,
+                                                KE ? &q.e : nullptr);
+            nx_ += (unsigned long long)nx;
+            nw_ += (unsigned long long)nw;
+            mx_ = max(mx_, (unsigned)nx);
+            lost = lost || rc < 0;
+            store_state(pa, slot, q.x, q.u);
+            if (KE) store_e(pa, slot, q.e);
+            key = rc == 1 ? -1 : c;
+            D.lkey[l0 + i] = key;
+            D.lsrc[l0 + i] = (uint32_t)slot | kNewBit;
+        }
+        if (key >= 0) atomicAdd(&D.cnt64[key], 1ULL);
+    }
+    block_counts<4>(D, nx_, nw_, mx_, lost, red);
+}
+
+// the leavers by end bucket: each group of one key takes its places from the bucket's counter,
+// which counts down (the order inside a bucket is fixed later by the gather).  An entry is the
+// leaver's order (its place in the lists, new particles after old ones) and its slot.  A group's
+// places are consecutive, its orders ascending, and, old and new particles apart, no order of
+// another group lies between its first and its last; kHeadBit marks where such a piece begins.
+__device__ __forceinline__ void scatter_run(const Dev &D, int li, int key, uint32_t src) {
+    const unsigned long long mine = key_group(key);
     const int lane = lane_id();
-    const long long w0 = b0 + (long long)(threadIdx.x / kWave) * (kWave * CH);
-    for (int h = threadIdx.x; h < TS; h += 256) {
-        tkey[h] = -1;
-        tcnt[h] = 0ULL;
+    const unsigned long long fresh = __ballot((src & kNewBit) != 0);
+    const int leader = mine ? __ffsll((long long)mine) - 1 : lane;
+    const int n = (int)__popcll(mine);
+    int at = 0;
+    if (mine && lane == leader) at = lo32(atomicAdd(&D.cnt64[key], 0ULL - (unsigned long long)n)) - n;
+    at = __shfl(at, leader);
+    if (mine) {
+        const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
+        const unsigned long long before = mine & below;
+        const long long j = (long long)lo32(D.off[key]) + at + (int)__popcll(before);
+        const int prev = 63 - __clzll((long long)before);  // the group's lane before this one
+        const bool head = before == 0 || ((fresh >> prev) & 1ULL) != ((fresh >> lane) & 1ULL);
+        D.perm[j] = ((unsigned long long)((uint32_t)li | (src & kNewBit)) << 32) | (src & ~kNewBit) | (head ? kHeadBit : 0u);
     }
-    int key[CH];
-    bool stay[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const long long i = w0 + j * kWave + lane;
-        const int kraw = i < n_tot ? D.key[i] : -1;
-        stay[j] = kraw >= 0 && (kraw & kStayBit) != 0;
-        key[j] = kraw >= 0 ? (kraw & ~kStayBit) : -1;
-    }
-    __syncthreads();
-    int slot[CH];
-    unsigned int local[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        // stayers (most lanes, usually one or two keys per run): grouped by ballots, each
-        // group's leader counts the group in the high word of its key's entry
-        const unsigned long long mine = key_group(stay[j] ? key[j] : -1);
-        const int leader = mine ? __ffsll((long long)mine) - 1 : lane;
-        const bool lead = mine && lane == leader;
-        // movers and collided particles (mostly distinct keys within a run): each lane on its
-        // own entry, whose low word hands out its place among the block's particles of the key
-        slot[j] = -1;
-        local[j] = 0;
-        if (lead || (key[j] >= 0 && !stay[j])) {
-            int sl = -1;
-            unsigned int h = ((unsigned int)key[j] * 0x9E3779B1u) >> (32 - LOG_TS);
-            for (int probe = 0; probe < TS; ++probe) {
-                const int k = atomicCAS(&tkey[h], -1, key[j]);
-                if (k == -1 || k == key[j]) {
-                    sl = (int)h;
-                    break;
-                }
-                h = (h + 1) & (unsigned int)(TS - 1);
-            }
-            // always found: distinct keys <= particles of the block = TS
-            if (sl < 0) {
-                atomicOr(&D.sc->err, kErrLost);
-            } else if (stay[j]) {
-                atomicAdd(&tcnt[sl], (unsigned long long)__popcll(mine) << 32);
-            } else {
-                slot[j] = sl;
-                local[j] = (unsigned int)(atomicAdd(&tcnt[sl], 1ULL) & 0xFFFFFFFFULL);
-            }
-        }
-    }
-    __syncthreads();
-    // block totals into the buckets; the entry's count is replaced by the block's base (all
-    // of a thread's atomics are issued before the first result is waited for)
-    {
-        constexpr int PT = TS / 256;
-        int hk[PT];
-        unsigned long long hv[PT];
-#pragma unroll
-        for (int q = 0; q < PT; ++q) {
-            hk[q] = tkey[q * 256 + threadIdx.x];
-            hv[q] = tcnt[q * 256 + threadIdx.x];
-        }
-#pragma unroll
-        for (int q = 0; q < PT; ++q)
-            if (hk[q] >= 0) hv[q] = atomicAdd(&D.cnt64[hk[q]], hv[q]);
-#pragma unroll
-        for (int q = 0; q < PT; ++q)
-            if (hk[q] >= 0) tcnt[q * 256 + threadIdx.x] = hv[q];
-    }
-    __syncthreads();
-    unsigned long long base[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) base[j] = tcnt[slot[j] >= 0 ? slot[j] : 0];
-#pragma unroll
-    for (int j = 0; j < CH; ++j)
-        if (key[j] >= 0 && !stay[j] && slot[j] >= 0)
-            D.rank[w0 + j * kWave + lane] = (int)(base[j] & 0xFFFFFFFFULL) + (int)local[j];
 }
-
-// bucket the movers (collisionless particles that changed cell) and the collided particles:
-// perm[off[key] + rank] = i (cnt holds their number per bucket); stayers are collected by
-// the gather from their own segment.  kScatterChunks particles per thread, strided by the
-// block; their loads are issued before the first store.
+template <int G>
 __global__ void __launch_bounds__(256) k_scatter(Dev D) {
-    constexpr int CH = kScatterChunks;
+    const int lane = lane_id();
+    const int c0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))) * G;
+    if (c0 >= D.nc || D.sc->none) return;
+    const unsigned long long run = lane < G && c0 + lane < D.nc ? D.lrun[c0 + lane] : 0ULL;
+    const Runs<G> L(hi32(run), lo32(run));
+    for (int k0 = 0; k0 < L.pre[G]; k0 += kWave) {
+        int j, li = 0, key = -1;
+        uint32_t src = 0;
+        if (k0 + lane < L.pre[G]) {
+            li = L.find(k0 + lane, j);
+            key = D.lkey[li];
+            src = D.lsrc[li];
+        }
+        scatter_run(D, li, key, src);
+    }
+}
+// the same for the list of the particles that entered
+__global__ void __launch_bounds__(256) k_scatter_in(Dev D) {
     const Scalars *sc = D.sc;
-    const long long n_tot = sc->n_old + sc->n_new + sc->n_inj;
-    const long long b0 = (long long)blockIdx.x * (256 * CH);
-    if (b0 >= n_tot) return;
-    int key[CH], dst[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const long long i = b0 + j * 256 + threadIdx.x;
-        key[j] = i < n_tot ? D.key[i] : -1;
+    const int l0 = (int)(sc->n_old + sc->n_new), n = (int)sc->n_inj, lane = lane_id();
+    for (int k0 = (int)(blockIdx.x * 256 + threadIdx.x - lane); k0 < n; k0 += (int)(gridDim.x * 256)) {
+        const int li = l0 + k0 + lane;
+        scatter_run(D, li, k0 + lane < n ? D.lkey[li] : -1, k0 + lane < n ? D.lsrc[li] : 0u);
     }
-    // the offsets and ranks of all chunks in flight together: a particle that is not bucketed
-    // here reads entry 0 of both (a line the wave shares) and discards it
-    int o[CH], r[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const bool mv = key[j] >= 0 && !(key[j] & kStayBit);
-        o[j] = D.off[mv ? key[j] : 0];
-        r[j] = D.rank[mv ? b0 + j * 256 + threadIdx.x : 0];
-    }
-#pragma unroll
-    for (int j = 0; j < CH; ++j) dst[j] = (key[j] >= 0 && !(key[j] & kStayBit)) ? o[j] + r[j] : -1;
-#pragma unroll
-    for (int j = 0; j < CH; ++j)
-        if (dst[j] >= 0) D.perm[dst[j]] = (int32_t)(b0 + j * 256 + threadIdx.x);
 }
 
-// ---------------------------------------------------------------------------------------
-// Sort by one wave of a short list of distinct ints, ascending.  Bitonic network whose
-// comparators all put the smaller value first, so entries past len behave as +infinity and
-// are never touched.  a may point to LDS or to global memory; only this wave touches it.
-// ---------------------------------------------------------------------------------------
 // orders this wave's LDS and global accesses (its lanes run together: no barrier needed)
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ void wave_sort(int *a, int len) {
+// ---------------------------------------------------------------------------------------
+// Sort by one wave of a list of distinct values, ascending.  Bitonic network whose
+// comparators all put the smaller value first, so entries past len behave as +infinity and
+// are never touched.  a may point to LDS or to global memory; only this wave touches it.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void wave_sort(unsigned long long *a, int len) {
     constexpr int BS = kWave;
-    if (len < 2) return;
     const int lane = lane_id();
     int bad = 0;
     for (int i = lane; i + 1 < len; i += BS) bad |= a[i] > a[i + 1];
@@ -2682,25 +2762,13 @@ __device__ void wave_sort(int *a, int len) {
     int N = 1;
     while (N < len) N <<= 1;
     for (int k = 2; k <= N; k <<= 1) {
-        const int h = k >> 1;
-        for (int p = lane; p < N / 2; p += BS) {
-            const int i = (p / h) * k + (p % h);
-            const int j = i ^ (k - 1);
-            if (j < len) {
-                int ai = a[i], aj = a[j];
-                if (ai > aj) {
-                    a[i] = aj;
-                    a[j] = ai;
-                }
-            }
-        }
-        wave_sync();
-        for (int j = h >> 1; j > 0; j >>= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const bool flip = j == (k >> 1);
             for (int p = lane; p < N / 2; p += BS) {
-                const int i = (p / j) * 2 * j + (p % j);
-                const int q = i + j;
+                const int i = 2 * (p & ~(j - 1)) + (p & (j - 1));
+                const int q = flip ? (i ^ (k - 1)) : i + j;
                 if (q < len) {
-                    int ai = a[i], aq = a[q];
+                    const unsigned long long ai = a[i], aq = a[q];
                     if (ai > aq) {
                         a[i] = aq;
                         a[q] = ai;
@@ -2712,359 +2780,262 @@ __device__ void wave_sort(int *a, int len) {
     }
 }
 
-
-
-// ---------------------------------------------------------------------------------------
-// S6 helpers: records of the gather (k_gather below)
-// ---------------------------------------------------------------------------------------
-// add phi of a record without copying it (collided particles).  KE: the particles carry an
-// internal energy (K > 0); the monatomic instantiations leave it out at compile time, which
-// keeps their register counts (and occupancy) those of a kernel without it.
-template <bool KE>
-__device__ __forceinline__ void add_rec(const Particles &src, int s, double acc[5], double) {
-    const double2 *a = reinterpret_cast<const double2 *>(src.rec + s);
-    const double2 r1 = a[1], r2 = a[2], r3 = a[3];
-    const double u[3] = {r1.y, r2.x, r2.y};
-    if constexpr (KE)
-        add_phi<double>(acc, r3.x, u, src.e64[s]);
-    else
-        add_phi<double>(acc, r3.x, u);
-}
-template <bool KE>
-__device__ __forceinline__ void add_rec(const Particles &src, int s, double acc[5], float) {
-    const float4 *a = reinterpret_cast<const float4 *>(src.rec32 + s);
-    const float4 r0 = a[0], r1 = a[1];
-    const float u[3] = {r0.w, r1.x, r1.y};
-    if constexpr (KE)
-        add_phi<float>(acc, src.m32[s], u, src.e32[s]);
-    else
-        add_phi<float>(acc, src.m32[s], u);
-}
-
-// a whole record in registers, so that several loads can be in flight before the stores
-// (scalar arrays: kept in registers, where structs of vectors went to scratch)
-struct Rec64 {
-    double v[8];  // x0 x1 | x2 u0 | u1 u2 | m id
-    double e;     // internal energy variable (K > 0)
-};
-struct Rec32 {
-    float v[9];  // x0 x1 x2 u0 | u1 u2 id.lo id.hi, then m
-    float e;
-};
-template <typename R>
-struct RecOf;
-template <>
-struct RecOf<double> {
-    using T = Rec64;
-};
-template <>
-struct RecOf<float> {
-    using T = Rec32;
-};
-template <bool KE>
-__device__ __forceinline__ void load_rec(const Particles &src, int s, Rec64 &q) {
-    const double2 *a = reinterpret_cast<const double2 *>(src.rec + s);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double2 t = a[k];
-        q.v[2 * k] = t.x;
-        q.v[2 * k + 1] = t.y;
-    }
-    if constexpr (KE) q.e = src.e64[s];
-}
-template <bool KE>
-__device__ __forceinline__ void load_rec(const Particles &src, int s, Rec32 &q) {
-    const float4 *a = reinterpret_cast<const float4 *>(src.rec32 + s);
-    const float4 t0 = a[0], t1 = a[1];
-    q.v[0] = t0.x;
-    q.v[1] = t0.y;
-    q.v[2] = t0.z;
-    q.v[3] = t0.w;
-    q.v[4] = t1.x;
-    q.v[5] = t1.y;
-    q.v[6] = t1.z;
-    q.v[7] = t1.w;
-    q.v[8] = src.m32[s];
-    if constexpr (KE) q.e = src.e32[s];
-}
-// Staged output: a lane adds phi of its record, puts the record into its slot of the wave's
-// LDS stage and writes the small per-particle arrays (cell; FP32: mass) itself; then the wave
-// stores the run of staged records with consecutive lanes on consecutive 16-byte chunks, a
-// few whole cache lines per instruction instead of a 16-byte piece of 64 lines.
-template <bool KE>
-__device__ __forceinline__ void stage_rec(const Particles &dst, int o, int c, const Rec64 &q, double acc[5],
-                                          uint4 *slot) {
-    const double u[3] = {q.v[3], q.v[4], q.v[5]};
-    if constexpr (KE)
-        add_phi<double>(acc, q.v[6], u, q.e);
-    else
-        add_phi<double>(acc, q.v[6], u);
-    double2 *b = reinterpret_cast<double2 *>(slot);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) b[k] = make_double2(q.v[2 * k], q.v[2 * k + 1]);
-    dst.cell[o] = c;
-    if constexpr (KE) dst.e64[o] = q.e;
-}
-template <bool KE>
-__device__ __forceinline__ void stage_rec(const Particles &dst, int o, int c, const Rec32 &q, double acc[5],
-                                          uint4 *slot) {
-    const float u[3] = {q.v[3], q.v[4], q.v[5]};
-    if constexpr (KE)
-        add_phi<float>(acc, q.v[8], u, q.e);
-    else
-        add_phi<float>(acc, q.v[8], u);
-    float4 *b = reinterpret_cast<float4 *>(slot);
-    b[0] = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
-    b[1] = make_float4(q.v[4], q.v[5], q.v[6], q.v[7]);
-    dst.m32[o] = q.v[8];
-    dst.cell[o] = c;
-    if constexpr (KE) dst.e32[o] = q.e;
-}
-// a stayer's state at the end of the step: x + u dt (its record holds the start of the step;
-// the same arithmetic as the transport's last move of a flight that meets no face)
-__device__ __forceinline__ void advance(Rec64 &q, double dt) {
-    q.v[0] = q.v[0] + q.v[3] * dt;
-    q.v[1] = q.v[1] + q.v[4] * dt;
-    q.v[2] = q.v[2] + q.v[5] * dt;
-}
-__device__ __forceinline__ void advance(Rec32 &q, float dt) {
-    q.v[0] = q.v[0] + q.v[3] * dt;
-    q.v[1] = q.v[1] + q.v[4] * dt;
-    q.v[2] = q.v[2] + q.v[5] * dt;
-}
-
-// the wave's n staged records to dst from record o0 on (called by the whole wave; the fences
-// order this wave's LDS accesses, which the hardware performs in order)
-template <typename R>
-__device__ __forceinline__ void stage_out(const uint4 *st, const Particles &dst, int o0, int n) {
-    constexpr int CPR = RecChunks<R>::N;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    uint4 *g = rec_chunks(dst, o0, R(0));
-    for (int k = lane_id(); k < n * CPR; k += kWave) st_nt(&g[k], st[k]);
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-// ---------------------------------------------------------------------------------------
-// S6: one wave per cell c.  The survivors ending in c are laid out in the next buffer as
-//   [movers into c, ascending source index] [stayers of c, in their segment order]
-// where stayers (collisionless for the whole step without meeting a face: advanced here by
-// u dt) are found by scanning c's own start segments (old particles, then the ones sampled
-// this step) and movers (every other survivor, including one that came back to its start
-// cell after a wall) come bucketed by k_scatter.  Sums over survivors give P^{n+1}; with the
-// collided particles ending in c they give E; then W^{n+1} = W^n + (-sum_f s_f Phi_f + E - S) /
-// Omega.  Fixed per-lane assignment and reduction tree: bitwise reproducible.
-// ---------------------------------------------------------------------------------------
-// The sums follow the output positions: the survivor at position base + l + 64 k is summed by
-// lane l, in increasing k, which is the order in which k_heat sums the same particles (so that
-// a state imported between steps gets the heat flux the gather would have left, bit for bit).
-// After a run of n records is stored from the stage to positions o0.., lane l takes the staged
-// record at index (l - (o0 - base)) mod 64.  FP32: the masses are staged beside the records.
-__device__ __forceinline__ void stage_mass(float *stm, int k, const Rec64 &) {}
-__device__ __forceinline__ void stage_mass(float *stm, int k, const Rec32 &q) { stm[k] = q.v[8]; }
-template <typename R>
-__device__ __forceinline__ void heat_from_stage(const uint4 *st, const float *stm, int r, int n, double H[9]) {
-    const int kk = (lane_id() - r) & (kWave - 1);
-    if (kk < n) {
-        if constexpr (sizeof(R) == 8) {
-            const double2 *a = reinterpret_cast<const double2 *>(st + kk * 4);
-            add_heat<true>(a[3].x, a[1].y, a[2].x, a[2].y, H);
-        } else {
-            const float4 *a = reinterpret_cast<const float4 *>(st + kk * 2);
-            add_heat<true>((double)stm[kk], (double)a[0].w, (double)a[1].x, (double)a[1].y, H);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-template <typename R, int WPB, bool KE, bool SH>
-__device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
-    constexpr int BS = kWave;
-    constexpr int kLds = 256;  // longer source lists are sorted in place in global memory
-    constexpr int CPR = RecChunks<R>::N;
-    __shared__ int lds_all[WPB][kLds];
-    __shared__ uint4 st_all[WPB][kWave * CPR];
-    __shared__ float stm_all[WPB][SH ? kWave : 1];  // staged FP32 masses (heat sums)
-    // WPB waves per block, one cell each, independent of one another (no block barrier).
-    // Blocks go round-robin to the 8 XCDs; give each XCD a contiguous range of cells so
-    // that neighbouring cells (whose particles are exchanged) share an L2
-    const int G = (int)gridDim.x, bidx = (int)blockIdx.x;
-    const int xcd = bidx & 7, q = G >> 3, rr = G & 7;
-    const int wave = (int)(threadIdx.x / kWave);
-    const int c = (xcd * q + (xcd < rr ? xcd : rr) + (bidx >> 3)) * WPB + wave;
-    const int nc = D.nc, nf = D.nf;
-    if (c >= nc) return;
-    int *lds = lds_all[wave];
-    uint4 *st = st_all[wave];
-    float *stm = stm_all[wave];
+// A bucket of 64 < n <= 256 entries sorted into lds, by its pieces (kHeadBit) if they are at most
+// 64: a piece stays together, behind the pieces whose first order is smaller.  tab: local memory
+// for 64 pieces.
+__device__ __forceinline__ void sort_pieces(const unsigned long long *a, int n, unsigned long long *lds,
+                                            unsigned long long *tab) {
     const int lane = lane_id();
-    const Particles src = D.pa[buf], dst = D.pa[buf ^ 1];
-    const Scalars *sc = D.sc;
-    // every per-cell scalar in one round of independent loads
-    const int base = D.off[c], bend = D.off[c + 1];
-    const int nmov = (int)(D.cnt64[c] & 0xFFFFFFFFULL);
-    const int cb0 = D.off[nc + c], cb1 = D.off[nc + c + 1];
-    const long long s00 = D.segoff[buf][c], s01 = D.segoff[buf][c + 1];
-    const long long n_old = sc->n_old, n_new = sc->n_new;
-    const long long s10 = n_old + D.samoff[c], s11 = n_old + D.samoff[c + 1];
-    const int nfc = D.nfc[c];
-    // face fluxes of this cell, lane k < 5 owns component k: acc_k = -sum_f s_f Phi_f,k
-    const int code = lane < nfc ? D.cface[c * 6 + lane] : 0;
-    double facc = 0.0;
-    {
-        int codes[6];
+    const unsigned long long upto = ~0ULL >> (63 - lane);
+    unsigned long long v[4], heads[4];
+    int H = 0;
 #pragma unroll
-        for (int lf = 0; lf < 6; ++lf) codes[lf] = __shfl(code, lf);
-        if (lane < 5) {
-            double ph[6];
-#pragma unroll
-            for (int lf = 0; lf < 6; ++lf) {
-                const int cd = codes[lf];
-                const int f = (cd > 0 ? cd : -cd) - 1;
-                ph[lf] = lf < nfc ? D.Phi[lane * nf + f] : 0.0;
-            }
-            for (int lf = 0; lf < nfc; ++lf) {
-                const double sg = codes[lf] > 0 ? 1.0 : -1.0;
-                facc = facc - sg * ph[lf];
-            }
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int k = q * kWave + lane;
+        v[q] = k < n ? a[k] : 0ULL;
     }
-    if (nmov == 0 && cb1 == cb0 && s00 == s01 && (n_new == 0 || s10 == s11)) {
-        // no particle ends in c and none stays there: the update is -sum_f s_f Phi_f - S, with
-        // the particle sums exactly 0 (as the reductions below would give)
-        if (lane < 5) {
-            const double acc = facc + (0.0 - D.S[lane * nc + c]);
-            D.W[lane * nc + c] = D.W[lane * nc + c] + acc / D.vol[c];
-            D.P[lane * nc + c] = 0.0;
-        }
-        if (lane == 0) {
-            D.nleft[c] = bend - base;
-            D.segoff[buf ^ 1][c] = base;
-            if (base != bend) atomicOr(&D.sc->err, kErrCapacity);
-        }
-        if (SH && lane < 3) D.qh[lane * nc + c] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool head = q * kWave + lane < n && ((unsigned)v[q] & kHeadBit) != 0;
+        heads[q] = __ballot(head);
+        const int h = H + (int)__popcll(heads[q] & upto) - 1;
+        if (head && h < kWave) tab[h] = (v[q] & ~0xFFFFFFFFULL) | (unsigned)(q * kWave + lane);
+        H += (int)__popcll(heads[q]);
+    }
+    wave_sync();
+    if (H > kWave) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q * kWave + lane < n) lds[q * kWave + lane] = v[q];
+        wave_sync();
+        wave_sort(lds, n);
         return;
     }
-    double Pn[5] = {0, 0, 0, 0, 0}, Cn[5] = {0, 0, 0, 0, 0};
-    double H[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const bool shc = SH && D.ip[inst_of(D, c)].pr != 1.0;
-    // movers (part 0) and collided (part 1): source lists sorted ascending
+    // lane h: piece h's first order, place and length; the places of the pieces before it
+    const unsigned long long t = lane < H ? tab[lane] : 0ULL;
+    const unsigned key = (unsigned)(t >> 32);
+    const int pos = lo32(t), nextp = __shfl_down(pos, 1);
+    const int len = lane < H ? (lane == H - 1 ? n : nextp) - pos : 0;
+    int base = -pos;
+    for (int i = 0; i < H; ++i)
+        if ((unsigned)__builtin_amdgcn_readlane((int)key, i) < key) base += __builtin_amdgcn_readlane(len, i);
+    int before = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int k = q * kWave + lane;
+        const int shift = __shfl(base, before + (int)__popcll(heads[q] & upto) - 1);
+        if (k < n) lds[k + shift] = v[q];
+        before += (int)__popcll(heads[q]);
+    }
+    wave_sync();
+}
+
+// ---------------------------------------------------------------------------------------
+// S6: the buckets.  Part 0, a cell's arrivals (survivors that left another cell, or came back
+// to this one after a wall), sorted by their order at the start of the step: their records go
+// to the second part of the next buffer (the stayers are in the first already, k_stream) and
+// their sums are added to P^{n+1}.  Part 1, the particles that collided elsewhere and end in
+// the cell: their sums come off S (E - S is P^{n+1} - (S - collided)).
+// One wave takes G consecutive cells: runs of cells whose entries fit in 64 lanes together are
+// sorted, moved and summed at once (segmented sums, whose order depends only on a particle's
+// place in its own bucket); a bucket of more than 64 has the wave to itself.  Which of the
+// two a bucket takes depends on its own length alone, so the sums do not depend on the cells
+// around it: bitwise reproducible, alone or in a batch.
+// ---------------------------------------------------------------------------------------
+template <typename R, int WPB, bool KE, int G>
+__device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
+    constexpr int BS = kWave;
+    constexpr int kLds = 256;  // longer lists are sorted in place in global memory
+    constexpr int CPR = RecChunks<R>::N;
+    __shared__ unsigned long long lds_all[WPB][kLds];
+    __shared__ uint4 st_all[WPB][kWave * CPR];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    // blocks go round-robin to the 8 XCDs; give each XCD a contiguous range of cells so that
+    // neighbouring cells (whose particles are exchanged) share an L2
+    const int nb = (int)gridDim.x, bidx = (int)blockIdx.x;
+    const int xcd = bidx & 7, q8 = nb >> 3, rr = nb & 7;
+    const int c0 = ((xcd * q8 + (xcd < rr ? xcd : rr) + (bidx >> 3)) * WPB + wave) * G;
+    const int nc = D.nc;
+    if (c0 >= nc || D.sc->none) return;
+    unsigned long long *lds = lds_all[wave];
+    uint4 *st = st_all[wave];
+    const Particles src = D.pa[buf], dst = D.pa[buf ^ 1];
+    const long long span = D.sc->span[buf ^ 1];
+#pragma unroll
     for (int part = 0; part < 2; ++part) {
-        const int a0 = part == 0 ? base : cb0;
-        const int len = part == 0 ? nmov : cb1 - cb0;
-        int *list;
-        if (len <= kLds) {
-            for (int j = lane; j < len; j += BS) lds[j] = D.perm[a0 + j];
-            wave_sync();
-            list = lds;
-        } else {
-            list = D.perm + a0;
+        const unsigned long long *off = D.off + (part == 0 ? 0 : nc);
+        double *to = part == 0 ? D.P : D.S;
+        int my_first = 0, my_len = 0;
+        if (lane < G && c0 + lane < nc) {
+            my_first = lo32(off[c0 + lane]);
+            my_len = lo32(off[c0 + lane + 1]) - my_first;
         }
-        wave_sort(list, len);
-        if (part == 0) {
-            // two records per lane in flight: both loads before either store
-            for (int j0 = 0; j0 < len; j0 += 2 * BS) {
-                const int j = j0 + lane;
-                const bool ha = j < len, hb = j + BS < len;
-                typename RecOf<R>::T A{}, B{};
-                if (ha) load_rec<KE>(src, list[j], A);
-                if (hb) load_rec<KE>(src, list[j + BS], B);
-                if (ha) stage_rec<KE>(dst, a0 + j, c, A, Pn, st + lane * CPR);
-                if (SH && ha) stage_mass(stm, lane, A);
-                stage_out<R>(st, dst, a0 + j0, min(BS, len - j0));
-                if (shc) heat_from_stage<R>(st, stm, (a0 + j0 - base) & 63, min(BS, len - j0), H);
-                if (hb) stage_rec<KE>(dst, a0 + j + BS, c, B, Pn, st + lane * CPR);
-                if (SH && hb) stage_mass(stm, lane, B);
-                stage_out<R>(st, dst, a0 + j0 + BS, max(0, min(BS, len - j0 - BS)));
-                if (shc) heat_from_stage<R>(st, stm, (a0 + j0 + BS - base) & 63, max(0, min(BS, len - j0 - BS)), H);
+        const Runs<G> L(my_first, my_len);  // the G buckets are consecutive in perm
+        const int a0 = L.first[0];
+        int g = 0;
+        while (g < G) {
+            // wave-uniform: the longest run [g, h) of buckets whose entries fit in 64 lanes
+            int h = g + 1, pg = 0, ph = 0;
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                if (j == g) {
+                    pg = L.pre[j];
+                    ph = L.pre[j + 1];
+                }
+                if (j == h && j > g && L.pre[j + 1] - pg <= BS) {
+                    h = j + 1;
+                    ph = L.pre[j + 1];
+                }
             }
-        } else {
-#pragma unroll 2
-            for (int j = lane; j < len; j += BS) add_rec<KE>(src, list[j], Cn, R(0));
-        }
-        wave_sync();
-    }
-    // stayers: own segment of old particles, then own new particles, compacted in order and
-    // advanced by u dt (the transport left their records as they were)
-    const R dtR = (R)D.is[inst_of(D, c)].dt;
-    const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
-    int pos = base + nmov;
-    for (int seg = 0; seg < 2; ++seg) {
-        const long long s0 = seg == 0 ? s00 : s10;
-        const long long s1 = seg == 0 ? s01 : (n_new == 0 ? s10 : s11);
-        // two runs of 64 per pass: both key loads, then both record loads, then the stores
-        for (long long j0 = s0; j0 < s1; j0 += 2 * BS) {
-            const long long ja = j0 + lane, jb = j0 + BS + lane;
-            const int ka = ja < s1 ? D.key[ja] : -1;
-            const int kb = jb < s1 ? D.key[jb] : -1;
-            const bool sa = ka >= 0 && (ka & kStayBit) != 0, sb = kb >= 0 && (kb & kStayBit) != 0;
-            const unsigned long long ma = __ballot(sa), mb = __ballot(sb);
-            typename RecOf<R>::T A{}, B{};
-            if (sa) load_rec<KE>(src, (int)ja, A);
-            if (sb) load_rec<KE>(src, (int)jb, B);
-            if (sa) advance(A, dtR);
-            if (sb) advance(B, dtR);
-            const int ra = (int)__popcll(ma & below), rb = (int)__popcll(mb & below);
-            if (sa) stage_rec<KE>(dst, pos + ra, c, A, Pn, st + ra * CPR);
-            if (SH && sa) stage_mass(stm, ra, A);
-            stage_out<R>(st, dst, pos, (int)__popcll(ma));
-            if (shc) heat_from_stage<R>(st, stm, (pos - base) & 63, (int)__popcll(ma), H);
-            pos += (int)__popcll(ma);
-            if (sb) stage_rec<KE>(dst, pos + rb, c, B, Pn, st + rb * CPR);
-            if (SH && sb) stage_mass(stm, rb, B);
-            stage_out<R>(st, dst, pos, (int)__popcll(mb));
-            if (shc) heat_from_stage<R>(st, stm, (pos - base) & 63, (int)__popcll(mb), H);
-            pos += (int)__popcll(mb);
-        }
-    }
-    double Pk, Ck;
-    wave_sum_pc(Pn, Cn, Pk, Ck);
-    double Wk = 0.0;
-    if (lane < 5) {
-        const double E = Pk + Ck;
-        const double acc = facc + (E - D.S[lane * nc + c]);
-        Wk = D.W[lane * nc + c] + acc / D.vol[c];
-        D.W[lane * nc + c] = Wk;
-        D.P[lane * nc + c] = Pk;
-    }
-    if (lane == 0) {
-        D.nleft[c] = bend - base;
-        D.segoff[buf ^ 1][c] = base;
-        if (pos != bend) atomicOr(&D.sc->err, kErrCapacity);
-    }
-    if constexpr (SH) {
-        // sum m c_i |c|^2 = S3_i - 2 sum_j U_j S2_ij - U_i tr S2 + |U|^2 S1_i + 2 U_i (U . S1) - U_i |U|^2 S0
-        if (shc) {
+            const int nr = ph - pg;
+            if (nr > 0 && nr <= BS) {
+                // this lane's bucket j and its first and last lane
+                int j = g, first = 0, last = 0;
 #pragma unroll
-            for (int k = 0; k < 9; ++k) H[k] = wave_sum(H[k]);
-        }
-        double Wn[5], Pv[5];
+                for (int i = 0; i < G; ++i)
+                    if (i >= g && i < h && L.pre[i] - pg <= lane && L.pre[i + 1] - pg > lane) {
+                        j = i;
+                        first = L.pre[i] - pg;
+                        last = L.pre[i + 1] - pg - 1;
+                    }
+                const bool act = lane < nr;
+                if (!act) first = last = lane;
+                // Place in the bucket: a piece (kHeadBit) stays together, behind the pieces of the
+                // bucket whose first order is smaller.  A cell's particles come from a handful of
+                // cells, so these are a handful of comparisons (a bitonic network over 64
+                // entries needs 21 exchanges).
+                const unsigned long long v = act ? D.perm[a0 + pg + lane] : 0ULL;
+                unsigned long long todo = __ballot(act && ((unsigned)v & kHeadBit) != 0);
+                const int my_head = act ? 63 - __clzll((long long)(todo & (~0ULL >> (63 - lane)))) : lane;
+                const unsigned key = (unsigned)__shfl((int)(v >> 32), my_head);
+                int r = first + (lane - my_head);
+                while (todo) {
+                    const int h = __ffsll((long long)todo) - 1;
+                    todo &= todo - 1;
+                    const int next = todo ? __ffsll((long long)todo) - 1 : nr;
+                    const unsigned kh = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), h);
+                    // a piece lies in one bucket, but its successor here may be another bucket's
+                    if (h >= first && h <= last && kh < key) r += next - h;
+                }
+                if (act) lds[r] = v;
+                wave_sync();
+                Part<R> A;
+                double acc[5] = {0, 0, 0, 0, 0};
+                if (act) {
+                    load_part<KE>(src, (long long)(lo32(lds[lane]) & ~kHeadBit), A);
+                    add_phi<R>(acc, A.m, A.u, A.e);
+                }
+                if (part == 0) {
+                    const int pl = a0 + pg;
+                    const bool wrap = (long long)pl + nr > D.cap - span;
+                    if (act) {
+                        const int o = wrap ? slot_of(D, buf ^ 1, span, pl + lane) : (int)span + pl + lane;
+                        store_side<KE>(dst, o, A);
+                        if (wrap)
+                            stage_part(rec_chunks(dst, o, R(0)), A);
+                        else
+                            stage_part(st + lane * CPR, A);
+                    }
+                    if (!wrap) {
+                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                        uint4 *gp = rec_chunks(dst, span + pl, R(0));
+                        for (int k = lane; k < nr * CPR; k += BS) st_nt(&gp[k], st[k]);
+                    }
+                }
+                double pv[5];
+                const int c = c0 + j;
+                const bool end = act && lane == last;
+                if (end) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            Wn[k] = __shfl(Wk, k);
-            Pv[k] = __shfl(Pk, k);
+                    for (int k = 0; k < 5; ++k) pv[k] = to[k * nc + c];
+                }
+#pragma unroll
+                for (int k = 0; k < 5; ++k) acc[k] = seg_sum(acc[k], first, last);
+                if (end) {
+#pragma unroll
+                    for (int k = 0; k < 5; ++k) to[k * nc + c] = part == 0 ? pv[k] + acc[k] : pv[k] - acc[k];
+                }
+                wave_sync();
+            } else if (nr > 0) {
+                // one bucket of more than 64
+                const int pl = a0 + pg;
+                unsigned long long *list = D.perm + pl;
+                if (nr <= kLds) {
+                    sort_pieces(list, nr, lds, reinterpret_cast<unsigned long long *>(st));
+                    list = lds;
+                } else {
+                    wave_sort(list, nr);
+                }
+                double acc[5] = {0, 0, 0, 0, 0};
+                for (int k0 = 0; k0 < nr; k0 += BS) {
+                    const int k = k0 + lane;
+                    if (k < nr) {
+                        Part<R> A;
+                        load_part<KE>(src, (long long)(lo32(list[k]) & ~kHeadBit), A);
+                        add_phi<R>(acc, A.m, A.u, A.e);
+                        if (part == 0) {
+                            store_side<KE>(dst, slot_of(D, buf ^ 1, span, pl + k), A);
+                            stage_part(st + lane * CPR, A);
+                        }
+                    }
+                    if (part == 0) {
+                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                        const int m = min(BS, nr - k0);
+                        for (int i = lane; i < m * CPR; i += BS)
+                            st_nt(&rec_chunks(dst, slot_of(D, buf ^ 1, span, pl + k0 + i / CPR), R(0))[i % CPR], st[i]);
+                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
+                double ak = acc[0];
+#pragma unroll
+                for (int k = 1; k < 5; ++k)
+                    if (lane == k) ak = acc[k];
+                if (lane < 5) to[lane * nc + c0 + g] = part == 0 ? to[lane * nc + c0 + g] + ak : to[lane * nc + c0 + g] - ak;
+                wave_sync();
+            }
+            g = h;
         }
-        if (lane < 3) D.qh[lane * nc + c] = shc ? heat_of(H, Wn, Pv, D.vol[c]) : 0.0;
     }
 }
 
 template <typename R, int WPB, bool KE>
 __global__ void __launch_bounds__(WPB * 64) k_gather(Dev D, int buf) {
-    gather_cells<R, WPB, KE, false>(D, buf);
+    gather_cells<R, WPB, KE, kListCellsDense>(D, buf);
 }
-// the gather of a batch with an instance of the Shakhov model (K = 0): also each cell's heat
-// flux for the next step
-template <typename R, int WPB>
-__global__ void __launch_bounds__(WPB * 64) k_gather_sh(Dev D, int buf) {
-    gather_cells<R, WPB, false, true>(D, buf);
+template <typename R, int WPB, bool KE>
+__global__ void __launch_bounds__(WPB * 64) k_gather_sparse(Dev D, int buf) {
+    gather_cells<R, WPB, KE, kListCellsSparse>(D, buf);
 }
 
-// S6 in a wave-only step with no particle anywhere (none is left, sampled or let in): the
-// update W^{n+1} = W^n + (-sum_f s_f Phi_f + E - S) / Omega with E = 0 and S = P = 0, one
-// thread per cell, in the arithmetic and order of the gather's cells without particles (so the
-// results are those of the full step bit for bit); the bucket offsets are those of empty cells
-__global__ void __launch_bounds__(256) k_gks_update(Dev D, int buf) {
+// the particles between two steps in their order (arrivals, stayers, cell by cell), one after
+// the other in the other buffer
+template <typename R, bool KE>
+__global__ void __launch_bounds__(256) k_pack(Dev D, int buf) {
+    const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    if (c >= D.nc) return;
+    const unsigned long long o0 = D.off[c], o1 = D.off[c + 1];
+    const int n = hi32(o1) - hi32(o0), nm = lo32(o1) - lo32(o0), m0 = lo32(o0), v0 = D.v0[buf][c];
+    const long long span = D.sc->span[buf];
+    const Particles pa = D.pa[buf], pb = D.pa[buf ^ 1];
+    for (int k = lane_id(); k < n; k += kWave) {
+        Part<R> q;
+        load_part<KE>(pa, k < nm ? slot_of(D, buf, span, m0 + k) : v0 + (k - nm), q);
+        const long long o = hi32(o0) + k;
+        stage_part(rec_chunks(pb, o, R(0)), q);
+        store_side<KE>(pb, o, q);
+    }
+}
+
+// S6: W^{n+1} = W^n + (-sum_f s_f Phi_f + E - S) / Omega, one thread per cell; E - S is P^{n+1}
+// minus what k_stream and the gather left of S.  In a step with no particle anywhere (none is
+// left, sampled or let in) no kernel between the preparation and this one does anything: then
+// P^{n+1} = 0 and S = P^n.
+__global__ void __launch_bounds__(256) k_update(Dev D) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= D.nc) return;
+    const bool none = D.sc->none != 0;
     const int nc = D.nc, nf = D.nf, nfc = D.nfc[c];
     int codes[6];
 #pragma unroll
@@ -3072,7 +3043,7 @@ __global__ void __launch_bounds__(256) k_gks_update(Dev D, int buf) {
     const double vol = D.vol[c];
     // every load before the first store (the stores could alias them as far as the compiler
     // knows, which would otherwise keep one round trip per component)
-    double ph[5][6], pv[5], wv[5];
+    double ph[5][6], pv[5], sv[5], wv[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
 #pragma unroll
@@ -3082,53 +3053,48 @@ __global__ void __launch_bounds__(256) k_gks_update(Dev D, int buf) {
             ph[k][lf] = lf < nfc ? D.Phi[k * nf + f] : 0.0;
         }
         pv[k] = D.P[k * nc + c];
+        sv[k] = D.S[k * nc + c];
         wv[k] = D.W[k * nc + c];
     }
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         double facc = 0.0;
-        for (int lf = 0; lf < nfc; ++lf) {
-            const double sg = codes[lf] > 0 ? 1.0 : -1.0;
-            facc = facc - sg * ph[k][lf];
-        }
-        const double S = pv[k] + 0.0;
-        const double acc = facc + (0.0 - S);
+#pragma unroll
+        for (int lf = 0; lf < 6; ++lf)  // (unrolled: arrays indexed at run time would live in scratch memory)
+            if (lf < nfc) facc = facc - (codes[lf] > 0 ? ph[k][lf] : -ph[k][lf]);
+        const double acc = facc + (none ? 0.0 - pv[k] : pv[k] - sv[k]);
         D.W[k * nc + c] = wv[k] + acc / vol;
-        D.P[k * nc + c] = 0.0;
+        if (none) D.P[k * nc + c] = 0.0;
     }
-    const int base = D.off[c], bend = D.off[c + 1];
-    D.nleft[c] = bend - base;
-    D.segoff[buf ^ 1][c] = base;
-    if (base != bend) atomicOr(&D.sc->err, kErrCapacity);
 }
 
-__global__ void __launch_bounds__(256) k_finalize(Dev D, int buf) {
-    __shared__ unsigned long long red[2][64];
+__global__ void __launch_bounds__(256) k_finalize(Dev D) {
+    __shared__ unsigned long long red[2][kWallSeg];
     Scalars *s = D.sc;
     const long long n_old = s->n_old, n_new = s->n_new, n_inj = s->n_inj;
     const long long n_tot = n_old + n_new + n_inj;
-    if (threadIdx.x < 64) {
+    if (threadIdx.x < kWallSeg) {
         red[0][threadIdx.x] = D.spart[threadIdx.x];
-        red[1][threadIdx.x] = D.spart[64 + threadIdx.x];
+        red[1][threadIdx.x] = D.spart[kWallSeg + threadIdx.x];
     }
     __syncthreads();
-    for (int h = 32; h > 0; h >>= 1) {
+    for (int h = kWallSeg / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) {
             red[0][threadIdx.x] += red[0][threadIdx.x + h];
             red[1][threadIdx.x] += red[1][threadIdx.x + h];
         }
         __syncthreads();
     }
-    // per instance: its particles occupy the buckets of its cell range, its old particles
-    // the survivor segments of those cells, its new ones the sampled and entering ranges of
-    // its cells and far-field faces; then its own clock advances
+    // per instance: its particles occupy the buckets of its cell range, its old ones are those
+    // the step before left, its new ones the sampled and entering ranges of its cells and
+    // far-field faces; then its own clock advances
     const int nc = D.nc;
     for (int k = threadIdx.x; k < D.n_inst; k += blockDim.x) {
         const InstP &P = D.ip[k];
         InstS &I = D.is[k];
-        const long long alive = D.off[P.cell1] - D.off[P.cell0];
-        const long long coll = D.off[nc + P.cell1] - D.off[nc + P.cell0];
-        const long long old = D.segoff[buf][P.cell1] - D.segoff[buf][P.cell0];
+        const long long alive = hi32(D.off[P.cell1]) - hi32(D.off[P.cell0]);
+        const long long coll = hi32(D.off[nc + P.cell1]) - hi32(D.off[nc + P.cell0]);
+        const long long old = I.n_alive;
         const long long smp = n_new > 0 ? D.samoff[P.cell1] - D.samoff[P.cell0] : 0;
         const long long inj = (n_inj > 0 && P.ff1 > P.ff0) ? D.injoff[P.ff1] - D.injoff[P.ff0] : 0;
         const long long tot = old + smp + inj;
@@ -3143,8 +3109,8 @@ __global__ void __launch_bounds__(256) k_finalize(Dev D, int buf) {
         I.dtmin_bits = 0x7FF0000000000000ULL;
     }
     if (threadIdx.x == 0) {
-        const long long alive = D.off[nc];
-        const long long ended = D.off[2 * nc];
+        const long long alive = hi32(D.off[nc]);
+        const long long ended = hi32(D.off[2 * nc]);
         s->n_cross = red[0][0];
         s->n_wall = red[1][0];
         s->n_collided = (unsigned long long)(ended - alive);
@@ -3152,7 +3118,7 @@ __global__ void __launch_bounds__(256) k_finalize(Dev D, int buf) {
         s->moved_total = s->moved_total + (unsigned long long)n_tot;
         s->n_alive = alive;
         s->n_old = alive;
-        D.segoff[buf ^ 1][nc] = (int32_t)alive;
+        s->n_mov = lo32(D.off[nc]);
         s->n_new = 0;
         s->n_inj = 0;
         s->t = s->t + s->dt;
@@ -3165,8 +3131,8 @@ __global__ void __launch_bounds__(256) k_finalize(Dev D, int buf) {
 // ---------------------------------------------------------------------------------------
 constexpr int kScanBS = 256, kScanPer = 8, kScanTile = kScanBS * kScanPer;
 
-// scan inputs: a plain array, or the bucket sizes (movers / collided in the low word of the
-// bucket counter, stayers in the high word)
+// scan inputs: a plain array, or the bucket sizes (all particles of the bucket in the high word,
+// those listed in perm in the low one; neither total reaches 2^31)
 template <typename T>
 struct LoadPlain {
     const T *p;
@@ -3174,9 +3140,9 @@ struct LoadPlain {
 };
 struct LoadBucket {
     const unsigned long long *p;
-    __device__ int32_t operator()(long long i) const {
+    __device__ unsigned long long operator()(long long i) const {
         const unsigned long long v = p[i];
-        return (int32_t)(v & 0xFFFFFFFFULL) + (int32_t)(v >> 32);
+        return v + (v << 32);
     }
 };
 
@@ -3374,50 +3340,71 @@ void launch_fill_f64(double *p, long long n, double v, hipStream_t s) {
 }
 
 namespace {
-// entries of one wall-queue segment for a transport grid of g blocks of `per` particles;
-// kWallSeg segments take at most cap + kWallSlack entries
-long long wall_qseg(long long g, long long per) { return (g + kWallSeg - 1) / kWallSeg * per; }
-
 template <typename R, bool MULTI, int ILP>
-long long launch_stream_i(const Dev &D, int buf, int bs, hipStream_t s) {
-    // ILP particles per thread over the capacity; blocks past the live particles exit at once
-    const long long per = (long long)bs * ILP;
-    const unsigned g = (unsigned)((D.cap + per - 1) / per);
-    const long long qseg = wall_qseg(g, per);
-    if (bs == 128)
-        k_stream<R, 128, MULTI, ILP><<<g, 128, 0, s>>>(D, buf, qseg);
-    else if (bs == 512)
-        k_stream<R, 512, MULTI, ILP><<<g, 512, 0, s>>>(D, buf, qseg);
-    else
-        k_stream<R, 256, MULTI, ILP><<<g, 256, 0, s>>>(D, buf, qseg);
-    return qseg;
-}
-
-template <typename R, bool MULTI>
-long long launch_stream_t(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
-    if (cfg.stream_ilp == 2) return launch_stream_i<R, MULTI, 2>(D, buf, cfg.stream_bs, s);
-    return launch_stream_i<R, MULTI, 1>(D, buf, cfg.stream_bs, s);
-}
-
-// returns the wall-queue segment length the transport grid used
-template <typename R>
-long long launch_stream(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
-    if (D.n_inst > 1) return launch_stream_t<R, true>(D, buf, cfg, s);
-    return launch_stream_t<R, false>(D, buf, cfg, s);
-}
-
-template <typename R>
-void launch_stream_wall(const Dev &D, int buf, long long qseg, hipStream_t s) {
-    // 16 blocks per queue segment, each segment's length known only on the device
-    const unsigned g = 16 * kWallSeg;
-    if (D.n_inst > 1 && D.K > 0)
-        k_stream_wall<R, true, true><<<g, 256, 0, s>>>(D, buf, qseg);
-    else if (D.n_inst > 1)
-        k_stream_wall<R, true, false><<<g, 256, 0, s>>>(D, buf, qseg);
+void launch_stream_i(const Dev &D, int buf, int bs, hipStream_t s) {
+    const unsigned g = (unsigned)((D.nc + bs / kWave - 1) / (bs / kWave));
+    if (D.K > 0 && bs == 128)
+        k_stream_e<R, 128, MULTI, ILP><<<g, 128, 0, s>>>(D, buf);
+    else if (D.K > 0 && bs == 512)
+        k_stream_e<R, 512, MULTI, ILP><<<g, 512, 0, s>>>(D, buf);
     else if (D.K > 0)
-        k_stream_wall<R, false, true><<<g, 256, 0, s>>>(D, buf, qseg);
+        k_stream_e<R, 256, MULTI, ILP><<<g, 256, 0, s>>>(D, buf);
+    else if (bs == 128)
+        k_stream<R, 128, MULTI, ILP><<<g, 128, 0, s>>>(D, buf);
+    else if (bs == 512)
+        k_stream<R, 512, MULTI, ILP><<<g, 512, 0, s>>>(D, buf);
     else
-        k_stream_wall<R, false, false><<<g, 256, 0, s>>>(D, buf, qseg);
+        k_stream<R, 256, MULTI, ILP><<<g, 256, 0, s>>>(D, buf);
+}
+
+// blocks of the kernels that take several cells per wave
+unsigned list_grid(const Dev &D, int waves = 4) {
+    const int per = waves * (D.list_sparse ? kListCellsSparse : kListCellsDense);
+    return (unsigned)((D.nc + per - 1) / per);
+}
+
+template <typename R, bool KE, int MESH>
+void launch_track_m(const Dev &D, int buf, hipStream_t s) {
+    if (D.nff > 0) k_stream_in<R, KE, MESH><<<256, 256, 0, s>>>(D, buf);
+    if (D.list_sparse)
+        k_track<R, KE, MESH, kListCellsSparse><<<list_grid(D), 256, 0, s>>>(D, buf);
+    else
+        k_track<R, KE, MESH, kListCellsDense><<<list_grid(D), 256, 0, s>>>(D, buf);
+}
+
+template <typename R, bool KE>
+void launch_track(const Dev &D, int buf, hipStream_t s) {
+    if (D.all_box)
+        launch_track_m<R, KE, 1>(D, buf, s);
+    else if (D.all_tet)
+        launch_track_m<R, KE, 2>(D, buf, s);
+    else
+        launch_track_m<R, KE, 0>(D, buf, s);
+}
+
+// the transport: flights that meet no face, those of the entering particles, the others
+template <typename R>
+void launch_stream(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
+    if (D.n_inst > 1 && cfg.stream_ilp == 2)
+        launch_stream_i<R, true, 2>(D, buf, cfg.stream_bs, s);
+    else if (D.n_inst > 1)
+        launch_stream_i<R, true, 1>(D, buf, cfg.stream_bs, s);
+    else if (cfg.stream_ilp == 2)
+        launch_stream_i<R, false, 2>(D, buf, cfg.stream_bs, s);
+    else
+        launch_stream_i<R, false, 1>(D, buf, cfg.stream_bs, s);
+    if (D.K > 0)
+        launch_track<R, true>(D, buf, s);
+    else
+        launch_track<R, false>(D, buf, s);
+}
+
+void launch_scatter(const Dev &D, hipStream_t s) {
+    if (D.list_sparse)
+        k_scatter<kListCellsSparse><<<list_grid(D), 256, 0, s>>>(D);
+    else
+        k_scatter<kListCellsDense><<<list_grid(D), 256, 0, s>>>(D);
+    if (D.nff > 0) k_scatter_in<<<256, 256, 0, s>>>(D);
 }
 
 template <typename R, bool KE, int G>
@@ -3519,7 +3506,7 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
         k_inject_count<<<(unsigned)((D.nff + 255) / 256), 256, 0, s>>>(D);
         scan<long long>(LoadPlain<long long>{D.ninj}, D.nff, D.injoff, D.scan64, s);
     }
-    k_sample_setup<<<1, 1, 0, s>>>(D);
+    k_sample_setup<<<1, 1, 0, s>>>(D, buf);
     pr->end(kSlotScan);
     const bool f32 = D.prec == 1;
     pr->begin(kSlotFlux);
@@ -3543,36 +3530,29 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
     }
     pr->end(kSlotSample);
     pr->begin(kSlotStream);
-    const long long qseg = f32 ? launch_stream<float>(D, buf, cfg, s) : launch_stream<double>(D, buf, cfg, s);
-    pr->end(kSlotStream);
-    pr->begin(kSlotStreamWall);
-    if (D.any_diffuse) {
-        if (f32)
-            launch_stream_wall<float>(D, buf, qseg, s);
-        else
-            launch_stream_wall<double>(D, buf, qseg, s);
-    }
-    pr->end(kSlotStreamWall);
-    pr->begin(kSlotCount);
-    if (D.count_ch == 4)
-        k_count<4><<<(unsigned)((D.cap + 256 * 4 - 1) / (256 * 4)), 256, 0, s>>>(D);
+    if (f32)
+        launch_stream<float>(D, buf, cfg, s);
     else
-        k_count<8><<<(unsigned)((D.cap + 256 * 8 - 1) / (256 * 8)), 256, 0, s>>>(D);
-    pr->end(kSlotCount);
+        launch_stream<double>(D, buf, cfg, s);
+    pr->end(kSlotStream);
     pr->begin(kSlotScan2);
-    scan<int32_t>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
+    scan<unsigned long long>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
     pr->end(kSlotScan2);
     pr->begin(kSlotScatter);
-    k_scatter<<<(unsigned)((D.cap + 256 * kScatterChunks - 1) / (256 * kScatterChunks)), 256, 0, s>>>(D);
+    launch_scatter(D, s);
     pr->end(kSlotScatter);
     pr->begin(kSlotGather);
     {
         constexpr int WPB = kGatherWaves;
-        const unsigned g = (unsigned)((nc + WPB - 1) / WPB);
-        if (D.sh_any && f32)
-            k_gather_sh<float, WPB><<<g, WPB * 64, 0, s>>>(D, buf);
-        else if (D.sh_any)
-            k_gather_sh<double, WPB><<<g, WPB * 64, 0, s>>>(D, buf);
+        const unsigned g = list_grid(D, WPB);
+        if (D.list_sparse && f32 && D.K > 0)
+            k_gather_sparse<float, WPB, true><<<g, WPB * 64, 0, s>>>(D, buf);
+        else if (D.list_sparse && f32)
+            k_gather_sparse<float, WPB, false><<<g, WPB * 64, 0, s>>>(D, buf);
+        else if (D.list_sparse && D.K > 0)
+            k_gather_sparse<double, WPB, true><<<g, WPB * 64, 0, s>>>(D, buf);
+        else if (D.list_sparse)
+            k_gather_sparse<double, WPB, false><<<g, WPB * 64, 0, s>>>(D, buf);
         else if (f32 && D.K > 0)
             k_gather<float, WPB, true><<<g, WPB * 64, 0, s>>>(D, buf);
         else if (f32)
@@ -3582,9 +3562,11 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
         else
             k_gather<double, WPB, false><<<g, WPB * 64, 0, s>>>(D, buf);
     }
+    k_update<<<gc, 256, 0, s>>>(D);
+    launch_heat(D, buf ^ 1, s);
     pr->end(kSlotGather);
     pr->begin(kSlotFinal);
-    k_finalize<<<1, 256, 0, s>>>(D, buf);
+    k_finalize<<<1, 256, 0, s>>>(D);
     if (D.avg_from >= 0) {
         k_avg_cells<<<(unsigned)(D.n_inst * kAvgBlocks), 256, 0, s>>>(D);
         k_avg_fin<<<(unsigned)D.n_inst, 64, 0, s>>>(D);
@@ -3612,7 +3594,7 @@ void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStrea
         k_inject_count<<<(unsigned)((D.nff + 255) / 256), 256, 0, s>>>(D);
         scan<long long>(LoadPlain<long long>{D.ninj}, D.nff, D.injoff, D.scan64, s);
     }
-    k_sample_setup<<<1, 1, 0, s>>>(D);
+    k_sample_setup<<<1, 1, 0, s>>>(D, buf);
     pr->end(kSlotScan);
     pr->begin(kSlotFlux);
     if (nf > 0) {
@@ -3623,18 +3605,30 @@ void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStrea
     }
     pr->end(kSlotFlux);
     pr->begin(kSlotScan2);
-    scan<int32_t>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
+    scan<unsigned long long>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
     pr->end(kSlotScan2);
     pr->begin(kSlotGather);
-    k_gks_update<<<gc, 256, 0, s>>>(D, buf);
+    k_update<<<gc, 256, 0, s>>>(D);
     pr->end(kSlotGather);
     pr->begin(kSlotFinal);
-    k_finalize<<<1, 256, 0, s>>>(D, buf);
+    k_finalize<<<1, 256, 0, s>>>(D);
     if (D.avg_from >= 0) {
         k_avg_cells<<<(unsigned)(D.n_inst * kAvgBlocks), 256, 0, s>>>(D);
         k_avg_fin<<<(unsigned)D.n_inst, 64, 0, s>>>(D);
     }
     pr->end(kSlotFinal);
+}
+
+void launch_pack(const Dev &D, int buf, hipStream_t s) {
+    const unsigned g = (unsigned)((D.nc + 3) / 4);
+    if (D.prec == 1 && D.K > 0)
+        k_pack<float, true><<<g, 256, 0, s>>>(D, buf);
+    else if (D.prec == 1)
+        k_pack<float, false><<<g, 256, 0, s>>>(D, buf);
+    else if (D.K > 0)
+        k_pack<double, true><<<g, 256, 0, s>>>(D, buf);
+    else
+        k_pack<double, false><<<g, 256, 0, s>>>(D, buf);
 }
 
 void launch_avg_out(const Dev &D, double *out, hipStream_t s) {

@@ -16,9 +16,9 @@ enum ProfSlot : int {
     kSlotScan,          // scan of N_sam, capacity check, clearing of the bucket counters
     kSlotFlux,          // k_flux
     kSlotSample,        // k_sample
-    kSlotStream,        // k_stream
-    kSlotStreamWall,    // k_stream_wall (diffuse re-emissions queued by k_stream)
-    kSlotCount,         // k_count
+    kSlotStream,        // k_stream, k_stream_in, k_track
+    kSlotStreamWall,    // (no kernels: k_track re-emits at walls)
+    kSlotCount,         // (no kernels: k_track counts)
     kSlotScan2,         // scan of the bucket counts
     kSlotScatter,       // k_scatter
     kSlotGather,        // k_gather
@@ -33,8 +33,8 @@ struct Prof {
 
 // launch shapes of the kernels whose shape is tunable; every choice gives the same results
 struct LaunchCfg {
-    int stream_bs = 256;  // k_stream block size: 128, 256 or 512
-    int stream_ilp = 1;   // k_stream particles per thread: 1 or 2
+    int stream_bs = 256;  // k_stream block size: 128, 256 or 512 (a wave per cell)
+    int stream_ilp = 1;   // k_stream runs of 64 particles loaded together: 1 or 2
     int sample_wpb = 4;   // k_sample waves (cells) per block: 1, 2, 4 or 8
     int flux_bs = 128;    // k_flux block size: 64, 128 or 256
 };
@@ -46,11 +46,12 @@ void launch_fill_f64(double *p, long long n, double v, hipStream_t s);
 void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Prof *pr);
 // a wave-only step when no particle exists anywhere (the same results as launch_step)
 void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Prof *pr);
-// Shakhov model: each cell's heat flux from the particles in pa[buf] (after the state is set;
-// the gather keeps it up to date from then on)
+// Shakhov model: each cell's heat flux from the particles in pa[buf]
 void launch_heat(const Dev &D, int buf, hipStream_t s);
 // [nc][5] field (0 W, 1 W^p, 2 W^h, 3 primitives) into device memory out
 void launch_moments(const Dev &D, int which, double *out, hipStream_t s);
+// the particles of pa[buf] in their order, one after the other, into pa[buf ^ 1] (between steps)
+void launch_pack(const Dev &D, int buf, hipStream_t s);
 // Wbar = A / D of the time averaging, [nc][5] in out
 void launch_avg_out(const Dev &D, double *out, hipStream_t s);
 

@@ -90,3 +90,10 @@ def test_buckets_of_every_length(name):
         run_pair(wl.sod(nx=4100, ny=2, nz=2, n_ref=12, kn=1e-3), 2, name=name, sampling=1)
     else:  # 16,464 tetrahedra
         run_pair(wl.closed_box(n=(14, 14, 14), n_ref=14, kn=0.2, tets=True, jitter=0.1, perturb=0.1), 2, name=name, sampling=1)
+
+
+@pytest.mark.parametrize("U", [0.0, 0.99, 1.01, 4.0])
+def test_inflow_speeds_on_both_sides_of_the_root_finders_rule(U):
+    """Faces with a = U.n / sigma in [-U, U]: the iteration above -1, the bisections below."""
+    run_pair(wl.free_stream_box(n=(3, 2, 2), U=(U, 0.0, 0.0), n_ref=20, kn=0.5, perturb=0.1), 2, vscale=3.0 + U,
+             name=f"inflow U={U}")

@@ -95,7 +95,7 @@ struct Scalars {
     unsigned long long moved_total;  // particles streamed since the state was set
     unsigned int err;
     unsigned int max_cross;  // the most face crossings of one particle in the step
-    unsigned int n_big;      // cells with more than 64 new particles this step (k_sample_big's list)
+    unsigned int n_big;      // cells with more than 64 new pairs this step (k_sample_big's list)
     unsigned int none;       // the step has no particle anywhere (old, sampled or entering)
 };
 
@@ -210,7 +210,7 @@ struct Dev {
     uint32_t *lsrc;         // [cap] the leaver's slot | kNewBit
     unsigned long long *perm; // [cap] leavers by end bucket: order << 32 | slot; during transport,
                               // the flight times of the lists' particles
-    int32_t *big;           // [nc] cells with more than 64 new particles (listed by k_sample)
+    int32_t *big;           // [nc] cells with more than 64 new pairs (listed by k_sample)
     Particles pa[2];
     Scalars *sc;
     // time averaging: steps n > avg_from are averaged (avg_from < 0: off)

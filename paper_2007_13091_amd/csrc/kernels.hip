@@ -323,6 +323,12 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
+// a value that every lane of the wave holds, as a scalar
+__device__ __forceinline__ long long uniform64(long long v) {
+    return ((long long)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+           (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
@@ -1326,29 +1332,30 @@ __global__ void __launch_bounds__(256) k_heat(Dev D, int buf) {
 }
 
 // ---------------------------------------------------------------------------------------
-// S3: hydro particles, one wave per cell, lane l takes the particles l, l + 64, ...  Pair
-// (2p, 2p+1) shares X ~ N(0, I) from Box-Muller on the draw keyed by the even partner's id:
-// X0, X1 = r1 (cos, sin)(2 pi e1), r1 = sqrt(-2 ln e0), and X2 = r2 cos(2 pi e3), r2 =
-// sqrt(-2 ln e2).  The even partner evaluates the first half, the odd one the second (the
-// same code on the other two uniforms), and they exchange halves.  Partners get
-// U + sqrt(T) X and U - sqrt(T) X, the pair of Sec. 2.4(b), and their own uniform position
-// (box: per axis; tetrahedron: Rocchini-Cignoni folding of the unit cube).  With the
-// energy-exact variant (sampling = 1, a departure from the paper) the deviations carry one
-// factor s per cell, s = sqrt(3 N_pairs / sum_j |X_j|^2): a first pass sums |X|^2 for s and
-// keeps each lane's first half for the second.
-// S = P + sum of phi over the new particles (fixed tree over the wave).
+// S3: hydro particles in pairs (2p, 2p+1), a lane per pair.  A pair shares X ~ N(0, I) from
+// Box-Muller on the draw keyed by the even partner's id: X0, X1 = r1 (cos, sin)(2 pi e1), r1 =
+// sqrt(-2 ln e0), and X2 = r2 cos(2 pi e3), r2 = sqrt(-2 ln e2).  Partners get U + sqrt(T) X and
+// U - sqrt(T) X, the pair of Sec. 2.4(b), and their own uniform position (box: per axis;
+// tetrahedron: Rocchini-Cignoni folding of the unit cube).  With the energy-exact variant
+// (sampling = 1, a departure from the paper) the deviations carry one factor s per cell,
+// s = sqrt(3 N_pairs / sum_j |X_j|^2): a first pass sums |X|^2 for s.
+// S = P + sum of phi over the new particles (fixed order over the cell's lanes).
 // ---------------------------------------------------------------------------------------
-// this lane's half of its pair's normal: (r cos a, r sin a), r = sqrt(-2 ln e0 or e2),
-// a = 2 pi e1 or e3 (odd lanes use only the cosine)
+// sine and cosine from one reduction of the argument (the same bits as the two calls)
+__device__ __forceinline__ void sin_cos(double a, double &s, double &c) { sincos(a, &s, &c); }
+__device__ __forceinline__ void sin_cos(float a, float &s, float &c) { sincosf(a, &s, &c); }
+
+// a pair's X ~ N(0, I) by Box-Muller on the draw keyed by the even partner's id
 template <typename R>
-__device__ __forceinline__ void half_normal(uint64_t seed, uint64_t puid, long long step, int inst, bool odd,
-                                            R &h0, R &h1) {
+__device__ __forceinline__ void pair_normal(uint64_t seed, uint64_t puid, long long step, int inst, R X[3]) {
     const R two_pi = (R)2 * (R)kPi;
     const U4 rv = draw(seed, puid, step, kTagVel, 0, inst);
-    const R ea = unif<R>(odd ? rv.v[2] : rv.v[0]), eb = unif<R>(odd ? rv.v[3] : rv.v[1]);
-    const R r = sqrt((R)-2 * log(ea));
-    h0 = r * cos(two_pi * eb);
-    h1 = r * sin(two_pi * eb);
+    const R r1 = sqrt((R)-2 * log(unif<R>(rv.v[0]))), r2 = sqrt((R)-2 * log(unif<R>(rv.v[2])));
+    R sn, cs;
+    sin_cos(two_pi * unif<R>(rv.v[1]), sn, cs);
+    X[0] = r1 * cs;
+    X[1] = r1 * sn;
+    X[2] = r2 * cos(two_pi * unif<R>(rv.v[3]));
 }
 // a uniform point of a cell from the draw (uid, step, kTagPos): per axis in a box, the unit cube
 // folded onto the tetrahedron (Rocchini-Cignoni) in a tetrahedron; org + s e1 + t e2 + w e3
@@ -1377,91 +1384,127 @@ __device__ __forceinline__ void cell_point(uint64_t seed, uint64_t uid, long lon
     for (int d = 0; d < 3; ++d) x[d] = org[d] + s * Ed[d] + t * Ed[3 + d] + w * Ed[6 + d];
 }
 
-// one cell's ns > 0 new particles by the whole wave in runs of 64 (ns is even, so a pair never
-// straddles two runs), and its S
-template <typename R, bool KE>
-__device__ __forceinline__ void sample_cell(const Dev &D, int buf, int c, long long ns) {
-    const int lane = lane_id();
+template <typename R>
+__device__ __forceinline__ void sample_state(const Dev &D, int c, R U[3], R &T) {
     const int nc = D.nc;
+    const double rho = D.W[c], m0 = D.W[nc + c], m1 = D.W[2 * nc + c], m2 = D.W[3 * nc + c], E = D.W[4 * nc + c];
+    U[0] = (R)(m0 / rho);
+    U[1] = (R)(m1 / rho);
+    U[2] = (R)(m2 / rho);
+    T = (R)((2.0 / (3.0 + D.K)) * (E - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho) / rho);
+}
+template <typename R>
+__device__ __forceinline__ void sample_geometry(const Dev &D, int c, int ns, R &msam, R org[3], R Ed[9], bool &tet) {
+    const int nc = D.nc;
+    msam = (R)(D.ec[c] * D.rhoh[c] * D.vol[c] / (double)ns);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) org[q] = (R)D.orig[q * nc + c];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) Ed[q] = (R)D.edge[q * nc + c];
+    tet = D.ctype[c] == 4;
+}
+// the two particles of a pair: U + sT X and U - sT X, each at its own point with its internal energy
+// e; their sums
+template <typename R, bool KE>
+__device__ __forceinline__ void put_pair(const Dev &D, const Particles &pa, int buf, long long span, long long place,
+                                         uint64_t seed, long long step, int inst, int cl, int k, const R U[3], R sT,
+                                         const R X[3], const R e2[2], R msam, const R org[3], const R Ed[9],
+                                         bool tet, double acc[5]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint64_t uid = make_uid(step, cl, k + q);
+        const long long i = slot_of(D, buf, span, place + q);
+        R u[3], x[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) u[d] = q == 0 ? U[d] + sT * X[d] : U[d] - sT * X[d];
+        cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
+        store_new(pa, i, x, u, msam, uid);
+        R e = (R)0;
+        if (KE) {
+            e = e2[q];
+            store_e(pa, i, e);
+        }
+        add_phi<R>(acc, msam, u, e);
+    }
+}
+// |X'|^2 of both particles' internal components
+template <typename R>
+__device__ __forceinline__ void pair_internal(uint64_t seed, long long step, int inst, int cl, int k, int K, R xi2[2]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) xi2[q] = internal_energy<R>(seed, make_uid(step, cl, k + q), step, kTagInt, 0, inst, K, (R)1);
+}
+
+// one cell's ns > 0 new particles by the whole wave, 64 pairs at a time, and its S (c and ns are
+// the wave's: the cell's data and the first rounds of the draws stay scalar)
+template <typename R, bool KE>
+__device__ __forceinline__ void sample_cell(const Dev &D, int buf, int c, int ns) {
+    const int lane = lane_id();
+    const int nc = D.nc, np = ns / 2;
     const Scalars *sc = D.sc;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     {
         const Particles pa = D.pa[buf];
         const long long span = sc->span[buf], base = sc->n_mov + D.samoff[c];
-        const int inst = inst_of(D, c);
+        const int inst = __builtin_amdgcn_readfirstlane(inst_of(D, c));
         const InstP &P = D.ip[inst];
-        const long long step = D.is[inst].step;
-        const unsigned long long seed = P.seed;
-        const int cl = c - P.cell0;  // ids carry the cell index within the instance
-        const double rho = D.W[c], m0 = D.W[nc + c], m1 = D.W[2 * nc + c], m2 = D.W[3 * nc + c], E = D.W[4 * nc + c];
-        const R U[3] = {(R)(m0 / rho), (R)(m1 / rho), (R)(m2 / rho)};
-        const R T = (R)((2.0 / (3.0 + D.K)) * (E - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho) / rho);
-        R sT = sqrt(T);
-        const int K = KE ? D.K : 0;  // KE: K > 0 (a compile-time switch, see add_rec)
-        // energy-exact variant with internal degrees of freedom: one factor K N_sam / sum_k |X'_k|^2
-        // on every particle's internal energy makes the sample's internal energy exact too
-        R fint = (R)1;
-        if (P.sampling == 1 && K > 0) {
-            R se = (R)0;
-            for (long long k = lane; k < ns; k += kWave)
-                se = se + internal_energy<R>(seed, make_uid(step, cl, k), step, kTagInt, 0, inst, K, (R)1);
-            double sd = wave_sum((double)se);
-            fint = (R)((double)K * (double)ns / sd);
-        }
-        const R one = (R)1;
-        const bool odd = (lane & 1) != 0;
+        const long long step = uniform64(D.is[inst].step);
+        const unsigned long long seed = (unsigned long long)uniform64((long long)P.seed);
+        const int cl = __builtin_amdgcn_readfirstlane(c - P.cell0);  // ids carry the cell index within the instance
         const bool exact = P.sampling == 1;
-        R f0 = (R)0, f1 = (R)0;  // this lane's half of its first pair's normal (energy-exact pass)
+        R U[3], T;
+        sample_state<R>(D, c, U, T);
+        R sT = sqrt(T), fint = (R)1;
+        // this lane's first pair's normal and internal components (energy-exact pass)
+        R F[3] = {(R)0, (R)0, (R)0}, Fi[2] = {(R)0, (R)0};
         if (exact) {
-            // energy-exact pairs: the pairs carry the momentum exactly; one factor on every
-            // thermal deviation of the cell, sqrt(3 N_pairs / sum_j |X_j|^2), makes the energy
-            // exact too (a first pass over the pairs' normal draws, summed in FP64)
-            double sx2 = 0.0;
-            for (long long k = lane; k < ns; k += kWave) {
-                R h0, h1;
-                half_normal<R>(seed, make_uid(step, cl, k & ~1LL), step, inst, odd, h0, h1);
-                if (k == lane) {
-                    f0 = h0;
-                    f1 = h1;
+            // energy-exact pairs: the pairs carry the momentum exactly; one factor on every thermal
+            // deviation of the cell, sqrt(3 N_pairs / sum_j |X_j|^2), makes the energy exact too (a
+            // first pass over the pairs' normal draws, summed in FP64); with internal degrees of
+            // freedom one factor K N_sam / sum_k |X'_k|^2 on every internal energy as well
+            double sx2 = 0.0, se = 0.0;
+            for (int p = lane; p < np; p += kWave) {
+                R X[3];
+                pair_normal<R>(seed, make_uid(step, cl, 2 * p), step, inst, X);
+                if (p == lane) {
+                    F[0] = X[0];
+                    F[1] = X[1];
+                    F[2] = X[2];
                 }
-                const double a = (double)h0, b = (double)h1;
-                sx2 += odd ? a * a : a * a + b * b;
+                const double x0 = (double)X[0], x1 = (double)X[1], x2 = (double)X[2];
+                sx2 += x0 * x0 + x1 * x1 + x2 * x2;
+                if (KE) {
+                    R xi2[2];
+                    pair_internal<R>(seed, step, inst, cl, 2 * p, D.K, xi2);
+                    if (p == lane) {
+                        Fi[0] = xi2[0];
+                        Fi[1] = xi2[1];
+                    }
+                    se += (double)xi2[0] + (double)xi2[1];
+                }
             }
             sx2 = wave_sum(sx2);
-            sT = (R)((double)sT * sqrt(3.0 * (double)(ns / 2) / sx2));
+            sT = (R)((double)sT * sqrt(3.0 * (double)np / sx2));
+            if (KE) fint = (R)((double)D.K * (double)ns / wave_sum(se));
         }
-        const double vol = D.vol[c];
-        const R msam = (R)(D.ec[c] * D.rhoh[c] * vol / (double)ns);
-        const R org[3] = {(R)D.orig[c], (R)D.orig[nc + c], (R)D.orig[2 * nc + c]};
-        R Ed[9];
-#pragma unroll
-        for (int q = 0; q < 9; ++q) Ed[q] = (R)D.edge[q * nc + c];
-        const bool tet = D.ctype[c] == 4;
-        // runs of 64 particles (ns is even, so a pair never straddles two runs)
-        for (long long k0 = 0; k0 < ns; k0 += kWave) {
-            const long long k = k0 + lane;
-            R h0 = f0, h1 = f1;
-            if ((k0 > 0 || !exact) && k < ns) half_normal<R>(seed, make_uid(step, cl, k & ~1LL), step, inst, odd, h0, h1);
-            const R X0 = __shfl(h0, lane & ~1), X1 = __shfl(h1, lane & ~1), X2 = __shfl(h0, lane | 1);
-            if (k < ns) {
-                const long long i = slot_of(D, buf, span, base + k);
-                const uint64_t uid = make_uid(step, cl, k);
-                const R sg = odd ? -one : one;
-                const R X[3] = {X0, X1, X2};
-                R u[3];
-#pragma unroll
-                for (int d = 0; d < 3; ++d) u[d] = U[d] + sg * (sT * X[d]);
-                R x[3];
-                cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
-                store_new(pa, i, x, u, msam, uid);
-                R e = (R)0;
-                if (K > 0) {
-                    e = internal_energy<R>(seed, uid, step, kTagInt, 0, inst, K, T);
-                    if (P.sampling == 1) e = e * fint;
-                    store_e(pa, i, e);
-                }
-                add_phi<R>(acc, msam, u, e);
+        R msam, org[3], Ed[9];
+        bool tet;
+        sample_geometry<R>(D, c, ns, msam, org, Ed, tet);
+        for (int p0 = 0; p0 < np; p0 += kWave) {
+            const int p = p0 + lane;
+            if (p >= np) continue;
+            R X[3] = {F[0], F[1], F[2]}, e2[2] = {Fi[0], Fi[1]};
+            if (p0 > 0 || !exact) {
+                pair_normal<R>(seed, make_uid(step, cl, 2 * p), step, inst, X);
+                if (KE) pair_internal<R>(seed, step, inst, cl, 2 * p, D.K, e2);
             }
+            e2[0] = T * e2[0];
+            e2[1] = T * e2[1];
+            if (exact) {
+                e2[0] = e2[0] * fint;
+                e2[1] = e2[1] * fint;
+            }
+            put_pair<R, KE>(D, pa, buf, span, base + 2 * p, seed, step, inst, cl, 2 * p, U, sT, X, e2, msam, org, Ed, tet,
+                            acc);
         }
     }
 #pragma unroll
@@ -1485,13 +1528,14 @@ __device__ __forceinline__ double seg_sum(double v, int first, int last) {
     return __shfl(v, last);
 }
 
-// Each wave takes G consecutive cells: runs of consecutive cells whose new particles fit in 64
-// lanes together are sampled at once, lane by lane in cell order (most cells sample a few
-// particles: one wave per cell left most lanes idle).  G = 8 on meshes of 32768 cells or more;
-// a smaller mesh would leave most of the chip idle with a wave per 8 cells, and takes G = 1.  A
-// cell with more than 64 is k_sample_big's.  A pair's partners sit in neighbouring lanes of
-// one cell (every count and prefix is even); the energy-exact factor and S come from
-// segmented sums over the cell's lanes.  The arithmetic per particle is that of sample_cell.
+// Each wave takes G consecutive cells: runs of consecutive cells whose new pairs fit in 64 lanes
+// together are sampled at once, a pair per lane in cell order (most cells sample a few
+// particles: one wave per cell left most lanes idle).  G = 8 on meshes of 32768 cells or more; a
+// smaller mesh would leave most of the chip idle with a wave per 8 cells, and takes G = 1.  A cell
+// with more than 64 pairs is k_sample_big's.  The energy-exact factor and S come from segmented
+// sums over the cell's lanes.  What bounds it: the vector ALU (Philox, logarithms, sines), so a lane
+// takes a whole pair: the pair's draw and its two logarithms and angles are evaluated once
+// instead of by both partners.
 template <typename R, int WPB, bool KE, int G>
 __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3))) k_sample(Dev D, int buf) {
     const int wave = threadIdx.x / kWave;
@@ -1511,15 +1555,15 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
         else
             myns = sc->n_new > 0 ? (int)D.nsam[c] : 0;  // even, at most 2^20
     }
-    // wave-uniform counts and prefixes (scalar registers)
-    int ns[G];
+    // wave-uniform pair counts and prefixes (scalar registers)
+    int np[G];
     int pre[G + 1];
     pre[0] = 0;
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-        ns[j] = __builtin_amdgcn_readfirstlane(__shfl(myns, j));
-        const int n = ns[j] > 0 ? ns[j] : 0;
-        pre[j + 1] = pre[j] + (n <= kWave ? n : kWave + 1);
+        const int n = __builtin_amdgcn_readlane(myns, j);
+        np[j] = n > 0 ? n / 2 : n;
+        pre[j + 1] = pre[j] + (n <= 0 ? 0 : (np[j] <= kWave ? np[j] : kWave + 1));
     }
     // cells without new particles: S = P (the five loads issued before the first store)
     if (lane < G && myns == 0) {
@@ -1530,9 +1574,9 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
 #pragma unroll
         for (int k = 0; k < 5; ++k) D.S[k * nc + c] = pv[k] + 0.0;
     }
-    // cells with more than 64 new particles go to k_sample_big's list (one atomic per wave)
+    // cells with more than 64 pairs go to k_sample_big's list (one atomic per wave)
     {
-        const bool big = lane < G && myns > kWave;
+        const bool big = lane < G && myns > 2 * kWave;
         const unsigned long long mb = __ballot(big);
         if (mb) {
             const int first = __ffsll((long long)mb) - 1;
@@ -1546,26 +1590,33 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
     int g = 0;
     while (g < G) {
         if (c0 + g >= nc) break;
-        if (ns[g] > kWave) {
-            ++g;  // k_sample_big's
-            continue;
+        // wave-uniform: the longest run [g, h) of cells whose pairs fit in 64 lanes
+        int h = g + 1, pg = 0, ph = 0;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j == g) {
+                pg = pre[j];
+                ph = pre[j + 1];
+            }
+            if (j == h && j > g && c0 + j < nc && pre[j + 1] - pg <= kWave) {
+                h = j + 1;
+                ph = pre[j + 1];
+            }
         }
-        // the longest run [g, h) of cells of at most 64 particles each that fits in 64 lanes
-        int h = g + 1;
+        const int nrun = ph - pg;
+        if (nrun > 0 && nrun <= kWave) {
+            // this lane's cell j of the run and its pair p there
+            int j = g, first = lane, last = lane, npj = 0;
 #pragma unroll
-        for (int j = 0; j < G; ++j)
-            if (j >= h && j == h && c0 + j < nc && ns[j] <= kWave && pre[j + 1] - pre[g] <= kWave) h = j + 1;
-        const int nrun = pre[h] - pre[g];
-        if (nrun > 0) {
-            // this lane's cell j of the run and its particle k there
-            int j = g;
-#pragma unroll
-            for (int jj = 0; jj < G; ++jj)
-                if (jj > g && jj < h && pre[jj] - pre[g] <= lane) j = jj;
+            for (int i = 0; i < G; ++i)
+                if (i >= g && i < h && pre[i] - pg <= lane && pre[i + 1] - pg > lane) {
+                    j = i;
+                    first = pre[i] - pg;
+                    last = pre[i + 1] - pg - 1;
+                    npj = np[i];
+                }
             const bool act = lane < nrun;
-            const int first = act ? pre[j] - pre[g] : lane, last = act ? pre[j + 1] - pre[g] - 1 : lane;
-            const long long k = act ? (long long)(lane - first) : 0;
-            const long long nsj = act ? (long long)ns[j] : 0;
+            const int k = 2 * (lane - first);  // its even partner's number
             const int c = c0 + j;
             double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
             const Particles pa = D.pa[buf];
@@ -1575,58 +1626,41 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
             const unsigned long long seed = P.seed;
             const int cl = c - P.cell0;
             const bool exact = P.sampling == 1;
-            const bool odd = (k & 1) != 0;
-            R h0 = (R)0, h1 = (R)0, sT = (R)0, T = (R)0, fint = (R)1;
-            R U[3] = {(R)0, (R)0, (R)0};
-            const int K = KE ? D.K : 0;
+            R U[3] = {(R)0, (R)0, (R)0}, X[3] = {(R)0, (R)0, (R)0}, e2[2] = {(R)0, (R)0}, sT = (R)0, T = (R)0;
             double sx2 = 0.0, se = 0.0;
             if (act) {
-                const double rho = D.W[c], m0 = D.W[nc + c], m1 = D.W[2 * nc + c], m2 = D.W[3 * nc + c],
-                             E = D.W[4 * nc + c];
-                U[0] = (R)(m0 / rho);
-                U[1] = (R)(m1 / rho);
-                U[2] = (R)(m2 / rho);
-                T = (R)((2.0 / (3.0 + D.K)) * (E - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho) / rho);
+                sample_state<R>(D, c, U, T);
                 sT = sqrt(T);
-                half_normal<R>(seed, make_uid(step, cl, k & ~1LL), step, inst, odd, h0, h1);
-                const double a = (double)h0, b = (double)h1;
-                sx2 = odd ? a * a : a * a + b * b;
-                if (exact && K > 0) se = (double)internal_energy<R>(seed, make_uid(step, cl, k), step, kTagInt, 0, inst, K, (R)1);
+                pair_normal<R>(seed, make_uid(step, cl, k), step, inst, X);
+                const double x0 = (double)X[0], x1 = (double)X[1], x2 = (double)X[2];
+                sx2 = x0 * x0 + x1 * x1 + x2 * x2;
+                if (KE) {
+                    pair_internal<R>(seed, step, inst, cl, k, D.K, e2);
+                    se = (double)e2[0] + (double)e2[1];
+                    e2[0] = T * e2[0];
+                    e2[1] = T * e2[1];
+                }
             }
             // energy-exact pairs: one factor per cell on every thermal deviation, sqrt(3 N_pairs /
             // sum_j |X_j|^2), and (K > 0) K N_sam / sum_k |X'_k|^2 on every internal energy
-            sx2 = seg_sum(sx2, first, last);
-            if (KE) se = seg_sum(se, first, last);
-            if (act && exact) {
-                sT = (R)((double)sT * sqrt(3.0 * (double)(nsj / 2) / sx2));
-                if (K > 0) fint = (R)((double)K * (double)nsj / se);
+            if (__ballot(act && exact)) {
+                sx2 = seg_sum(sx2, first, last);
+                if (KE) se = seg_sum(se, first, last);
             }
-            const R X0 = __shfl(h0, lane & ~1), X1 = __shfl(h1, lane & ~1), X2 = __shfl(h0, lane | 1);
+            if (act && exact) {
+                sT = (R)((double)sT * sqrt(3.0 * (double)npj / sx2));
+                if (KE) {
+                    const R fint = (R)((double)D.K * (double)(2 * npj) / se);
+                    e2[0] = e2[0] * fint;
+                    e2[1] = e2[1] * fint;
+                }
+            }
             if (act) {
                 const long long span = sc->span[buf], base = sc->n_mov + D.samoff[c];
-                const R msam = (R)(D.ec[c] * D.rhoh[c] * D.vol[c] / (double)nsj);
-                const R org[3] = {(R)D.orig[c], (R)D.orig[nc + c], (R)D.orig[2 * nc + c]};
-                R Ed[9];
-#pragma unroll
-                for (int q = 0; q < 9; ++q) Ed[q] = (R)D.edge[q * nc + c];
-                const bool tet = D.ctype[c] == 4;
-                const long long i = slot_of(D, buf, span, base + k);
-                const uint64_t uid = make_uid(step, cl, k);
-                const R sg = odd ? (R)-1 : (R)1;
-                const R X[3] = {X0, X1, X2};
-                R u[3];
-#pragma unroll
-                for (int d = 0; d < 3; ++d) u[d] = U[d] + sg * (sT * X[d]);
-                R x[3];
-                cell_point<R>(seed, uid, step, inst, org, Ed, tet, x);
-                store_new(pa, i, x, u, msam, uid);
-                R e = (R)0;
-                if (K > 0) {
-                    e = internal_energy<R>(seed, uid, step, kTagInt, 0, inst, K, T);
-                    if (exact) e = e * fint;
-                    store_e(pa, i, e);
-                }
-                add_phi<R>(acc, msam, u, e);
+                R msam, org[3], Ed[9];
+                bool tet;
+                sample_geometry<R>(D, c, 2 * npj, msam, org, Ed, tet);
+                put_pair<R, KE>(D, pa, buf, span, base + k, seed, step, inst, cl, k, U, sT, X, e2, msam, org, Ed, tet, acc);
             }
 #pragma unroll
             for (int q = 0; q < 5; ++q) acc[q] = seg_sum(acc[q], first, last);
@@ -1642,7 +1676,7 @@ __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(3
     }
 }
 
-// The cells with more than 64 new particles, which k_sample listed, one wave each (a launch
+// The cells with more than 64 new pairs, which k_sample listed, one wave each (a launch
 // of its own, so that its registers do not add to k_sample's); the waves take the list in a
 // grid-stride loop (a cell's particles do not depend on which wave samples it).
 template <typename R, bool KE>
@@ -1650,8 +1684,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) k
     const long long nb = (long long)D.sc->n_big;
     const long long waves = (long long)gridDim.x * 8;
     for (long long k = (long long)blockIdx.x * 8 + (int)(threadIdx.x / kWave); k < nb; k += waves) {
-        const int c = D.big[k];
-        sample_cell<R, KE>(D, buf, c, D.nsam[c]);
+        const int c = __builtin_amdgcn_readfirstlane(D.big[k]);
+        sample_cell<R, KE>(D, buf, c, __builtin_amdgcn_readfirstlane((int)D.nsam[c]));
     }
 }
 
@@ -1763,8 +1797,9 @@ __global__ void __launch_bounds__(256) k_sample_gp(Dev D, int buf) {
             const uint64_t uidp = make_uid(step, cl, p);
             const U4 rv = draw(seed, uidp, step, kTagGP, 0u, inst);
             const R r1 = sqrt((R)-2 * log(unif<R>(rv.v[0]))), r2 = sqrt((R)-2 * log(unif<R>(rv.v[2])));
-            const R a1 = two_pi * unif<R>(rv.v[1]), a2 = two_pi * unif<R>(rv.v[3]);
-            const R X[3] = {(R)(r1 * cos(a1)), (R)(r1 * sin(a1)), (R)(r2 * cos(a2))};
+            R sn, cs;
+            sin_cos(two_pi * unif<R>(rv.v[1]), sn, cs);
+            const R X[3] = {(R)(r1 * cs), (R)(r1 * sn), (R)(r2 * cos(two_pi * unif<R>(rv.v[3])))};
 #pragma unroll
             for (int d = 0; d < 3; ++d) u[d] = U[d] + sT * X[d];
             e = (R)0;

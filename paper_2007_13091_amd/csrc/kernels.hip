@@ -837,18 +837,10 @@ __device__ __forceinline__ void frame_derivs(const double *G, long long stride, 
     }
 }
 
-// second-order flux between two sides (face frame), per unit area:
-//   W0 from the upwind half moments; side slopes; abar_d from W_x = rho_l <(a_l . psi) psi>_{>0}
-//   + rho_r <(a_r . psi) psi>_{<0}; Abar from <(u abar_n + v abar_t1 + w abar_t2 + Abar) . psi psi> = 0;
-//   F = rho0 [q1 <u psi> + q2 <u (u.abar) psi> + q3 <u Abar psi>]
-//     + sum_s rho^h_s [(q4 - dt e) <u psi>_s + (q5 + dt^2 e/2) <u (u.a~_s) psi>_s]
-// (Shakhov model: + q1 qsh in energy, as in flux_pair)
+// W0 of a face from the upwind half moments, as primitives
 template <typename R>
-__device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref, R omega, R c2, bool gks, R qsh,
-                           R Ff[5]) {
-    Mom3<R> ML, MR, M0;
-    mom3<R>(1, L.g, ML);
-    mom3<R>(-1, Rs.g, MR);
+__device__ __forceinline__ void face_state(const Side2<R> &L, const Side2<R> &Rs, const Mom3<R> &ML, const Mom3<R> &MR,
+                                           Prim<R> &z) {
     R W0[5];
     {
         const R one[5] = {(R)1, (R)0, (R)0, (R)0, (R)0};
@@ -858,7 +850,6 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
 #pragma unroll
         for (int k = 0; k < 5; ++k) W0[k] = L.g.rho * Hl[k] + Rs.g.rho * Hr[k];
     }
-    Prim<R> z;
     z.rho = W0[0];
     z.un = W0[1] / W0[0];
     z.v = W0[2] / W0[0];
@@ -866,32 +857,42 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
     z.K = L.g.K;
     z.T = ((R)2 / (R)(3 + z.K)) * (W0[4] - (R)0.5 * (W0[1] * W0[1] + W0[2] * W0[2] + W0[3] * W0[3]) / W0[0]) / W0[0];
     z.lam = (R)1 / ((R)2 * z.T);
-    mom3<R>(0, z, M0);
-    R abar[3][5];
+}
+// the slope abar_A along axis A (0 n, 1 t1, 2 t2) from
+// W_x = rho_l <(a_l . psi) psi>_{>0} + rho_r <(a_r . psi) psi>_{<0}
+template <int A, typename R>
+__device__ __forceinline__ void face_slope(const Side2<R> &L, const Side2<R> &Rs, const Mom3<R> &ML, const Mom3<R> &MR,
+                                           const Prim<R> &z, R abar[5]) {
+    R al[5], ar[5], Sl[5], Sr[5], Wx[5];
+    slope_of<R>(L.g, L.dW[A], al);
+    slope_of<R>(Rs.g, Rs.dW[A], ar);
+    gvec<0, 0, 0, R>(ML, al, Sl);
+    gvec<0, 0, 0, R>(MR, ar, Sr);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        R al[5], ar[5], Sl[5], Sr[5], Wx[5];
-        slope_of<R>(L.g, L.dW[d], al);
-        slope_of<R>(Rs.g, Rs.dW[d], ar);
-        gvec<0, 0, 0, R>(ML, al, Sl);
-        gvec<0, 0, 0, R>(MR, ar, Sr);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) Wx[k] = L.g.rho * Sl[k] + Rs.g.rho * Sr[k];
-        slope_of<R>(z, Wx, abar[d]);
-    }
-    R At[5];
-    {
-        R t0[5], t1[5], t2[5], bt[5];
-        gvec<1, 0, 0, R>(M0, abar[0], t0);
-        gvec<0, 1, 0, R>(M0, abar[1], t1);
-        gvec<0, 0, 1, R>(M0, abar[2], t2);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) bt[k] = -(t0[k] + t1[k] + t2[k]);
-        slope<R>(z, bt, At);
-    }
+    for (int k = 0; k < 5; ++k) Wx[k] = L.g.rho * Sl[k] + Rs.g.rho * Sr[k];
+    slope_of<R>(z, Wx, abar);
+}
+// <u_A (a . psi) psi>, u_A the velocity along axis A, and <u u_A (a . psi) psi>
+template <int A, typename R>
+__device__ __forceinline__ void gaxis(const Mom3<R> &M, const R a[5], R out[5]) {
+    gvec<A == 0, A == 1, A == 2, R>(M, a, out);
+}
+template <int A, typename R>
+__device__ __forceinline__ void guaxis(const Mom3<R> &M, const R a[5], R out[5]) {
+    gvec<1 + (A == 0), A == 1, A == 2, R>(M, a, out);
+}
+// <u u_A (a~_A . psi) psi> of a side's hydro part
+template <int A, typename R>
+__device__ __forceinline__ void hydro_axis(const Mom3<R> &MH, const Side2<R> &S, R out[5]) {
+    R ah[5];
+    slope_of<R>(S.h, S.dWh[A], ah);
+    guaxis<A, R>(MH, ah, out);
+}
+template <typename R>
+__device__ __forceinline__ void face_q(const Side2<R> &L, const Side2<R> &Rs, const Prim<R> &z, R dt, R mu_ref, R omega,
+                                       R c2, bool gks, R q[5]) {
     const R pl = L.g.rho * L.g.T, pr = Rs.g.rho * Rs.g.T;
     const R tau = mu_ref * pow(z.T, omega) / (z.rho * z.T) + c2 * (fabs(pl - pr) / (pl + pr)) * dt;
-    R q[5];
     qcoef5<R>(dt, tau, q);
     if (gks) {
         // wave-only start: q4 = (q4 - dt e) + dt e, q5 = (q5 + dt^2 e / 2) - dt^2 e / 2
@@ -899,15 +900,56 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
         q[3] = q[3] + dt * e;
         q[4] = q[4] - (R)0.5 * dt * dt * e;
     }
-    {
-        R G0[5], X0[5], X1[5], X2[5], GA[5];
-        uvec<R>(M0, G0);
-        gvec<2, 0, 0, R>(M0, abar[0], X0);
-        gvec<1, 1, 0, R>(M0, abar[1], X1);
-        gvec<1, 0, 1, R>(M0, abar[2], X2);
-        gvec<1, 0, 0, R>(M0, At, GA);
+}
+// the equilibrium part of the flux from t = sum_A <u_A (abar_A . psi) psi> and
+// X = sum_A <u u_A (abar_A . psi) psi>
+template <typename R>
+__device__ __forceinline__ void face_eq(const Prim<R> &z, const Mom3<R> &M0, const R t[5], const R X[5], const R q[5],
+                                        R Ff[5]) {
+    R At[5], bt[5], G0[5], GA[5];
 #pragma unroll
-        for (int k = 0; k < 5; ++k) Ff[k] = z.rho * (q[0] * G0[k] + q[1] * (X0[k] + X1[k] + X2[k]) + q[2] * GA[k]);
+    for (int k = 0; k < 5; ++k) bt[k] = -t[k];
+    slope<R>(z, bt, At);
+    uvec<R>(M0, G0);
+    gvec<1, 0, 0, R>(M0, At, GA);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) Ff[k] = z.rho * (q[0] * G0[k] + q[1] * X[k] + q[2] * GA[k]);
+}
+
+// second-order flux between two sides (face frame), per unit area:
+//   W0 from the upwind half moments; side slopes; abar_d as above;
+//   Abar from <(u abar_n + v abar_t1 + w abar_t2 + Abar) . psi psi> = 0;
+//   F = rho0 [q1 <u psi> + q2 <u (u.abar) psi> + q3 <u Abar psi>]
+//     + sum_s rho^h_s [(q4 - dt e) <u psi>_s + (q5 + dt^2 e/2) <u (u.a~_s) psi>_s]
+// (Shakhov model: + q1 qsh in energy, as in flux_pair)
+template <typename R>
+__device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref, R omega, R c2, bool gks, R qsh,
+                           R Ff[5]) {
+    Mom3<R> ML, MR, M0;
+    mom3<R>(1, L.g, ML);
+    mom3<R>(-1, Rs.g, MR);
+    Prim<R> z;
+    face_state<R>(L, Rs, ML, MR, z);
+    mom3<R>(0, z, M0);
+    R abar[3][5];
+    face_slope<0, R>(L, Rs, ML, MR, z, abar[0]);
+    face_slope<1, R>(L, Rs, ML, MR, z, abar[1]);
+    face_slope<2, R>(L, Rs, ML, MR, z, abar[2]);
+    R q[5];
+    face_q<R>(L, Rs, z, dt, mu_ref, omega, c2, gks, q);
+    {
+        R t[5], X[5], y[5], v[5];
+        gaxis<0, R>(M0, abar[0], t);
+        gaxis<1, R>(M0, abar[1], y);
+        gaxis<2, R>(M0, abar[2], v);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) t[k] = t[k] + y[k] + v[k];
+        guaxis<0, R>(M0, abar[0], X);
+        guaxis<1, R>(M0, abar[1], y);
+        guaxis<2, R>(M0, abar[2], v);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) X[k] = X[k] + y[k] + v[k];
+        face_eq<R>(z, M0, t, X, q, Ff);
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -915,24 +957,20 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
         if (!(S.h.rho > (R)0)) continue;
         Mom3<R> MH;
         mom3<R>(s == 0 ? 1 : -1, S.h, MH);
-        R ah[5], Gh[5], Y[5], acc[5];
+        R Gh[5], Y[5], acc[5];
         uvec<R>(MH, Gh);
-        slope_of<R>(S.h, S.dWh[0], ah);
-        gvec<2, 0, 0, R>(MH, ah, acc);
-        slope_of<R>(S.h, S.dWh[1], ah);
-        gvec<1, 1, 0, R>(MH, ah, Y);
+        hydro_axis<0, R>(MH, S, acc);
+        hydro_axis<1, R>(MH, S, Y);
 #pragma unroll
         for (int k = 0; k < 5; ++k) acc[k] += Y[k];
-        slope_of<R>(S.h, S.dWh[2], ah);
-        gvec<1, 0, 1, R>(MH, ah, Y);
+        hydro_axis<2, R>(MH, S, Y);
 #pragma unroll
         for (int k = 0; k < 5; ++k) Ff[k] += S.h.rho * (q[3] * Gh[k] + q[4] * (acc[k] + Y[k]));
     }
     if (qsh != (R)0) Ff[4] = Ff[4] + q[0] * qsh;
 }
 
-
-// Gradients for second order, one cell per thread, FP64 in both forms: the unweighted
+// Gradients for second order, FP64 in both forms: the unweighted
 // least-squares gradient over the face neighbours of the 5 components of W and of the hydro
 // state (rho^h / rho) W; boundary ghosts at the centre mirrored in the face plane (specular:
 // mirror state; diffuse: the cell's density and temperature, velocity reflected about the
@@ -941,56 +979,68 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
 // non-physical (rho <= 0, T <= 0, hydro density < 0 or hydro temperature <= 0) falls back to
 // first order; a face hydro density within 1e-12 of the face density of zero counts as zero
 // (roundoff of an empty hydro part, which the limiter can pin to a neighbour's zero).
-__global__ void __launch_bounds__(128) k_grad(Dev D) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= D.nc) return;
-    const int nc = D.nc;
+// Bound by the latency of dependent loads and by its FP64 divisions (two a face and component in
+// the limiter), not by its bytes.  Five waves have 64 cells, each one component of W and of the hydro
+// state; the values and gradients meet in local memory for the face states, a face a wave.  One
+// thread per cell held ten components and their gradients in registers, one wave per SIMD:
+// 32,768 cells 30 us, now 19.5; the 2,709 cells of a 301 x 3 x 3 tube 26 us, now 12.7.  Ten waves of one component each:
+// 32 and 11.3 us, the neighbours' centres and densities read twice as often.
+constexpr int kGradCells = kWave;
+
+__global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
+    __shared__ double sv[10][4][kGradCells];  // cell value and limited gradient by component (W, hydro)
+    __shared__ int sok[kGradCells];
+    const int cl = lane_id(), kk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int nc = D.nc, c0 = blockIdx.x * kGradCells + cl;
+    const bool in = c0 < nc;
+    const int c = in ? c0 : nc - 1;
     const InstP &P = D.ip[inst_of(D, c)];
-    if (P.recon == 0) return;
-    double vc[10];
-    const double fc = D.rhoh[c] / D.W[c];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        vc[k] = D.W[k * nc + c];
-        vc[5 + k] = fc * vc[k];
-    }
-    const double xc[3] = {D.xc[c], D.xc[nc + c], D.xc[2 * nc + c]};
-    double A00 = 0, A01 = 0, A02 = 0, A11 = 0, A12 = 0, A22 = 0;
-    double r[10][3], vmax[10], vmin[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) {
-        r[k][0] = r[k][1] = r[k][2] = 0.0;
-        vmax[k] = vmin[k] = vc[k];
-    }
+    const bool live = in && P.recon != 0;
+    if (kk == 0) sok[cl] = 1;
     const int nfc = D.nfc[c];
-    for (int lf = 0; lf < nfc; ++lf) {
-        const int2 nbl = D.nbl[c * 6 + lf];
-        double xj[3], vj[10];
-        if (nbl.x >= 0) {
-            const int j = nbl.x;
-            const double fj = D.rhoh[j] / D.W[j];
+    const double *lfx = D.lfx + (long long)c * 18;
+    double Wc[5], g[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
 #pragma unroll
-            for (int d = 0; d < 3; ++d) xj[d] = D.xc[d * nc + j];
+    for (int i = 0; i < 5; ++i) Wc[i] = D.W[i * nc + c];
+    const double fc = D.rhoh[c] / Wc[0];
+    const double xc[3] = {D.xc[c], D.xc[nc + c], D.xc[2 * nc + c]};
+    // component kk of a state in registers
+    auto comp = [kk](const double v[5]) {
+        return kk == 0 ? v[0] : kk == 1 ? v[1] : kk == 2 ? v[2] : kk == 3 ? v[3] : v[4];
+    };
+    double vc[2];
+    vc[0] = comp(Wc);
+    vc[1] = fc * vc[0];
+    if (live) {
+        int nb[6];
+        double xj[6][3], vj[6][2];
 #pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                vj[k] = D.W[k * nc + j];
-                vj[5 + k] = fj * vj[k];
-            }
-        } else {
+        for (int lf = 0; lf < 6; ++lf) nb[lf] = lf < nfc ? D.nbl[c * 6 + lf].x : c;
+        // every neighbour's loads before the first use
+#pragma unroll
+        for (int lf = 0; lf < 6; ++lf) {
+            const int j = nb[lf] >= 0 ? nb[lf] : c;
+            vj[lf][0] = D.W[kk * nc + j];
+            vj[lf][1] = D.rhoh[j] / D.W[j] * vj[lf][0];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) xj[lf][d] = D.xc[d * nc + j];
+        }
+#pragma unroll
+        for (int lf = 0; lf < 6; ++lf) {
+            if (nb[lf] >= 0) continue;
             const double4 pl = D.plane[c * 6 + lf];
             const double nn[3] = {pl.x, pl.y, pl.z};
             const double dist = pl.w - (nn[0] * xc[0] + nn[1] * xc[1] + nn[2] * xc[2]);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) xj[d] = xc[d] + 2.0 * dist * nn[d];
-            const DevBC &b = D.bc[-1 - nbl.x];
+            for (int d = 0; d < 3; ++d) xj[lf][d] = xc[d] + 2.0 * dist * nn[d];
+            const DevBC &b = D.bc[-1 - nb[lf]];
             if (b.type == 2) {
-#pragma unroll
-                for (int k = 0; k < 5; ++k) vj[k] = vj[5 + k] = b.Winf[k];
+                vj[lf][0] = vj[lf][1] = b.Winf[kk];
             } else {
-                const double rho = vc[0];
-                const double U[3] = {vc[1] / rho, vc[2] / rho, vc[3] / rho};
-                const double T = temp_k(vc, D.K);
-                double Ug[3];
+                const double rho = Wc[0];
+                const double U[3] = {Wc[1] / rho, Wc[2] / rho, Wc[3] / rho};
+                const double T = temp_k(Wc, D.K);
+                double Ug[3], vg[5];
                 if (b.type == 0) {
                     const double un = U[0] * nn[0] + U[1] * nn[1] + U[2] * nn[2];
 #pragma unroll
@@ -999,89 +1049,98 @@ __global__ void __launch_bounds__(128) k_grad(Dev D) {
 #pragma unroll
                     for (int d = 0; d < 3; ++d) Ug[d] = 2.0 * b.Uw[d] - U[d];
                 }
-                vj[0] = rho;
+                vg[0] = rho;
 #pragma unroll
-                for (int d = 0; d < 3; ++d) vj[1 + d] = rho * Ug[d];
-                vj[4] = 0.5 * rho * (Ug[0] * Ug[0] + Ug[1] * Ug[1] + Ug[2] * Ug[2]) + 0.5 * (3.0 + D.K) * rho * T;
-#pragma unroll
-                for (int k = 0; k < 5; ++k) vj[5 + k] = fc * vj[k];
+                for (int d = 0; d < 3; ++d) vg[1 + d] = rho * Ug[d];
+                vg[4] = 0.5 * rho * (Ug[0] * Ug[0] + Ug[1] * Ug[1] + Ug[2] * Ug[2]) + 0.5 * (3.0 + D.K) * rho * T;
+                vj[lf][0] = comp(vg);
+                vj[lf][1] = fc * vj[lf][0];
             }
         }
-        const double dx[3] = {xj[0] - xc[0], xj[1] - xc[1], xj[2] - xc[2]};
-        A00 += dx[0] * dx[0];
-        A01 += dx[0] * dx[1];
-        A02 += dx[0] * dx[2];
-        A11 += dx[1] * dx[1];
-        A12 += dx[1] * dx[2];
-        A22 += dx[2] * dx[2];
+        double A00 = 0, A01 = 0, A02 = 0, A11 = 0, A12 = 0, A22 = 0;
+        double r[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, vmax[2] = {vc[0], vc[1]}, vmin[2] = {vc[0], vc[1]};
 #pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            const double dv = vj[k] - vc[k];
-            r[k][0] += dx[0] * dv;
-            r[k][1] += dx[1] * dv;
-            r[k][2] += dx[2] * dv;
-            vmax[k] = fmax(vmax[k], vj[k]);
-            vmin[k] = fmin(vmin[k], vj[k]);
+        for (int lf = 0; lf < 6; ++lf) {
+            if (lf >= nfc) break;
+            const double dx[3] = {xj[lf][0] - xc[0], xj[lf][1] - xc[1], xj[lf][2] - xc[2]};
+            A00 += dx[0] * dx[0];
+            A01 += dx[0] * dx[1];
+            A02 += dx[0] * dx[2];
+            A11 += dx[1] * dx[1];
+            A12 += dx[1] * dx[2];
+            A22 += dx[2] * dx[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double dv = vj[lf][h] - vc[h];
+                r[h][0] += dx[0] * dv;
+                r[h][1] += dx[1] * dv;
+                r[h][2] += dx[2] * dv;
+                vmax[h] = fmax(vmax[h], vj[lf][h]);
+                vmin[h] = fmin(vmin[h], vj[lf][h]);
+            }
         }
-    }
-    // inverse of the symmetric normal matrix by cofactors
-    const double C00 = A11 * A22 - A12 * A12, C01 = A02 * A12 - A01 * A22, C02 = A01 * A12 - A02 * A11;
-    const double C11 = A00 * A22 - A02 * A02, C12 = A02 * A01 - A00 * A12, C22 = A00 * A11 - A01 * A01;
-    const double det = A00 * C00 + A01 * C01 + A02 * C02;
-    double g[10][3];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) {
-        g[k][0] = (C00 * r[k][0] + C01 * r[k][1] + C02 * r[k][2]) / det;
-        g[k][1] = (C01 * r[k][0] + C11 * r[k][1] + C12 * r[k][2]) / det;
-        g[k][2] = (C02 * r[k][0] + C12 * r[k][1] + C22 * r[k][2]) / det;
-    }
-    const double *lfx = D.lfx + (long long)c * 18;
-    {
-        const double h = cbrt(D.vol[c]);
-        const double kh = P.venkat_k * h;
+        // inverse of the symmetric normal matrix by cofactors
+        const double C00 = A11 * A22 - A12 * A12, C01 = A02 * A12 - A01 * A22, C02 = A01 * A12 - A02 * A11;
+        const double C11 = A00 * A22 - A02 * A02, C12 = A02 * A01 - A00 * A12, C22 = A00 * A11 - A01 * A01;
+        const double det = A00 * C00 + A01 * C01 + A02 * C02;
+        const double kh = P.venkat_k * cbrt(D.vol[c]);
         const double eps2 = kh * kh * kh;
 #pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            double phi = 1.0;
-            for (int lf = 0; lf < nfc; ++lf) {
-                const double Dk = g[k][0] * (lfx[3 * lf] - xc[0]) + g[k][1] * (lfx[3 * lf + 1] - xc[1]) +
-                                  g[k][2] * (lfx[3 * lf + 2] - xc[2]);
+        for (int h = 0; h < 2; ++h) {
+            g[h][0] = (C00 * r[h][0] + C01 * r[h][1] + C02 * r[h][2]) / det;
+            g[h][1] = (C01 * r[h][0] + C11 * r[h][1] + C12 * r[h][2]) / det;
+            g[h][2] = (C02 * r[h][0] + C12 * r[h][1] + C22 * r[h][2]) / det;
+        }
+        double phi[2] = {1.0, 1.0};
+        for (int lf = 0; lf < nfc; ++lf) {
+            const double dx[3] = {lfx[3 * lf] - xc[0], lfx[3 * lf + 1] - xc[1], lfx[3 * lf + 2] - xc[2]};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double Dk = g[h][0] * dx[0] + g[h][1] * dx[1] + g[h][2] * dx[2];
                 double pf = 1.0;
                 if (Dk != 0.0) {
-                    const double M = Dk > 0.0 ? vmax[k] - vc[k] : vmin[k] - vc[k];
+                    const double M = Dk > 0.0 ? vmax[h] - vc[h] : vmin[h] - vc[h];
                     if (P.recon == 1)
                         pf = fmin(1.0, M / Dk);
                     else
-                        pf = ((M * M + eps2) * Dk + 2.0 * Dk * Dk * M) / (Dk * (M * M + 2.0 * Dk * Dk + M * Dk + eps2));
+                        pf = ((M * M + eps2) * Dk + 2.0 * Dk * Dk * M) /
+                             (Dk * (M * M + 2.0 * Dk * Dk + M * Dk + eps2));
                 }
-                phi = fmin(phi, pf);
+                phi[h] = fmin(phi[h], pf);
             }
-            g[k][0] *= phi;
-            g[k][1] *= phi;
-            g[k][2] *= phi;
         }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) g[h][d] *= phi[h];
     }
-    bool ok = true;
-    for (int lf = 0; lf < nfc; ++lf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        sv[5 * h + kk][0][cl] = vc[h];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) sv[5 * h + kk][1 + d][cl] = g[h][d];
+    }
+    __syncthreads();
+    // the states extrapolated to the faces: one face a wave, the last of six to the first wave
+    for (int lf = kk; lf < nfc && live; lf += 5) {
+        const double dx[3] = {lfx[3 * lf] - xc[0], lfx[3 * lf + 1] - xc[1], lfx[3 * lf + 2] - xc[2]};
         double wf[10];
 #pragma unroll
-        for (int k = 0; k < 10; ++k)
-            wf[k] = vc[k] + g[k][0] * (lfx[3 * lf] - xc[0]) + g[k][1] * (lfx[3 * lf + 1] - xc[1]) +
-                    g[k][2] * (lfx[3 * lf + 2] - xc[2]);
-        if (!(wf[0] > 0.0) || !(temp_k(wf, D.K) > 0.0)) ok = false;
-        if (!(wf[5] >= -1e-12 * wf[0])) ok = false;
+        for (int i = 0; i < 10; ++i)
+            wf[i] = sv[i][0][cl] + sv[i][1][cl] * dx[0] + sv[i][2][cl] * dx[1] + sv[i][3][cl] * dx[2];
+        bool ok = wf[0] > 0.0 && temp_k(wf, D.K) > 0.0 && wf[5] >= -1e-12 * wf[0];
         if (wf[5] > 1e-12 * wf[0] && !(temp_k(wf + 5, D.K) > 0.0)) ok = false;
+        if (!ok) atomicAnd(&sok[cl], 0);
     }
-    // every store after the last load (a load issued after a store waits for it as well)
+    __syncthreads();
+    if (!live) return;
+    const bool ok = sok[cl] != 0;
+    D.Wh[kk * nc + c] = vc[1];
 #pragma unroll
-    for (int k = 0; k < 5; ++k) D.Wh[k * nc + c] = vc[5 + k];
-#pragma unroll
-    for (int k = 0; k < 5; ++k)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            D.gW[(3 * k + d) * nc + c] = ok ? g[k][d] : 0.0;
-            D.gH[(3 * k + d) * nc + c] = ok ? g[5 + k][d] : 0.0;
-        }
+    for (int d = 0; d < 3; ++d) {
+        D.gW[(3 * kk + d) * nc + c] = ok ? g[0][d] : 0.0;
+        D.gH[(3 * kk + d) * nc + c] = ok ? g[1][d] : 0.0;
+    }
 }
 
 // a cell's state (and hydro state) extrapolated to point x, FP64
@@ -1097,20 +1156,106 @@ __device__ __forceinline__ void extrap(const Dev &D, int c, const double x[3], d
     }
 }
 
+// one face at second order: its frame and its two sides' states
 template <typename R>
-__device__ __forceinline__ void make_side(const Dev &D, int c, const double W[5], const double Wh[5], const R n[3],
-                                          const R t1[3], const R t2[3], Side2<R> &S) {
-    S.g = to_frame<R>(W, n, t1, t2, D.K);
-    frame_derivs<R>(D.gW, D.nc, c, n, t1, t2, S.dW);
-    // a face hydro density at or below 1e-12 of the face density is roundoff of an empty hydro
-    // part (the limiter can pin it exactly to a neighbour's zero): no hydro wave on that side
-    if (Wh[0] > 1e-12 * W[0]) {
-        S.h = to_frame<R>(Wh, n, t1, t2, D.K);
-        frame_derivs<R>(D.gH, D.nc, c, n, t1, t2, S.dWh);
-    } else {
-        S.h.rho = (R)0;
-        S.h.K = D.K;
+struct Face2 {
+    int f, c, nb, type;  // type: the boundary condition's (nb < 0)
+    bool pair;           // two sides (an inner face, a mirror, the free stream); else a diffuse wall
+    R n[3], t1[3], t2[3];
+    R dt;
+    bool gks;
+    Side2<R> L, Rs;
+    double Whl0, Wl0;
+};
+template <typename R>
+__device__ __forceinline__ bool open_face(const Dev &D, int f, Face2<R> &F) {
+    const int nf = D.nf;
+    F.f = f;
+    F.c = D.fown[f];
+    const int inst = inst_of(D, F.c);
+    const InstP &P = D.ip[inst];
+    if (P.recon == 0) return false;
+    F.dt = (R)D.is[inst].dt;
+    F.gks = D.is[inst].step < P.gks_steps;
+    F.nb = D.fnb[f];
+    F.type = F.nb >= 0 ? -1 : D.bc[-1 - F.nb].type;
+    F.pair = F.type != 1;
+    F.n[0] = (R)D.fn[f];
+    F.n[1] = (R)D.fn[nf + f];
+    F.n[2] = (R)D.fn[2 * nf + f];
+    face_frame<R>(F.n, F.t1, F.t2);
+    const double xf[3] = {D.fx[f], D.fx[nf + f], D.fx[2 * nf + f]};
+    auto side = [&](int c, Side2<R> &S, double &w0, double &wh0) {
+        double W[5], Wh[5];
+        extrap(D, c, xf, W, Wh);
+        w0 = W[0];
+        wh0 = Wh[0];
+        S.g = to_frame<R>(W, F.n, F.t1, F.t2, D.K);
+        // a face hydro density at or below 1e-12 of the face density is roundoff of an empty hydro
+        // part (the limiter can pin it exactly to a neighbour's zero): no hydro wave on that side
+        if (Wh[0] > 1e-12 * W[0]) {
+            S.h = to_frame<R>(Wh, F.n, F.t1, F.t2, D.K);
+        } else {
+            S.h.rho = (R)0;
+            S.h.K = D.K;
+        }
+    };
+    side(F.c, F.L, F.Wl0, F.Whl0);
+    if (F.nb >= 0) {
+        double a, b;
+        side(F.nb, F.Rs, a, b);
+    } else if (F.type == 0) {
+        F.Rs.g = F.L.g;
+        F.Rs.h = F.L.h;
+        F.Rs.g.un = -F.L.g.un;
+        F.Rs.h.un = -F.L.h.un;
+    } else if (F.type == 2) {
+        F.Rs.g = to_frame<R>(D.bc[-1 - F.nb].Winf, F.n, F.t1, F.t2, D.K);
+        F.Rs.h = F.Rs.g;
     }
+    return true;
+}
+// both sides' derivatives along the frame's axes (specular walls mirror them: along n and the normal
+// momentum flip; the free stream has none)
+template <typename R>
+__device__ __forceinline__ void face_derivs(const Dev &D, Face2<R> &F) {
+    frame_derivs<R>(D.gW, D.nc, F.c, F.n, F.t1, F.t2, F.L.dW);
+    if (F.L.h.rho > (R)0) frame_derivs<R>(D.gH, D.nc, F.c, F.n, F.t1, F.t2, F.L.dWh);
+    if (F.nb >= 0) {
+        frame_derivs<R>(D.gW, D.nc, F.nb, F.n, F.t1, F.t2, F.Rs.dW);
+        if (F.Rs.h.rho > (R)0) frame_derivs<R>(D.gH, D.nc, F.nb, F.n, F.t1, F.t2, F.Rs.dWh);
+        return;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const R sg = ((d == 0) != (k == 1)) ? (R)-1 : (R)1;
+            F.Rs.dW[d][k] = F.type == 0 ? sg * F.L.dW[d][k] : (R)0;
+            F.Rs.dWh[d][k] = F.type == 0 ? sg * F.L.dWh[d][k] : (R)0;
+        }
+}
+// the face's flux, times its area, oriented owner -> neighbour
+template <typename R>
+__device__ __forceinline__ void close_face(const Dev &D, const Face2<R> &F, R Ff[5]) {
+    const int nf = D.nf, f = F.f;
+    if (F.type == 0) {
+        Ff[0] = (R)0;
+        Ff[2] = (R)0;
+        Ff[3] = (R)0;
+        Ff[4] = (R)0;
+    }
+    const R a = (R)D.farea[f];
+    D.Phi[f] = (double)(Ff[0] * a);
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        D.Phi[(1 + d) * nf + f] = (double)((Ff[1] * F.n[d] + Ff[2] * F.t1[d] + Ff[3] * F.t2[d]) * a);
+    D.Phi[4 * nf + f] = (double)(Ff[4] * a);
+}
+template <typename R>
+__device__ __forceinline__ void wall_flux2(const Dev &D, const Face2<R> &F, R Ff[5]) {
+    diffuse_flux<R>(F.L.g, (R)(F.Whl0 > 1e-12 * F.Wl0 ? F.Whl0 : 0.0), (R)D.tau[F.c], F.n, F.t1, F.t2, D.bc[-1 - F.nb],
+                    F.dt, F.gks, Ff);
 }
 
 // S2 at second order: per face, states extrapolated to the face centre from both sides
@@ -1121,67 +1266,124 @@ template <typename R, int BS>
 __global__ void __launch_bounds__(BS) k_flux2(Dev D) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= D.nf) return;
-    const int nf = D.nf;
-    const int c = D.fown[f];
-    const int inst = inst_of(D, c);
-    const InstP &P = D.ip[inst];
-    if (P.recon == 0) return;
-    const R dt = (R)D.is[inst].dt;
-    const R mu = (R)P.mu_ref, om = (R)P.omega, c2 = (R)P.c2;
-    const bool gks = D.is[inst].step < P.gks_steps;
-    const int nb = D.fnb[f];
-    R n[3] = {(R)D.fn[f], (R)D.fn[nf + f], (R)D.fn[2 * nf + f]};
-    R t1[3], t2[3];
-    face_frame<R>(n, t1, t2);
-    const double xf[3] = {D.fx[f], D.fx[nf + f], D.fx[2 * nf + f]};
-    double Wl[5], Whl[5];
-    extrap(D, c, xf, Wl, Whl);
-    Side2<R> L, Rs;
-    make_side<R>(D, c, Wl, Whl, n, t1, t2, L);
-    const R qsh = (R)shakhov_qsh(D, P, f, c, nb);
+    Face2<R> F;
+    if (!open_face<R>(D, f, F)) return;
+    const InstP &P = D.ip[inst_of(D, F.c)];
     R Ff[5];
-    if (nb >= 0) {
-        double Wr[5], Whr[5];
-        extrap(D, nb, xf, Wr, Whr);
-        make_side<R>(D, nb, Wr, Whr, n, t1, t2, Rs);
-        flux2_pair<R>(L, Rs, dt, mu, om, c2, gks, qsh, Ff);
+    if (F.pair) {
+        face_derivs<R>(D, F);
+        const R qsh = F.type == 0 ? (R)0 : (R)shakhov_qsh(D, P, f, F.c, F.nb);
+        flux2_pair<R>(F.L, F.Rs, F.dt, (R)P.mu_ref, (R)P.omega, (R)P.c2, F.gks, qsh, Ff);
     } else {
-        const DevBC bc = D.bc[-1 - nb];
-        if (bc.type == 0) {
-            Rs = L;
-            Rs.g.un = -L.g.un;
-            Rs.h.un = -L.h.un;
+        wall_flux2<R>(D, F, Ff);
+    }
+    close_face<R>(D, F, Ff);
+}
+
+// The same for a mesh of few faces, whose waves do not fill the chip: a face is a chain of some
+// 7,000 dependent operations, so three waves share 64 faces, one per axis of the face frame.  Each
+// forms the states and the sums of its axis and hands them over in local memory; the second also
+// has the time coefficients, the first joins the axes in the order of flux2_pair (the same bits).
+// 9,331 faces of a 301 x 3 x 3 tube: 21 us against 32; the 101,376 of a 32^3 cavity, which fill
+// the chip anyway: 100 us against 52.  The limit is one round of such waves, one to a SIMD.
+constexpr int kFluxSplitMax = 64 * 1024 / 3;
+template <typename R>
+struct AxisPart {
+    R T[5], X[5], Y[2][5];
+};
+template <int A, typename R>
+__device__ __forceinline__ void axis_part(const Dev &D, Face2<R> &F, const Mom3<R> &ML, const Mom3<R> &MR,
+                                          const Prim<R> &z, const Mom3<R> &M0, AxisPart<R> &p) {
+    face_derivs<R>(D, F);
+    R abar[5];
+    face_slope<A, R>(F.L, F.Rs, ML, MR, z, abar);
+    gaxis<A, R>(M0, abar, p.T);
+    guaxis<A, R>(M0, abar, p.X);
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+    for (int s = 0; s < 2; ++s) {
+        const Side2<R> &S = s == 0 ? F.L : F.Rs;
 #pragma unroll
-                for (int k = 0; k < 5; ++k) {
-                    const R sg = ((d == 0) != (k == 1)) ? (R)-1 : (R)1;
-                    Rs.dW[d][k] = sg * L.dW[d][k];
-                    Rs.dWh[d][k] = sg * L.dWh[d][k];
-                }
-            flux2_pair<R>(L, Rs, dt, mu, om, c2, gks, (R)0, Ff);
-            Ff[0] = (R)0;
-            Ff[2] = (R)0;
-            Ff[3] = (R)0;
-            Ff[4] = (R)0;
-        } else if (bc.type == 1) {
-            diffuse_flux<R>(L.g, (R)(Whl[0] > 1e-12 * Wl[0] ? Whl[0] : 0.0), (R)D.tau[c], n, t1, t2, bc, dt, gks,
-                            Ff);
-        } else {
-            Rs.g = to_frame<R>(bc.Winf, n, t1, t2, D.K);
-            Rs.h = Rs.g;
+        for (int k = 0; k < 5; ++k) p.Y[s][k] = (R)0;
+        if (!(S.h.rho > (R)0)) continue;
+        Mom3<R> MH;
+        mom3<R>(s == 0 ? 1 : -1, S.h, MH);
+        hydro_axis<A, R>(MH, S, p.Y[s]);
+    }
+}
+template <typename R>
+__global__ void __launch_bounds__(3 * kWave) k_flux2_axes(Dev D) {
+    __shared__ R part[2][20][kWave];
+    __shared__ R qs[5][kWave];
+    const int axis = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    const int f = blockIdx.x * kWave + lane;
+    Face2<R> F;
+    Prim<R> z;
+    Mom3<R> M0;
+    AxisPart<R> p;
+    const bool live = f < D.nf && open_face<R>(D, f, F);
+    if (live && F.pair) {
+        Mom3<R> ML, MR;
+        mom3<R>(1, F.L.g, ML);
+        mom3<R>(-1, F.Rs.g, MR);
+        face_state<R>(F.L, F.Rs, ML, MR, z);
+        mom3<R>(0, z, M0);
+        if (axis == 0)
+            axis_part<0, R>(D, F, ML, MR, z, M0, p);
+        else if (axis == 1)
+            axis_part<1, R>(D, F, ML, MR, z, M0, p);
+        else
+            axis_part<2, R>(D, F, ML, MR, z, M0, p);
+        if (axis > 0) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+            for (int k = 0; k < 5; ++k) {
+                part[axis - 1][k][lane] = p.T[k];
+                part[axis - 1][5 + k][lane] = p.X[k];
+                part[axis - 1][10 + k][lane] = p.Y[0][k];
+                part[axis - 1][15 + k][lane] = p.Y[1][k];
+            }
+        }
+        if (axis == 1) {
+            const InstP &P = D.ip[inst_of(D, F.c)];
+            R q[5];
+            face_q<R>(F.L, F.Rs, z, F.dt, (R)P.mu_ref, (R)P.omega, (R)P.c2, F.gks, q);
 #pragma unroll
-                for (int k = 0; k < 5; ++k) Rs.dW[d][k] = Rs.dWh[d][k] = (R)0;
-            flux2_pair<R>(L, Rs, dt, mu, om, c2, gks, qsh, Ff);
+            for (int k = 0; k < 5; ++k) qs[k][lane] = q[k];
         }
     }
-    const R a = (R)D.farea[f];
-    D.Phi[f] = (double)(Ff[0] * a);
+    __syncthreads();
+    if (axis != 0 || !live) return;
+    R Ff[5];
+    if (F.pair) {
+        R q[5];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) D.Phi[(1 + d) * nf + f] = (double)((Ff[1] * n[d] + Ff[2] * t1[d] + Ff[3] * t2[d]) * a);
-    D.Phi[4 * nf + f] = (double)(Ff[4] * a);
+        for (int k = 0; k < 5; ++k) q[k] = qs[k][lane];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                p.T[k] = p.T[k] + part[a][k][lane];
+                p.X[k] = p.X[k] + part[a][5 + k][lane];
+                p.Y[0][k] = p.Y[0][k] + part[a][10 + k][lane];
+                p.Y[1][k] = p.Y[1][k] + part[a][15 + k][lane];
+            }
+        face_eq<R>(z, M0, p.T, p.X, q, Ff);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const Side2<R> &S = s == 0 ? F.L : F.Rs;
+            if (!(S.h.rho > (R)0)) continue;
+            Mom3<R> MH;
+            mom3<R>(s == 0 ? 1 : -1, S.h, MH);
+            R Gh[5];
+            uvec<R>(MH, Gh);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) Ff[k] += S.h.rho * (q[3] * Gh[k] + q[4] * p.Y[s][k]);
+        }
+        const R qsh = F.type == 0 ? (R)0 : (R)shakhov_qsh(D, D.ip[inst_of(D, F.c)], f, F.c, F.nb);
+        if (qsh != (R)0) Ff[4] = Ff[4] + q[0] * qsh;
+    } else {
+        wall_flux2<R>(D, F, Ff);
+    }
+    close_face<R>(D, F, Ff);
 }
 
 // particle store access for the two forms
@@ -3519,10 +3721,12 @@ void launch_flux(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
     const int bs = cfg.flux_bs, nf = D.nf;
     const unsigned g = (unsigned)((nf + bs - 1) / bs);
     if (D.recon_any) {
-        // second order: gradients (one thread per cell), then the faces of reconstructing
-        // instances; the first-order kernel takes the others
-        k_grad<<<(unsigned)((D.nc + 127) / 128), 128, 0, s>>>(D);
-        if (bs == 64)
+        // second order: gradients, then the faces of reconstructing instances; the first-order
+        // kernel takes the others
+        k_grad<<<(unsigned)((D.nc + kGradCells - 1) / kGradCells), 5 * kGradCells, 0, s>>>(D);
+        if (nf <= kFluxSplitMax)
+            k_flux2_axes<R><<<(unsigned)((nf + kWave - 1) / kWave), 3 * kWave, 0, s>>>(D);
+        else if (bs == 64)
             k_flux2<R, 64><<<g, 64, 0, s>>>(D);
         else if (bs == 256)
             k_flux2<R, 256><<<g, 256, 0, s>>>(D);

@@ -2,8 +2,8 @@
 
 A mesh of few faces shares each group of faces among three waves, a larger one does not.  A
 batch is one mesh to the kernels, so instances alone (few faces) and in one batch (many) take the
-two paths; without particles, whose numbers a batch gives out in common, they are bitwise
-equal.  Faces of every kind: inner,
+two paths; without particles they are bitwise equal, and the batch with particles is the
+oracle's at the bar of tests/parity.py.  Faces of every kind: inner,
 specular, diffuse, free stream, of boxes and of tetrahedra; both limiters; the Shakhov energy term;
 internal degrees of freedom; a first-order instance among the others.
 """
@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 from paper_2007_13091_amd import workloads as wl
+from test_gpu_batch import _run_batch
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,8 @@ def test_wave_only_steps_alone_and_in_a_batch_are_bitwise_equal(name, precision)
         s.init_state(w.W0)
         s.step(steps)
         np.testing.assert_array_equal(s.moments(0), Wb[first[k]:first[k + 1]])
+
+
+@pytest.mark.parametrize("name", ["boxes", "tets"])
+def test_many_faces_with_particles_match_the_oracle(name):
+    _run_batch(_instances(name), 3, name=f"many-faces {name}")

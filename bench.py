@@ -528,7 +528,7 @@ def averaging_side(steps, warmup):
     """Side number: the cost of time averaging (Sec. 2.4(c)) on the FP64 cavity: the same
     solver timed over `steps` steps without averaging and then over `steps` steps averaging
     every step, and the averaging kernels' position against HBM (k_avg_cells and k_avg_fin are
-    timed with k_finalize in one group; the group's time without averaging is subtracted)."""
+    timed in the group after k_update; the group's time without averaging, empty, is subtracted)."""
     import torch
 
     from paper_2007_13091_amd import workloads as wl

@@ -222,7 +222,11 @@ size_t carve(const HostMesh &H, int n_inst, long long cap, int prec, bool recon,
     D.S = C.take<double>(5 * nc);
     D.nsam = C.take<long long>(nc);
     D.samoff = C.take<long long>(nc + 1);
-    D.scan64 = C.take<long long>((size_t)ugkwp::scan_partials_needed((long long)(nc > nff ? nc : nff)));
+    D.scan64 = C.take<long long>((size_t)ugkwp::count_partials_needed((long long)nc, (long long)nff));
+    // several words an instance, each in a line of its own, unless the instances are many (and small)
+    D.dt_slots = n_inst <= 64 ? ugkwp::kDtSlots : 1;
+    D.dt_stride = n_inst <= 64 ? 16 : 1;
+    D.dtmin = C.take<unsigned long long>((size_t)n_inst * D.dt_slots * D.dt_stride);
     D.lrun = reinterpret_cast<unsigned long long *>(D.nsam);  // (N_sam is not read after the sampling)
     D.off = C.take<unsigned long long>(2 * nc + 1);
     D.scan32 = C.take<unsigned long long>((size_t)ugkwp::scan_partials_needed(2 * (long long)nc));
@@ -623,19 +627,18 @@ int32_t ugkwp_init_state(ugkwp_ctx *ctx, const double *W0) {
     hipStream_t s = ctx->stream;
     Scalars sc;
     std::memset(&sc, 0, sizeof(sc));
-    sc.dtmin_bits = 0x7FF0000000000000ULL;
     HIPCHK(ctx, up(D.W, Wt, s));
     ugkwp::launch_fill_f64(D.P, 5 * (long long)nc, 0.0, s);
     ugkwp::launch_fill_i32(D.v0[0], (long long)nc + 1, 0, s);
     ugkwp::launch_fill_i32(D.v0[1], (long long)nc + 1, 0, s);
     ugkwp::launch_fill_f64(reinterpret_cast<double *>(D.off), 2 * (long long)nc + 1, 0.0, s);
     ugkwp::launch_fill_f64(D.avgA, 5 * (long long)nc, 0.0, s);
+    ugkwp::launch_fill_f64(reinterpret_cast<double *>(D.dtmin), (long long)D.n_inst * D.dt_slots * D.dt_stride, INFINITY, s);
     ugkwp::launch_heat(D, 0, s);  // no particle yet: zero heat fluxes
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipMemcpyAsync(D.sc, &sc, sizeof(sc), hipMemcpyHostToDevice, s));
     std::vector<ugkwp::InstS> is((size_t)D.n_inst);
     std::memset(is.data(), 0, is.size() * sizeof(ugkwp::InstS));
-    for (auto &v : is) v.dtmin_bits = 0x7FF0000000000000ULL;
     HIPCHK(ctx, up(D.is, is, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
     ctx->buf = 0;
@@ -991,7 +994,6 @@ int32_t ugkwp_import_state(ugkwp_ctx *ctx, const double *W, const double *P, int
     // step bookkeeping as after a step: the particles are the old ones of the next step
     Scalars sc;
     std::memset(&sc, 0, sizeof(sc));
-    sc.dtmin_bits = 0x7FF0000000000000ULL;
     sc.n_old = n;
     sc.n_alive = n;
     sc.span[b] = n;
@@ -1002,13 +1004,13 @@ int32_t ugkwp_import_state(ugkwp_ctx *ctx, const double *W, const double *P, int
     std::memset(is.data(), 0, is.size() * sizeof(ugkwp::InstS));
     for (int32_t k = 0; k < D.n_inst; ++k) {
         const ugkwp::InstRange &r = ctx->ranges[k];
-        is[k].dtmin_bits = 0x7FF0000000000000ULL;
         is[k].step = step[k];
         is[k].t = t[k];
         is[k].n_alive = seg[(size_t)r.cell1] - seg[(size_t)r.cell0];
     }
     HIPCHK(ctx, up(D.is, is, s));
     ugkwp::launch_fill_f64(D.avgA, 5 * (long long)nc, 0.0, s);
+    ugkwp::launch_fill_f64(reinterpret_cast<double *>(D.dtmin), (long long)D.n_inst * D.dt_slots * D.dt_stride, INFINITY, s);
     ugkwp::launch_heat(D, b, s);  // the imported particles' heat fluxes (Shakhov model)
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipStreamSynchronize(s));

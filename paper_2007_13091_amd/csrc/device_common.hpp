@@ -56,10 +56,11 @@ struct InstP {
     double pr;             // Prandtl number: 1 the BGK model, otherwise the Shakhov model
 };
 
+constexpr int kDtSlots = 8;  // words for the minimum of Omega / Lambda of an instance of many blocks
+
 // Step state of one instance: its own time step, time and step counter, and the counts of
 // its last step.
 struct InstS {
-    unsigned long long dtmin_bits;  // bit pattern of min Omega/Lambda over its cells
     double dt, t;
     long long step;
     long long n_alive, n_sampled, n_injected, n_collided, n_escaped;
@@ -81,7 +82,6 @@ constexpr int kAvgBlocks = 64;
 // Step scalars of the whole batch, resident in device memory: the host never reads them
 // inside a step.  dt, t and step mirror instance 0.
 struct Scalars {
-    unsigned long long dtmin_bits;  // bit pattern of min Omega/Lambda (positive doubles order as integers)
     double dt;
     double t;
     long long step;
@@ -195,7 +195,11 @@ struct Dev {
     double *S;              // [5][nc] particle sums at the start of the step
     long long *nsam;        // [nc]
     long long *samoff;      // [nc+1]
-    long long *scan64;      // scan partials
+    long long *scan64;      // sums of nsam and ninj over the blocks of k_cell_prep
+    // bit patterns of min Omega / Lambda (positive doubles order as integers): [n_inst][dt_slots],
+    // dt_stride words apart; dt_slots is 1 or kDtSlots
+    unsigned long long *dtmin;
+    int32_t dt_slots, dt_stride;
     long long *ninj;        // [nff] particles entering through each far-field face
     long long *injoff;      // [nff+1]
     unsigned long long *off;   // [2nc+1] prefix of the buckets: high word all their particles, low

@@ -3,8 +3,9 @@
 // Order inside a step (paper Sec. 2.3, the four-step particle procedure, and Eq.
 // update_macro_variables):
 //   k_prim_dt      S0  primitives, tau = mu_ref T^omega / p, min Omega/Lambda     (Sec. 2.4(a))
-//   k_cell_prep    S0  dt, exp(-dt/tau), rho^h, sample counts N_sam            (Sec. 2.4(b))
-//   scan           exclusive prefix of N_sam -> slots of the new particles
+//   k_cell_prep    S0  dt, exp(-dt/tau), rho^h, sample counts N_sam            (Sec. 2.4(b));
+//                  counts of the particles entering through far-field faces
+//   k_offsets      exclusive prefixes of both counts, capacity check
 //   k_grad         S1  least-squares gradients and limiters (second order only)
 //   k_flux(2)      S2  wave flux F^eq + F^{fr,wave} per face                    (Sec. 2.2, 2.4)
 //   k_sample       S3  antithetic Maxwellian pairs, uniform positions; start sums S
@@ -16,8 +17,8 @@
 //   k_track        S5  the listed flights, face to face; bucket sizes
 //   scan           exclusive prefix of the bucket sizes
 //   k_scatter      the leavers by end cell
-//   k_gather       S6  arrivals in a fixed order, sums E and W^p, update of W
-//   k_finalize     step bookkeeping
+//   k_gather       S6  arrivals in a fixed order, sums E and W^p
+//   k_update       S6  update of W; step bookkeeping
 //   k_avg_cells,   time averaging for steady states, when turned on        (Sec. 2.4(c))
 //   k_avg_fin
 // No floating-point atomics: per-cell sums use fixed reduction trees, so a run is bitwise
@@ -47,6 +48,7 @@ __device__ __forceinline__ void st_nt(uint4 *p, const uint4 &v) {
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4_nt *>(p));
 }
 constexpr int kWave = 64;
+constexpr int kCountBS = 256;      // cells (far-field faces) per block of k_cell_prep
 constexpr int kGatherWaves = 1;    // waves per block in k_gather
 constexpr int kSampleCells = 8;     // consecutive cells per wave in k_sample (meshes of 32768 cells or more)
 constexpr int kSampleCellsMin = 32768;
@@ -424,8 +426,23 @@ __device__ __forceinline__ void wave_sum_pc(const double P[5], const double C[5]
 // ---------------------------------------------------------------------------------------
 // S0: primitives, tau, min Omega / Lambda
 // ---------------------------------------------------------------------------------------
+// min Omega / Lambda of an instance, as bits: the blocks' minima go to dt_slots words, each in a
+// memory line of its own: the atomics on a line are served one after the other (349,224
+// tetrahedra, 1,365 blocks on one word: 22 us, now 9.2; 32 cavities of 32^3 cells, 70 us, now 16)
+__device__ __forceinline__ unsigned long long *dt_slot(const Dev &D, int inst, int slot) {
+    return D.dtmin + ((long long)inst * D.dt_slots + slot) * D.dt_stride;
+}
+__device__ __forceinline__ double step_dt(const Dev &D, int inst) {
+    unsigned long long m = *dt_slot(D, inst, 0);
+    if (D.dt_slots == kDtSlots) {
+#pragma unroll
+        for (int k = 1; k < kDtSlots; ++k) m = min(m, *dt_slot(D, inst, k));
+    }
+    return D.ip[inst].cfl * __longlong_as_double((long long)m);
+}
+
 __global__ void __launch_bounds__(256) k_prim_dt(Dev D) {
-    __shared__ double smin[256];
+    __shared__ double smin[256 / kWave];
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         Scalars *s = D.sc;
@@ -468,29 +485,28 @@ __global__ void __launch_bounds__(256) k_prim_dt(Dev D) {
     // reports per cell (positive doubles order as their bit patterns)
     const int cfirst = blockIdx.x * blockDim.x;
     const int clast = min(cfirst + (int)blockDim.x, D.nc) - 1;
+    const int slot = (int)blockIdx.x & (D.dt_slots - 1);
     if (D.n_inst > 1 && D.cinst[cfirst] != D.cinst[clast]) {
-        if (r < INFINITY && r > 0.0) atomicMin(&D.is[inst].dtmin_bits, (unsigned long long)__double_as_longlong(r));
+        if (r < INFINITY && r > 0.0) atomicMin(dt_slot(D, inst, slot), (unsigned long long)__double_as_longlong(r));
         return;
     }
-    smin[threadIdx.x] = r;
+#pragma unroll
+    for (int m = kWave / 2; m > 0; m >>= 1) r = fmin(r, __shfl_xor(r, m));
+    if (lane_id() == 0) smin[threadIdx.x / kWave] = r;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) smin[threadIdx.x] = fmin(smin[threadIdx.x], smin[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && smin[0] < INFINITY && smin[0] > 0.0)
-        atomicMin(&D.is[inst_of(D, cfirst)].dtmin_bits, (unsigned long long)__double_as_longlong(smin[0]));
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 256 / kWave; ++w) r = fmin(r, smin[w]);
+    if (r < INFINITY && r > 0.0)
+        atomicMin(dt_slot(D, inst_of(D, cfirst), slot), (unsigned long long)__double_as_longlong(r));
 }
 
 // ---------------------------------------------------------------------------------------
 // S0 (cont.): dt, collisionless fraction, hydro density, number of particles to sample
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_cell_prep(Dev D) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= D.nc) return;
+__device__ __forceinline__ long long cell_prep(const Dev &D, int c) {
     const int inst = inst_of(D, c);
     const InstP &P = D.ip[inst];
-    const double dt = P.cfl * __longlong_as_double((long long)D.is[inst].dtmin_bits);
+    const double dt = step_dt(D, inst);
     const long long step = D.is[inst].step;
     // every per-cell value loaded before the first store
     const double vol = D.vol[c];
@@ -535,27 +551,7 @@ __global__ void __launch_bounds__(256) k_cell_prep(Dev D) {
         }
     }
     D.nsam[c] = ns;
-}
-
-// capacity check of the step: old + sampled + entering must fit
-__global__ void k_sample_setup(Dev D, int buf) {
-    Scalars *s = D.sc;
-    const long long nn = D.samoff[D.nc];
-    const long long ni = D.nff > 0 ? D.injoff[D.nff] : 0;
-    if (s->n_old + nn + ni > D.cap) {
-        atomicOr(&s->err, kErrCapacity);
-        s->n_new = 0;
-        s->n_inj = 0;
-    } else {
-        s->n_new = nn;
-        s->n_inj = ni;
-    }
-    s->none = s->n_old + s->n_new + s->n_inj == 0 ? 1u : 0u;
-    s->n_sampled = (unsigned long long)s->n_new;
-    s->n_injected = (unsigned long long)s->n_inj;
-    // the next buffer's regions: a cell's is as long as its old and new particles are many
-    s->span[buf ^ 1] = s->n_old + s->n_new;
-    D.v0[buf ^ 1][D.nc] = (int32_t)(s->n_old + s->n_new);
+    return ns;
 }
 
 // Diffuse isothermal wall (Sec. 2.4(e)), first order at the state l (n out of the domain):
@@ -2141,13 +2137,12 @@ struct Inflow {
     double nin[3], t1[3], t2[3];
 };
 
-__device__ Inflow inflow_face(const Dev &D, int j) {
+__device__ Inflow inflow_face(const Dev &D, int j, double dt) {
     Inflow q;
     const int4 fi = D.ffi[j];
     q.c = fi.x;
     q.inst = inst_of(D, q.c);
     const InstP &P = D.ip[q.inst];
-    const double dt = D.is[q.inst].dt;
     q.dt = dt;
     q.lf = fi.y & 0xFF;
     q.tri = fi.y >> 8;
@@ -2183,16 +2178,38 @@ __device__ Inflow inflow_face(const Dev &D, int j) {
     return q;
 }
 
-__global__ void __launch_bounds__(256) k_inject_count(Dev D) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= D.nff) return;
-    const Inflow q = inflow_face(D, j);
+__device__ __forceinline__ long long inject_count(const Dev &D, int j) {
+    const Inflow q = inflow_face(D, j, step_dt(D, inst_of(D, D.ffi[j].x)));
     long long n = q.N;
     if (n < 0) {
         atomicOr(&D.sc->err, kErrCellCount);
         n = 0;
     }
     D.ninj[j] = n;
+    return n;
+}
+
+// The counts of new particles: per cell (its first blocks) and per far-field face (the others),
+// with each block's sum for k_offsets, so that no kernel reads the counts only to sum them: a step
+// takes two launches to its offsets instead of four (seven with inflow), 7.2 us on 2,709 cells
+// against 9.8, 22 against 46 on 349,224 tetrahedra with a far field.
+__global__ void __launch_bounds__(kCountBS) k_cell_prep(Dev D) {
+    __shared__ long long ws[kCountBS / kWave];
+    const int gc = (D.nc + kCountBS - 1) / kCountBS;
+    long long n = 0;
+    if ((int)blockIdx.x < gc) {
+        const int c = blockIdx.x * kCountBS + threadIdx.x;
+        if (c < D.nc) n = cell_prep(D, c);
+    } else {
+        const int j = ((int)blockIdx.x - gc) * kCountBS + threadIdx.x;
+        if (j < D.nff) n = inject_count(D, j);
+    }
+    n = (long long)wave_sum_u64((unsigned long long)n);
+    if (lane_id() == 0) ws[threadIdx.x / kWave] = n;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kCountBS / kWave; ++w) n += ws[w];
+    D.scan64[blockIdx.x] = n;
 }
 
 // one thread per entering particle, whose face it finds among the prefix sums (a face lets a few
@@ -2215,7 +2232,7 @@ __global__ void __launch_bounds__(256) k_inject(Dev D, int buf) {
                 end = mid;
         }
         const long long k = p - D.injoff[j];
-        const Inflow q = inflow_face(D, j);
+        const Inflow q = inflow_face(D, j, D.is[inst_of(D, D.ffi[j].x)].dt);
         const long long step = D.is[q.inst].step;
         const unsigned long long seed = D.ip[q.inst].seed;
         const double *g = D.ffg + 10 * j;
@@ -3308,47 +3325,8 @@ __global__ void __launch_bounds__(256) k_pack(Dev D, int buf) {
     }
 }
 
-// S6: W^{n+1} = W^n + (-sum_f s_f Phi_f + E - S) / Omega, one thread per cell; E - S is P^{n+1}
-// minus what k_stream and the gather left of S.  In a step with no particle anywhere (none is
-// left, sampled or let in) no kernel between the preparation and this one does anything: then
-// P^{n+1} = 0 and S = P^n.
-__global__ void __launch_bounds__(256) k_update(Dev D) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= D.nc) return;
-    const bool none = D.sc->none != 0;
-    const int nc = D.nc, nf = D.nf, nfc = D.nfc[c];
-    int codes[6];
-#pragma unroll
-    for (int lf = 0; lf < 6; ++lf) codes[lf] = lf < nfc ? D.cface[c * 6 + lf] : 0;
-    const double vol = D.vol[c];
-    // every load before the first store (the stores could alias them as far as the compiler
-    // knows, which would otherwise keep one round trip per component)
-    double ph[5][6], pv[5], sv[5], wv[5];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-#pragma unroll
-        for (int lf = 0; lf < 6; ++lf) {
-            const int cd = codes[lf];
-            const int f = (cd > 0 ? cd : -cd) - 1;
-            ph[k][lf] = lf < nfc ? D.Phi[k * nf + f] : 0.0;
-        }
-        pv[k] = D.P[k * nc + c];
-        sv[k] = D.S[k * nc + c];
-        wv[k] = D.W[k * nc + c];
-    }
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        double facc = 0.0;
-#pragma unroll
-        for (int lf = 0; lf < 6; ++lf)  // (unrolled: arrays indexed at run time would live in scratch memory)
-            if (lf < nfc) facc = facc - (codes[lf] > 0 ? ph[k][lf] : -ph[k][lf]);
-        const double acc = facc + (none ? 0.0 - pv[k] : pv[k] - sv[k]);
-        D.W[k * nc + c] = wv[k] + acc / vol;
-        if (none) D.P[k * nc + c] = 0.0;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_finalize(Dev D) {
+// the step's bookkeeping, one block
+__device__ __forceinline__ void finalize(const Dev &D) {
     __shared__ unsigned long long red[2][kWallSeg];
     Scalars *s = D.sc;
     const long long n_old = s->n_old, n_new = s->n_new, n_inj = s->n_inj;
@@ -3386,7 +3364,7 @@ __global__ void __launch_bounds__(256) k_finalize(Dev D) {
         I.moved_total = I.moved_total + tot;
         I.t = I.t + I.dt;
         I.step = I.step + 1;
-        I.dtmin_bits = 0x7FF0000000000000ULL;
+        for (int i = 0; i < D.dt_slots; ++i) *dt_slot(D, k, i) = 0x7FF0000000000000ULL;
     }
     if (threadIdx.x == 0) {
         const long long alive = hi32(D.off[nc]);
@@ -3406,80 +3384,198 @@ __global__ void __launch_bounds__(256) k_finalize(Dev D) {
     }
 }
 
+// S6: W^{n+1} = W^n + (-sum_f s_f Phi_f + E - S) / Omega, one thread per cell; E - S is P^{n+1}
+// minus what k_stream and the gather left of S.  In a step with no particle anywhere (none is
+// left, sampled or let in) no kernel between the preparation and this one does anything: then
+// P^{n+1} = 0 and S = P^n.
+// The last block keeps the step's books meanwhile: nothing that it writes is read by the others.
+__global__ void __launch_bounds__(256) k_update(Dev D) {
+    if (blockIdx.x == gridDim.x - 1) {
+        finalize(D);
+        return;
+    }
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= D.nc) return;
+    const bool none = D.sc->none != 0;
+    const int nc = D.nc, nf = D.nf, nfc = D.nfc[c];
+    int codes[6];
+#pragma unroll
+    for (int lf = 0; lf < 6; ++lf) codes[lf] = lf < nfc ? D.cface[c * 6 + lf] : 0;
+    const double vol = D.vol[c];
+    // every load before the first store (the stores could alias them as far as the compiler
+    // knows, which would otherwise keep one round trip per component)
+    double ph[5][6], pv[5], sv[5], wv[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+#pragma unroll
+        for (int lf = 0; lf < 6; ++lf) {
+            const int cd = codes[lf];
+            const int f = (cd > 0 ? cd : -cd) - 1;
+            ph[k][lf] = lf < nfc ? D.Phi[k * nf + f] : 0.0;
+        }
+        pv[k] = D.P[k * nc + c];
+        sv[k] = D.S[k * nc + c];
+        wv[k] = D.W[k * nc + c];
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        double facc = 0.0;
+#pragma unroll
+        for (int lf = 0; lf < 6; ++lf)  // (unrolled: arrays indexed at run time would live in scratch memory)
+            if (lf < nfc) facc = facc - (codes[lf] > 0 ? ph[k][lf] : -ph[k][lf]);
+        const double acc = facc + (none ? 0.0 - pv[k] : pv[k] - sv[k]);
+        D.W[k * nc + c] = wv[k] + acc / vol;
+        if (none) D.P[k * nc + c] = 0.0;
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // exclusive scan (integers, deterministic): out[i] = sum_{j<i} in[j], out[n] = total
 // ---------------------------------------------------------------------------------------
 constexpr int kScanBS = 256, kScanPer = 8, kScanTile = kScanBS * kScanPer;
+static_assert(kScanTile % kCountBS == 0);
 
-// scan inputs: a plain array, or the bucket sizes (all particles of the bucket in the high word,
-// those listed in perm in the low one; neither total reaches 2^31)
-template <typename T>
-struct LoadPlain {
-    const T *p;
-    __device__ T operator()(long long i) const { return p[i]; }
-};
-struct LoadBucket {
-    const unsigned long long *p;
-    __device__ unsigned long long operator()(long long i) const {
-        const unsigned long long v = p[i];
-        return v + (v << 32);
-    }
-};
-
-template <typename T>
+// exclusive prefix over the block's threads
+template <typename T, int BS>
 __device__ T block_exclusive_scan(T v, T *sh, T &total) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 1; s < kScanBS; s <<= 1) {
-        T t = (int)threadIdx.x >= s ? sh[threadIdx.x - s] : T(0);
-        __syncthreads();
-        sh[threadIdx.x] = sh[threadIdx.x] + t;
-        __syncthreads();
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    T incl = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const T t = __shfl_up(incl, d);
+        if (lane >= d) incl = incl + t;
     }
-    T incl = sh[threadIdx.x];
-    total = sh[kScanBS - 1];
+    __syncthreads();  // (sh may still be read from the call before)
+    if (lane == kWave - 1) sh[wave] = incl;
     __syncthreads();
-    return incl - v;
+    T before = T(0);
+    total = T(0);
+#pragma unroll
+    for (int w = 0; w < BS / kWave; ++w) {
+        const T t = sh[w];
+        if (w < wave) before = before + t;
+        total = total + t;
+    }
+    return before + incl - v;
+}
+template <typename T, int BS>
+__device__ T block_total(T v, T *sh) {
+    T total;
+    block_exclusive_scan<T, BS>(v, sh, total);
+    return total;
 }
 
-template <typename T, typename L>
-__global__ void k_scan_reduce(L in, long long n, T *part) {
-    __shared__ T sh[kScanBS];
-    const long long base = (long long)blockIdx.x * kScanTile;
-    T s = 0;
-    for (int q = 0; q < kScanPer; ++q) {
-        long long i = base + (long long)threadIdx.x * kScanPer + q;
-        if (i < n) s = s + in(i);
+// The counts' prefixes, a tile per block: an offset is the sum of k_cell_prep's block sums before
+// the tile (a few thousand at most, from the L2).  The last block checks the capacity of the step
+// (old + sampled + entering must fit) and sets its counts.
+__global__ void __launch_bounds__(kScanBS) k_offsets(Dev D, int buf) {
+    __shared__ long long sh[kScanBS / kWave];
+    const int tc = (D.nc + kScanTile - 1) / kScanTile, ti = (D.nff + kScanTile - 1) / kScanTile;
+    const int gc = (D.nc + kCountBS - 1) / kCountBS, gi = (D.nff + kCountBS - 1) / kCountBS;
+    const int tile = blockIdx.x;
+    auto sum_of = [&](const long long *part, int n) {
+        long long o = 0;
+        for (int b = threadIdx.x; b < n; b += kScanBS) o += part[b];
+        return block_total<long long, kScanBS>(o, sh);
+    };
+    if (tile == tc + ti) {
+        const long long nn = sum_of(D.scan64, gc), ni = sum_of(D.scan64 + gc, gi);
+        if (threadIdx.x != 0) return;
+        Scalars *s = D.sc;
+        const bool fits = s->n_old + nn + ni <= D.cap;
+        if (!fits) atomicOr(&s->err, kErrCapacity);
+        s->n_new = fits ? nn : 0;
+        s->n_inj = fits ? ni : 0;
+        s->none = s->n_old + s->n_new + s->n_inj == 0 ? 1u : 0u;
+        s->n_sampled = (unsigned long long)s->n_new;
+        s->n_injected = (unsigned long long)s->n_inj;
+        // the next buffer's regions: a cell's is as long as its old and new particles are many
+        s->span[buf ^ 1] = s->n_old + s->n_new;
+        D.v0[buf ^ 1][D.nc] = (int32_t)(s->n_old + s->n_new);
+        return;
     }
-    T tot;
-    block_exclusive_scan<T>(s, sh, tot);
+    const bool cells = tile < tc;
+    const int t = cells ? tile : tile - tc;
+    const long long *in = cells ? D.nsam : D.ninj, *part = cells ? D.scan64 : D.scan64 + gc;
+    long long *out = cells ? D.samoff : D.injoff;
+    const long long n = cells ? D.nc : D.nff;
+    const long long base = (long long)t * kScanTile + (long long)threadIdx.x * kScanPer;
+    long long v[kScanPer], s = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) v[q] = base + q < n ? in[base + q] : 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) s += v[q];
+    const long long off = sum_of(part, t * (kScanTile / kCountBS));
+    long long tot;
+    long long ex = block_exclusive_scan<long long, kScanBS>(s, sh, tot) + off;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        if (base + q < n) out[base + q] = ex;
+        ex += v[q];
+    }
+    if (t == (cells ? tc : ti) - 1 && threadIdx.x == 0) out[n] = off + tot;
+}
+
+// The prefix of the bucket sizes (all particles of the bucket in the high word, those listed in
+// perm in the low one; neither total reaches 2^31).  Up to 8,192 buckets: one launch of one block
+// of 1,024 threads (5,418 buckets: 4.0 us against 7.6 in two launches).  More: the tiles' totals
+// first (65,536 buckets: 8.9 us; eight such blocks, each summing all that is before its own tile,
+// took 15.5).
+__device__ __forceinline__ unsigned long long bucket(unsigned long long v) { return v + (v << 32); }
+
+constexpr int kSmallBS = 1024, kSmallPer = 8;
+constexpr long long kScanSmall = kSmallBS * kSmallPer;
+
+__global__ void __launch_bounds__(kSmallBS) k_scan_small(const unsigned long long *in, long long n,
+                                                         unsigned long long *out) {
+    __shared__ unsigned long long sh[kSmallBS / kWave];
+    const long long first = (long long)threadIdx.x * kSmallPer;
+    unsigned long long v[kSmallPer], s = 0;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) v[q] = first + q < n ? bucket(in[first + q]) : 0;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) s += v[q];
+    unsigned long long tot;
+    unsigned long long ex = block_exclusive_scan<unsigned long long, kSmallBS>(s, sh, tot);
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q) {
+        if (first + q < n) out[first + q] = ex;
+        ex += v[q];
+    }
+    if (threadIdx.x == 0) out[n] = tot;
+}
+
+__global__ void __launch_bounds__(kScanBS) k_scan_reduce(const unsigned long long *in, long long n,
+                                                         unsigned long long *part) {
+    __shared__ unsigned long long sh[kScanBS / kWave];
+    const long long base = (long long)blockIdx.x * kScanTile + threadIdx.x;
+    unsigned long long s = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) s += base + q * kScanBS < n ? bucket(in[base + q * kScanBS]) : 0;
+    const unsigned long long tot = block_total<unsigned long long, kScanBS>(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
 // Each block finds its own offset, the totals of the blocks before it (a few thousand at
 // most, read from the L2), so no kernel in between scans the block totals; the last block
 // writes the grand total to out[n].  Integer sums: the order does not matter.
-template <typename T, typename L>
-__global__ void k_scan_apply(L in, long long n, const T *part, T *out) {
-    __shared__ T sh[kScanBS];
-    T o = 0;
-    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kScanBS) o = o + part[b];
-    T off;
-    block_exclusive_scan<T>(o, sh, off);
+__global__ void __launch_bounds__(kScanBS) k_scan_apply(const unsigned long long *in, long long n,
+                                                        const unsigned long long *part, unsigned long long *out) {
+    __shared__ unsigned long long sh[kScanBS / kWave];
     const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanPer;
-    T v[kScanPer];
-    T s = 0;
+    unsigned long long v[kScanPer], s = 0, o = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) v[q] = base + q < n ? bucket(in[base + q]) : 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kScanBS) o += part[b];
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) s += v[q];
+    const unsigned long long off = block_total<unsigned long long, kScanBS>(o, sh);
+    unsigned long long tot;
+    unsigned long long ex = block_exclusive_scan<unsigned long long, kScanBS>(s, sh, tot) + off;
+#pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
-        long long i = base + q;
-        v[q] = i < n ? in(i) : T(0);
-        s = s + v[q];
-    }
-    T tot;
-    T ex = block_exclusive_scan<T>(s, sh, tot) + off;
-    for (int q = 0; q < kScanPer; ++q) {
-        long long i = base + q;
-        if (i < n) out[i] = ex;
-        ex = ex + v[q];
+        if (base + q < n) out[base + q] = ex;
+        ex += v[q];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + tot;
 }
@@ -3497,7 +3593,7 @@ __global__ void k_fill(T *p, long long n, T v) {
 // (+infinity until two steps are averaged).  k_avg_cells: kAvgBlocks blocks per instance,
 // each a contiguous run of its cells, fixed per-thread assignment and reduction tree;
 // k_avg_fin: one wave per instance sums its blocks' partials and advances D.  Both run after
-// k_finalize (the instance's step counter and dt are those of the step just taken).
+// k_update (the instance's step counter and dt are those of the step just taken).
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_avg_cells(Dev D) {
     __shared__ double red[2][256];
@@ -3595,21 +3691,35 @@ __global__ void k_moments(Dev D, int which, double *out) {
     for (int k = 0; k < 5; ++k) out[5 * c + k] = o[k];
 }
 
-// exclusive scan of n entries of in into out[0..n]; part: scan_partials_needed(n) entries
-template <typename T, typename L>
-void scan(L in, long long n, T *out, T *part, hipStream_t s) {
-    const int nb = (int)((n + kScanTile - 1) / kScanTile);
-    if (nb == 0) {
-        k_fill<T><<<1, 1, 0, s>>>(out, 1, T(0));
+// prefix of the bucket sizes into D.off
+void scan_buckets(const Dev &D, hipStream_t s) {
+    const long long n = 2LL * D.nc;
+    if (n <= kScanSmall) {
+        k_scan_small<<<1, kSmallBS, 0, s>>>(D.cnt64, n, D.off);
         return;
     }
-    k_scan_reduce<T, L><<<nb, kScanBS, 0, s>>>(in, n, part);
-    k_scan_apply<T, L><<<nb, kScanBS, 0, s>>>(in, n, part, out);
+    const unsigned nb = (unsigned)((n + kScanTile - 1) / kScanTile);
+    k_scan_reduce<<<nb, kScanBS, 0, s>>>(D.cnt64, n, D.scan32);
+    k_scan_apply<<<nb, kScanBS, 0, s>>>(D.cnt64, n, D.scan32, D.off);
+}
+// counts of the new particles and their offsets
+void count_new(const Dev &D, int buf, hipStream_t s, Prof *pr) {
+    const int gc = (D.nc + kCountBS - 1) / kCountBS, gi = (D.nff + kCountBS - 1) / kCountBS;
+    pr->begin(kSlotCellPrep);
+    k_cell_prep<<<(unsigned)(gc + gi), kCountBS, 0, s>>>(D);
+    pr->end(kSlotCellPrep);
+    pr->begin(kSlotScan);
+    const int tc = (D.nc + kScanTile - 1) / kScanTile, ti = (D.nff + kScanTile - 1) / kScanTile;
+    k_offsets<<<(unsigned)(tc + ti + 1), kScanBS, 0, s>>>(D, buf);
+    pr->end(kSlotScan);
 }
 
 }  // namespace
 
 long long scan_partials_needed(long long n) { return (n + kScanTile - 1) / kScanTile + 1; }
+long long count_partials_needed(long long nc, long long nff) {
+    return (nc + kCountBS - 1) / kCountBS + (nff + kCountBS - 1) / kCountBS;
+}
 
 
 void launch_fill_i32(int32_t *p, long long n, int32_t v, hipStream_t s) {
@@ -3779,17 +3889,7 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
     pr->begin(kSlotPrim);
     k_prim_dt<<<gc, 256, 0, s>>>(D);
     pr->end(kSlotPrim);
-    pr->begin(kSlotCellPrep);
-    k_cell_prep<<<gc, 256, 0, s>>>(D);
-    pr->end(kSlotCellPrep);
-    pr->begin(kSlotScan);
-    scan<long long>(LoadPlain<long long>{D.nsam}, nc, D.samoff, D.scan64, s);
-    if (D.nff > 0) {
-        k_inject_count<<<(unsigned)((D.nff + 255) / 256), 256, 0, s>>>(D);
-        scan<long long>(LoadPlain<long long>{D.ninj}, D.nff, D.injoff, D.scan64, s);
-    }
-    k_sample_setup<<<1, 1, 0, s>>>(D, buf);
-    pr->end(kSlotScan);
+    count_new(D, buf, s, pr);
     const bool f32 = D.prec == 1;
     pr->begin(kSlotFlux);
     if (nf > 0) {
@@ -3818,7 +3918,7 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
         launch_stream<double>(D, buf, cfg, s);
     pr->end(kSlotStream);
     pr->begin(kSlotScan2);
-    scan<unsigned long long>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
+    scan_buckets(D, s);
     pr->end(kSlotScan2);
     pr->begin(kSlotScatter);
     launch_scatter(D, s);
@@ -3844,11 +3944,10 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
         else
             k_gather<double, WPB, false><<<g, WPB * 64, 0, s>>>(D, buf);
     }
-    k_update<<<gc, 256, 0, s>>>(D);
+    k_update<<<gc + 1, 256, 0, s>>>(D);
     launch_heat(D, buf ^ 1, s);
     pr->end(kSlotGather);
     pr->begin(kSlotFinal);
-    k_finalize<<<1, 256, 0, s>>>(D);
     if (D.avg_from >= 0) {
         k_avg_cells<<<(unsigned)(D.n_inst * kAvgBlocks), 256, 0, s>>>(D);
         k_avg_fin<<<(unsigned)D.n_inst, 64, 0, s>>>(D);
@@ -3867,17 +3966,7 @@ void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStrea
     pr->begin(kSlotPrim);
     k_prim_dt<<<gc, 256, 0, s>>>(D);
     pr->end(kSlotPrim);
-    pr->begin(kSlotCellPrep);
-    k_cell_prep<<<gc, 256, 0, s>>>(D);
-    pr->end(kSlotCellPrep);
-    pr->begin(kSlotScan);
-    scan<long long>(LoadPlain<long long>{D.nsam}, nc, D.samoff, D.scan64, s);
-    if (D.nff > 0) {
-        k_inject_count<<<(unsigned)((D.nff + 255) / 256), 256, 0, s>>>(D);
-        scan<long long>(LoadPlain<long long>{D.ninj}, D.nff, D.injoff, D.scan64, s);
-    }
-    k_sample_setup<<<1, 1, 0, s>>>(D, buf);
-    pr->end(kSlotScan);
+    count_new(D, buf, s, pr);
     pr->begin(kSlotFlux);
     if (nf > 0) {
         if (D.prec == 1)
@@ -3887,13 +3976,12 @@ void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStrea
     }
     pr->end(kSlotFlux);
     pr->begin(kSlotScan2);
-    scan<unsigned long long>(LoadBucket{D.cnt64}, 2LL * nc, D.off, D.scan32, s);
+    scan_buckets(D, s);
     pr->end(kSlotScan2);
     pr->begin(kSlotGather);
-    k_update<<<gc, 256, 0, s>>>(D);
+    k_update<<<gc + 1, 256, 0, s>>>(D);
     pr->end(kSlotGather);
     pr->begin(kSlotFinal);
-    k_finalize<<<1, 256, 0, s>>>(D);
     if (D.avg_from >= 0) {
         k_avg_cells<<<(unsigned)(D.n_inst * kAvgBlocks), 256, 0, s>>>(D);
         k_avg_fin<<<(unsigned)D.n_inst, 64, 0, s>>>(D);

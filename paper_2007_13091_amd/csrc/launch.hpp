@@ -8,12 +8,13 @@ namespace ugkwp {
 
 // scan partial slots needed for an exclusive scan over n integers
 long long scan_partials_needed(long long n);
+long long count_partials_needed(long long nc, long long nff);
 
 // measurement hook: called around each group of launches of a step (no-op by default)
 enum ProfSlot : int {
     kSlotPrim = 0,      // k_prim_dt
-    kSlotCellPrep,      // k_cell_prep
-    kSlotScan,          // scan of N_sam, capacity check, clearing of the bucket counters
+    kSlotCellPrep,      // k_cell_prep (with the counts of entering particles)
+    kSlotScan,          // k_offsets
     kSlotFlux,          // k_flux
     kSlotSample,        // k_sample
     kSlotStream,        // k_stream, k_stream_in, k_track
@@ -21,8 +22,8 @@ enum ProfSlot : int {
     kSlotCount,         // (no kernels: k_track counts)
     kSlotScan2,         // scan of the bucket counts
     kSlotScatter,       // k_scatter
-    kSlotGather,        // k_gather
-    kSlotFinal,         // k_finalize (and the averaging kernels when averaging is on)
+    kSlotGather,        // k_gather, k_update
+    kSlotFinal,         // (the averaging kernels when averaging is on)
     kNumSlots
 };
 struct Prof {

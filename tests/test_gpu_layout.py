@@ -12,6 +12,7 @@ import pytest
 import oracle
 from paper_2007_13091_amd import workloads as wl
 from parity import compare_fields, compare_particles, compare_stats
+from test_gpu_batch import _run_batch
 from test_gpu_parity import run_pair
 
 pytestmark = pytest.mark.gpu
@@ -92,8 +93,20 @@ def test_buckets_of_every_length(name):
         run_pair(wl.closed_box(n=(14, 14, 14), n_ref=14, kn=0.2, tets=True, jitter=0.1, perturb=0.1), 2, name=name, sampling=1)
 
 
-@pytest.mark.parametrize("U", [0.0, 0.99, 1.01, 4.0])
+@pytest.mark.parametrize("U", [0.0, 0.99, 1.01, 2.99, 3.01, 4.0])
 def test_inflow_speeds_on_both_sides_of_the_root_finders_rule(U):
-    """Faces with a = U.n / sigma in [-U, U]: the iteration above -1, the bisections below."""
+    """Faces with a = U.n / sigma in [-U, U]: the iteration above -3, the plain bisections below."""
     run_pair(wl.free_stream_box(n=(3, 2, 2), U=(U, 0.0, 0.0), n_ref=20, kn=0.5, perturb=0.1), 2, vscale=3.0 + U,
              name=f"inflow U={U}")
+
+
+@pytest.mark.parametrize("name", ["4096-cells", "4100-cells", "486-far-field-faces", "65-instances"])
+def test_prefixes_on_both_sides_of_their_tiles(name):
+    """8,192 buckets and a few more (one launch, two); more far-field faces than a block counts;
+    more instances than have several words for their time step each."""
+    if name == "65-instances":
+        _run_batch(wl.small_batch(65), 2, name=name)
+    elif name == "486-far-field-faces":
+        run_pair(wl.free_stream_box(n=(9, 9, 9), U=(0.6, 0.2, 0.0), n_ref=12, kn=0.5, perturb=0.1), 2, name=name)
+    else:
+        run_pair(wl.sod(nx=int(name[:4]) // 4, ny=2, nz=2, n_ref=12, kn=1e-3), 2, name=name, sampling=1)

@@ -3580,8 +3580,7 @@ __global__ void __launch_bounds__(kScanBS) k_scan_apply(const unsigned long long
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + tot;
 }
 
-template <typename T>
-__global__ void k_fill(T *p, long long n, T v) {
+__global__ void k_fill(double *p, long long n, double v) {
     long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
@@ -3691,6 +3690,61 @@ __global__ void k_moments(Dev D, int which, double *out) {
     for (int k = 0; k < 5; ++k) out[5 * c + k] = o[k];
 }
 
+// A new state from W0 [nc][5] (already in device memory): its check, each block's first bad cell to
+// `bad` (LLONG_MAX: none), and if no block found one, every array that a run starts from.  With a
+// bad cell nothing is written and the state before stays.
+__global__ void __launch_bounds__(kCountBS) k_check_state(Dev D, const double *W0, long long *bad) {
+    __shared__ int first;
+    if (threadIdx.x == 0) first = kCountBS;
+    __syncthreads();
+    const int c = blockIdx.x * kCountBS + threadIdx.x;
+    if (c < D.nc) {
+        const double *w = W0 + 5LL * c;
+        const double rho = w[0];
+        const double T = (2.0 / (3.0 + D.K)) * (w[4] - 0.5 * (w[1] * w[1] + w[2] * w[2] + w[3] * w[3]) / rho) / rho;
+        if (!(rho > 0.0) || !(T > 0.0) || !isfinite(rho) || !isfinite(T)) atomicMin(&first, (int)threadIdx.x);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        bad[blockIdx.x] = first < kCountBS ? (long long)blockIdx.x * kCountBS + first : 0x7FFFFFFFFFFFFFFFLL;
+}
+__global__ void __launch_bounds__(kCountBS) k_take_state(Dev D, const double *W0, const long long *bad, long long *worst) {
+    __shared__ long long sm[kCountBS / kWave];
+    const int gc = (D.nc + kCountBS - 1) / kCountBS;
+    long long m = 0x7FFFFFFFFFFFFFFFLL;
+    for (int b = threadIdx.x; b < gc; b += kCountBS) m = min(m, bad[b]);
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) m = min(m, __shfl_xor(m, d));
+    if (lane_id() == 0) sm[threadIdx.x / kWave] = m;
+    __syncthreads();
+    for (int w = 0; w < kCountBS / kWave; ++w) m = min(m, sm[w]);
+    const long long i = (long long)blockIdx.x * kCountBS + threadIdx.x;
+    if (i == 0) *worst = m;
+    if (m != 0x7FFFFFFFFFFFFFFFLL) return;
+    const long long nc = D.nc, all = (long long)gridDim.x * kCountBS;
+    if (i < nc) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            D.W[k * nc + i] = W0[5 * i + k];
+            D.P[k * nc + i] = 0.0;
+            D.avgA[k * nc + i] = 0.0;
+        }
+        D.v0[0][i] = 0;
+        D.v0[1][i] = 0;
+        D.off[i] = 0ULL;
+        D.off[nc + i] = 0ULL;
+    }
+    if (i == 0) {
+        D.v0[0][nc] = 0;
+        D.v0[1][nc] = 0;
+        D.off[2 * nc] = 0ULL;
+    }
+    for (long long k = i; k < (long long)D.n_inst * D.dt_slots * D.dt_stride; k += all) D.dtmin[k] = 0x7FF0000000000000ULL;
+    uint32_t *const is = reinterpret_cast<uint32_t *>(D.is), *const sc = reinterpret_cast<uint32_t *>(D.sc);
+    for (long long k = i; k < (long long)(D.n_inst * (sizeof(InstS) / 4)); k += all) is[k] = 0u;
+    for (long long k = i; k < (long long)(sizeof(Scalars) / 4); k += all) sc[k] = 0u;
+}
+
 // prefix of the bucket sizes into D.off
 void scan_buckets(const Dev &D, hipStream_t s) {
     const long long n = 2LL * D.nc;
@@ -3722,11 +3776,14 @@ long long count_partials_needed(long long nc, long long nff) {
 }
 
 
-void launch_fill_i32(int32_t *p, long long n, int32_t v, hipStream_t s) {
-    if (n > 0) k_fill<int32_t><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n, v);
+void launch_take_state(const Dev &D, const double *W0, long long *worst, hipStream_t s) {
+    const unsigned g = (unsigned)((D.nc + kCountBS - 1) / kCountBS);
+    k_check_state<<<g, kCountBS, 0, s>>>(D, W0, D.scan64);
+    k_take_state<<<g, kCountBS, 0, s>>>(D, W0, D.scan64, worst);
 }
+
 void launch_fill_f64(double *p, long long n, double v, hipStream_t s) {
-    if (n > 0) k_fill<double><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n, v);
+    if (n > 0) k_fill<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n, v);
 }
 
 namespace {

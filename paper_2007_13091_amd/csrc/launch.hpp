@@ -41,8 +41,10 @@ struct LaunchCfg {
 };
 bool launch_cfg_valid(const LaunchCfg &c);
 
-void launch_fill_i32(int32_t *p, long long n, int32_t v, hipStream_t s);
 void launch_fill_f64(double *p, long long n, double v, hipStream_t s);
+// a new state from W0 [nc][5] in device memory; *worst: its first non-physical cell, which leaves the
+// state before as it is, or LLONG_MAX
+void launch_take_state(const Dev &D, const double *W0, long long *worst, hipStream_t s);
 // one full time step on stream s; particles are read from pa[buf] and left in pa[buf ^ 1]
 void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Prof *pr);
 // a wave-only step when no particle exists anywhere (the same results as launch_step)

@@ -2079,20 +2079,22 @@ __device__ __forceinline__ double ncdf(double t) { return 0.5 * erfc(-t / sqrt(2
 // z = v_n / sigma has density g(z) = z phi(z - a) / Z(a) on z > 0, Z(a) = phi(a) + a Phi(a), and
 // distribution G(z) = (phi(a) - phi(z - a) + a (Phi(z - a) - Phi(-a))) / Z(a); the root of
 // G(z) = eta is the result of 60 bisections of [0, max(a, 0) + 40].  Where g is small the
-// rounding of G decides their last steps, so that another way to the root ends up to 1e-8 from
+// rounding of G decides their last steps, so that another way to the root ends up to 1e-7 from
 // it; the same bisections are therefore made, but G is evaluated only where it has to be.
-// Halley's iteration from the mode of g (G''/G' = 1/z - (z - a)) finds the root, and the sign of
-// G - eta further than `band` from it is known: the band is 16 times the rounding of G's terms
-// over g (the 60 evaluations' bits for 3 million draws with a from -3 to 40; an eighth of it
-// did not give them).  Below a = -3 the cancellation in Z leaves little to gain.  Some 13 evaluations instead of 60, 18 for the
-// slowest of 64.
+// Halley's iteration from the mode of g (G''/G' = 1/z - (z - a)) finds the root, and G is
+// evaluated at `band` on either side of it: G grows with z, so where it is further from eta than
+// `noise` there (several times the rounding of its terms), the side of every point beyond is
+// known, whatever the iteration left.  If it is not, the band is widened, at last to the plain
+// bisections.  Below a = -3 the cancellation in Z leaves little to gain.  Some 15 evaluations
+// instead of 60.
 __device__ double flux_speed(double a, double eta) {
     const double pa = npdf(a), Z = pa + a * ncdf(a), cm = ncdf(-a), top = (a > 0.0 ? a : 0.0) + 40.0;
+    auto dist = [&](double m) { return (pa - npdf(m - a) + a * (ncdf(m - a) - cm)) / Z; };
     double z = 0.5 * (a + sqrt(a * a + 4.0)), band = 1e9;
     // (at the very ends of the distribution the rounding has no scale: the plain bisections)
     if (a >= -3.0 && eta > 1e-12 && eta < 1.0 - 1e-12) {
         const double noise = 2e-15 * (1.0 + (pa + fabs(a)) / Z);
-        double lo = 0.0, hi = top;
+        double lo = 0.0, hi = top, b = 0.0;
         for (int it = 0; it < 24; ++it) {
             const double t = z - a, p = npdf(t);
             const double f = (pa - p + a * (ncdf(t) - cm)) / Z - eta, g = z * p / Z;
@@ -2105,12 +2107,15 @@ __device__ double flux_speed(double a, double eta) {
             if (den > 0.5) dz = dz / den;
             double zn = z - dz;
             if (!(zn >= lo && zn <= hi)) zn = 0.5 * (lo + hi);
-            const double moved = fabs(zn - z), b = noise / g + 2e-15 * (z + 1.0);
+            const double moved = fabs(zn - z);
+            b = 2.0 * noise / g + 2e-15 * (z + 1.0);
             z = zn;
-            if (moved <= 1e-6 || moved <= 0.25 * b) {
-                band = b;
-                break;
-            }
+            if (moved <= 1e-6 * fmin(z, 1.0) || moved <= 0.25 * b) break;
+        }
+        for (int k = 0; k < 3 && band > 1e8; ++k) {
+            const double zl = z - b, zr = z + b;
+            if ((zl <= 0.0 || dist(zl) < eta - noise) && (zr >= top || dist(zr) > eta + noise)) band = b;
+            b = 8.0 * b;
         }
     }
     double lo = 0.0, hi = top;
@@ -2119,7 +2124,7 @@ __device__ double flux_speed(double a, double eta) {
         bool below = m < z - band;
         if (!below && !(m > z + band)) {
             if (m <= lo || m >= hi) break;  // neighbouring numbers: m is the side it was before
-            below = (pa - npdf(m - a) + a * (ncdf(m - a) - cm)) / Z < eta;
+            below = dist(m) < eta;
         }
         if (below)
             lo = m;

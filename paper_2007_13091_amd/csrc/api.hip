@@ -500,6 +500,14 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
         for (int k = 0; k < n_inst; ++k)
             per_cell += (double)(ctx->ranges[k].cell1 - ctx->ranges[k].cell0) * std::max(p[k].n_ref, p[k].n_min);
         D.list_sparse = H.nc >= 16384 && per_cell < 320.0 * (double)H.nc ? 1 : 0;
+        D.long_any = 0;
+        D.list_split = 1;
+        for (int k = 0; k < n_inst; ++k) {
+            const int ref = std::max(p[k].n_ref, p[k].n_min);
+            if (!ugkwp::long_cells(ctx->ranges[k].cell1 - ctx->ranges[k].cell0, ref)) continue;
+            D.long_any = 1;
+            D.list_split = std::max(D.list_split, ugkwp::list_split(H.nc, D.list_sparse != 0, ref));
+        }
     }
     D.cap = cap;
     D.prec = p[0].precision;
@@ -517,6 +525,7 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
         q.c2 = p[k].c2;
         q.n_ref = p[k].n_ref;
         q.n_min = p[k].n_min;
+        q.long_cells = ugkwp::long_cells(r.cell1 - r.cell0, std::max(q.n_ref, q.n_min)) ? 1 : 0;
         q.max_cross = p[k].max_crossings;
         q.recon = p[k].recon;
         q.venkat_k = p[k].venkat_k;

@@ -2682,16 +2682,37 @@ __device__ __forceinline__ void block_counts(const Dev &D, unsigned long long nx
     }
 }
 
-// BS threads per block (a wave per cell), ILP runs of 64 particles loaded together
-template <typename R, int BS, bool MULTI, int ILP, bool KE>
-__device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
-    constexpr int CPR = RecChunks<R>::N, WPB = BS / kWave;
-    __shared__ uint4 stage[WPB][kWave * CPR];  // output stage of each wave
+// Cells with many particles.  A wave per cell goes through its cell's runs of 64 one after the other, so a few
+// cells of thousands of particles leave the chip idle: in an instance of at most kLongCells cells and
+// kLongRef or more reference particles a cell of more than kLongCell particles is left to
+// k_stream_long.  There the kLongWaves waves of a block take the runs in turn, with the same
+// places for every particle (the runs' counts meet in local memory); the sums are those of the
+// waves in their order.  The rule looks at the instance and the cell alone, so a cell's bits do
+// not depend on the batch around it.
+// 64 boxes of 10,000 particles, FP64: 331 us with a wave per cell, 105 with four (a step, with the
+// lists split as well and k_gather_long, 1.03 ms and 0.30; a thread per particle 0.70).  The
+// limits: 64 boxes of 700 particles 0.116 and 0.090 ms a step, of 500 particles 0.102 with a wave
+// (0.117 a thread per particle); 1,000 boxes of 700 particles are 0.133 ms with a wave per cell
+// and 0.153 with a thread per particle.  A batch of 32 x 512 boxes, whose cells would fill the chip
+// either way: 700 particles 0.604 and 0.601 ms (FP32 0.438 and 0.453), 1,500 particles 1.175 and
+// 1.157 (0.845 and 0.827); eight waves took 0.722 (0.525) there, most of them idle in the last round.
+constexpr int kLongRef = 640, kLongCell = 512, kLongWaves = 4;
+constexpr long long kLongCells = 512;
+template <int W>
+struct LongShared {
+    int2 cnt[2][W];       // stayers and listed particles of the waves' runs, two rounds
+    double sum[W][10];    // P and collided sums of the waves
+    int own[W];
+};
+
+// One cell's free flight by the W waves of a block (W = 1: by one wave, without a barrier), ILP runs of 64
+// particles loaded together.
+template <typename R, bool MULTI, int ILP, bool KE, int W>
+__device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w, uint4 *st, LongShared<W> *sh) {
+    constexpr int CPR = RecChunks<R>::N;
     const Scalars *sc = D.sc;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
-    const int c = blockIdx.x * WPB + wave;
+    const int lane = lane_id();
     const int nc = D.nc;
-    if (c >= nc || sc->none) return;
     const Particles pa = D.pa[buf], pb = D.pa[buf ^ 1];
     const long long n_new = sc->n_new, span = sc->span[buf], n_mov = sc->n_mov;
     const unsigned long long o0 = D.off[c], o1 = D.off[c + 1];
@@ -2699,6 +2720,11 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
     const int ns = n_new > 0 ? (int)(D.samoff[c + 1] - so) : 0;
     const int nold = hi32(o1) - hi32(o0), nm = lo32(o1) - lo32(o0);
     const int n = nold + ns;
+    if (D.long_any || W > 1) {
+        // (no list of these cells: a store before the loads below would take them off the scalar unit)
+        const bool many = n > kLongCell && D.ip[MULTI ? D.cinst[c] : 0].long_cells;
+        if (many != (W > 1)) return;
+    }
     const int v0 = hi32(o0) + (int)so;  // this cell's region of the next buffer
     const int vs = D.v0[buf][c] - nm;   // slot of an old particle k >= nm: vs + k
     // places of its arrivals and of its new particles in the second part of this buffer: am + k
@@ -2724,10 +2750,11 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
     }
     const R elow = e * (sizeof(R) == 8 ? (R)(1.0 - 1e-12) : (R)(1.0f - 1e-5f));
     const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
-    uint4 *st = stage[wave];
     double Pn[5] = {0, 0, 0, 0, 0}, Cn[5] = {0, 0, 0, 0, 0};
     int nst = 0, nlv = 0, nco = 0;  // stayers, particles that meet a face, collided here
-    for (int k0 = 0; k0 < n; k0 += ILP * kWave) {
+    int round = 0;
+    for (int r0 = 0; r0 < n; r0 += W * ILP * kWave) {
+        const int k0 = r0 + w * kWave;
         Part<R> q[ILP];
         int slot[ILP];
 #pragma unroll
@@ -2780,6 +2807,24 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
             const bool stay = k < n && !meets && !collided, own = k < n && !meets && collided;
             const unsigned long long ms = __ballot(stay), ml = __ballot(meets), mo = __ballot(own);
             const int cs = (int)__popcll(ms);
+            int ps = nst, pl = nlv, as = cs, al = (int)__popcll(ml);  // first places, and the round's counts
+            if (W > 1) {
+                int2 *cnt = sh->cnt[round & 1];
+                ++round;
+                if (lane == 0) cnt[w] = make_int2(as, al);
+                __syncthreads();  // (the next but one round writes these again: one barrier a round is enough)
+                as = al = 0;
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    const int2 v = cnt[i];
+                    if (i < w) {
+                        ps += v.x;
+                        pl += v.y;
+                    }
+                    as += v.x;
+                    al += v.y;
+                }
+            }
             if (stay) {
                 // the transport's last move of a flight that meets no face
 #pragma unroll
@@ -2787,21 +2832,21 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
                 add_phi<R>(Pn, q[j].m, q[j].u, q[j].e);
                 const int rs = (int)__popcll(ms & below);
                 stage_part(st + rs * CPR, q[j]);
-                store_side<KE>(pb, v0 + nst + rs, q[j]);
+                store_side<KE>(pb, v0 + ps + rs, q[j]);
             }
             if (mo && own) add_phi<R>(Cn, q[j].m, q[j].u, q[j].e);
             if (meets) {
-                const int li = v0 + nlv + (int)__popcll(ml & below);
+                const int li = v0 + pl + (int)__popcll(ml & below);
                 D.lsrc[li] = (uint32_t)slot[j] | (k < nold ? 0u : kNewBit);
                 reinterpret_cast<R *>(D.perm + li)[0] = collided ? -ts : ts;  // (ts > 0)
             }
             // the wave's LDS accesses stay in order; consecutive lanes on consecutive chunks
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            uint4 *g = rec_chunks(pb, v0 + nst, R(0));
+            uint4 *g = rec_chunks(pb, v0 + ps, R(0));
             for (int i = lane; i < cs * CPR; i += kWave) st_nt(&g[i], st[i]);
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            nst += cs;
-            nlv += (int)__popcll(ml);
+            nst += as;
+            nlv += al;
             nco += (int)__popcll(mo);
         }
     }
@@ -2809,6 +2854,23 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
     // what collided here comes off S
     double Pk, Ck;
     wave_sum_pc(Pn, Cn, Pk, Ck);
+    if (W > 1) {
+        if (lane < 5) {
+            sh->sum[w][lane] = Pk;
+            sh->sum[w][5 + lane] = Ck;
+        }
+        if (lane == 0) sh->own[w] = nco;
+        __syncthreads();
+        if (w != 0) return;
+        nco = 0;
+        for (int i = 0; i < W; ++i) nco += sh->own[i];
+        if (lane < 5) {
+            for (int i = 1; i < W; ++i) {
+                Pk += sh->sum[i][lane];
+                Ck += sh->sum[i][5 + lane];
+            }
+        }
+    }
     if (lane < 5) {
         if (nco) D.S[lane * nc + c] = D.S[lane * nc + c] - Ck;
         D.P[lane * nc + c] = Pk;
@@ -2821,6 +2883,16 @@ __device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
     }
 }
 
+// BS threads per block, a wave per cell
+template <typename R, int BS, bool MULTI, int ILP, bool KE>
+__device__ __forceinline__ void stream_cells(const Dev &D, int buf) {
+    constexpr int CPR = RecChunks<R>::N, WPB = BS / kWave;
+    __shared__ uint4 stage[WPB][kWave * CPR];  // output stage of each wave
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int c = blockIdx.x * WPB + wave;
+    if (c >= D.nc || D.sc->none) return;
+    stream_cell<R, MULTI, ILP, KE, 1>(D, buf, c, 0, stage[wave], nullptr);
+}
 template <typename R, int BS, bool MULTI, int ILP>
 __global__ void __launch_bounds__(BS) k_stream(Dev D, int buf) {
     stream_cells<R, BS, MULTI, ILP, false>(D, buf);
@@ -2829,6 +2901,16 @@ __global__ void __launch_bounds__(BS) k_stream(Dev D, int buf) {
 template <typename R, int BS, bool MULTI, int ILP>
 __global__ void __launch_bounds__(BS) k_stream_e(Dev D, int buf) {
     stream_cells<R, BS, MULTI, ILP, true>(D, buf);
+}
+
+// the cells that k_stream leaves, a block each (the blocks of other cells leave at once)
+template <typename R, bool MULTI, bool KE>
+__global__ void __launch_bounds__(kLongWaves * kWave) k_stream_long(Dev D, int buf) {
+    __shared__ uint4 stage[kLongWaves][kWave * RecChunks<R>::N];
+    __shared__ LongShared<kLongWaves> sh;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    if (D.sc->none) return;
+    stream_cell<R, MULTI, 1, KE, kLongWaves>(D, buf, (int)blockIdx.x, wave, stage[wave], &sh);
 }
 
 // Lanes of a wave grouped by key with ballots only: mine = the lanes that share this lane's
@@ -2912,7 +2994,7 @@ __global__ void __launch_bounds__(256) k_track(Dev D, int buf) {
         const int n = L.pre[G];
         uint4 *st = stage[wave];
         int *ls = lslot[wave];
-        for (int k0 = 0; k0 < n; k0 += kWave) {
+        for (int k0 = (int)blockIdx.y * kWave; k0 < n; k0 += D.list_split * kWave) {
             const int k = k0 + lane, nr = min(kWave, n - k0);
             int key = -1, li = 0;
             if (k < n) {
@@ -3025,7 +3107,7 @@ __global__ void __launch_bounds__(256) k_scatter(Dev D) {
     if (c0 >= D.nc || D.sc->none) return;
     const unsigned long long run = lane < G && c0 + lane < D.nc ? D.lrun[c0 + lane] : 0ULL;
     const Runs<G> L(hi32(run), lo32(run));
-    for (int k0 = 0; k0 < L.pre[G]; k0 += kWave) {
+    for (int k0 = (int)blockIdx.y * kWave; k0 < L.pre[G]; k0 += D.list_split * kWave) {
         int j, li = 0, key = -1;
         uint32_t src = 0;
         if (k0 + lane < L.pre[G]) {
@@ -3053,22 +3135,23 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ---------------------------------------------------------------------------------------
-// Sort by one wave of a list of distinct values, ascending.  Bitonic network whose
-// comparators all put the smaller value first, so entries past len behave as +infinity and
-// are never touched.  a may point to LDS or to global memory; only this wave touches it.
+// Sort of a list of distinct values by the W waves of a block (t: the thread's number among theirs),
+// ascending.  Bitonic network whose comparators all put the smaller value first, so entries past
+// len behave as +infinity and are never touched.  a may point to LDS or to global memory; only
+// these waves touch it.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void wave_sort(unsigned long long *a, int len) {
-    constexpr int BS = kWave;
-    const int lane = lane_id();
+template <int W>
+__device__ __forceinline__ void sort_list(unsigned long long *a, int len, int t) {
+    constexpr int BS = W * kWave;
     int bad = 0;
-    for (int i = lane; i + 1 < len; i += BS) bad |= a[i] > a[i + 1];
-    if (!__ballot(bad)) return;
+    for (int i = t; i + 1 < len; i += BS) bad |= a[i] > a[i + 1];
+    if (W == 1 ? !__any(bad) : !__syncthreads_or(bad)) return;
     int N = 1;
     while (N < len) N <<= 1;
     for (int k = 2; k <= N; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
             const bool flip = j == (k >> 1);
-            for (int p = lane; p < N / 2; p += BS) {
+            for (int p = t; p < N / 2; p += BS) {
                 const int i = 2 * (p & ~(j - 1)) + (p & (j - 1));
                 const int q = flip ? (i ^ (k - 1)) : i + j;
                 if (q < len) {
@@ -3079,10 +3162,14 @@ __device__ __forceinline__ void wave_sort(unsigned long long *a, int len) {
                     }
                 }
             }
-            wave_sync();
+            if (W == 1)
+                wave_sync();
+            else
+                __syncthreads();
         }
     }
 }
+__device__ __forceinline__ void wave_sort(unsigned long long *a, int len) { sort_list<1>(a, len, lane_id()); }
 
 // A bucket of 64 < n <= 256 entries sorted into lds, by its pieces (kHeadBit) if they are at most
 // 64: a piece stays together, behind the pieces whose first order is smaller.  tab: local memory
@@ -3146,12 +3233,12 @@ __device__ __forceinline__ void sort_pieces(const unsigned long long *a, int n, 
 // two a bucket takes depends on its own length alone, so the sums do not depend on the cells
 // around it: bitwise reproducible, alone or in a batch.
 // ---------------------------------------------------------------------------------------
+constexpr int kGatherLds = 256;  // longer lists are sorted in place in global memory
 template <typename R, int WPB, bool KE, int G>
 __device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
     constexpr int BS = kWave;
-    constexpr int kLds = 256;  // longer lists are sorted in place in global memory
     constexpr int CPR = RecChunks<R>::N;
-    __shared__ unsigned long long lds_all[WPB][kLds];
+    __shared__ unsigned long long lds_all[WPB][kGatherLds];
     __shared__ uint4 st_all[WPB][kWave * CPR];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
     // blocks go round-robin to the 8 XCDs; give each XCD a contiguous range of cells so that
@@ -3260,11 +3347,13 @@ __device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
                     for (int k = 0; k < 5; ++k) to[k * nc + c] = part == 0 ? pv[k] + acc[k] : pv[k] - acc[k];
                 }
                 wave_sync();
+            } else if (nr > kGatherLds && D.long_any && D.ip[inst_of(D, c0 + g)].long_cells) {
+                // k_gather_long's
             } else if (nr > 0) {
                 // one bucket of more than 64
                 const int pl = a0 + pg;
                 unsigned long long *list = D.perm + pl;
-                if (nr <= kLds) {
+                if (nr <= kGatherLds) {
                     sort_pieces(list, nr, lds, reinterpret_cast<unsigned long long *>(st));
                     list = lds;
                 } else {
@@ -3311,6 +3400,59 @@ __global__ void __launch_bounds__(WPB * 64) k_gather(Dev D, int buf) {
 template <typename R, int WPB, bool KE>
 __global__ void __launch_bounds__(WPB * 64) k_gather_sparse(Dev D, int buf) {
     gather_cells<R, WPB, KE, kListCellsSparse>(D, buf);
+}
+
+// The buckets of more than kGatherLds entries in the cells whose transport a block may share
+// (k_stream_long): a block each, its waves taking the runs of 64 in turn.  What bounds a wave alone
+// there is the sort (78 passes over 4,096 entries in global memory); here up to kLongSort entries
+// are sorted in local memory.  64 boxes of 10,000 particles: 330 us in k_gather, 33 here.
+constexpr int kLongSort = 4096, kSortWaves = 8;
+template <typename R, bool KE>
+__global__ void __launch_bounds__(kSortWaves * kWave) k_gather_long(Dev D, int buf) {
+    __shared__ unsigned long long lds[kLongSort];
+    __shared__ double sum[kSortWaves][5];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    const int c = (int)blockIdx.x, nc = D.nc;
+    if (D.sc->none || !D.ip[inst_of(D, c)].long_cells) return;
+    const Particles src = D.pa[buf], dst = D.pa[buf ^ 1];
+    const long long span = D.sc->span[buf ^ 1];
+    for (int part = 0; part < 2; ++part) {
+        const unsigned long long *off = D.off + (part == 0 ? 0 : nc);
+        const int first = lo32(off[c]), nr = lo32(off[c + 1]) - first;
+        if (nr <= kGatherLds) continue;
+        unsigned long long *list = D.perm + first;
+        if (nr <= kLongSort) {
+            for (int k = threadIdx.x; k < nr; k += kSortWaves * kWave) lds[k] = list[k];
+            __syncthreads();
+            list = lds;
+        }
+        sort_list<kSortWaves>(list, nr, (int)threadIdx.x);
+        double acc[5] = {0, 0, 0, 0, 0};
+        for (int k = wave * kWave + lane; k < nr; k += kSortWaves * kWave) {
+            Part<R> A;
+            load_part<KE>(src, (long long)(lo32(list[k]) & ~kHeadBit), A);
+            add_phi<R>(acc, A.m, A.u, A.e);
+            if (part == 0) {
+                const int o = slot_of(D, buf ^ 1, span, first + k);
+                store_side<KE>(dst, o, A);
+                stage_part(rec_chunks(dst, o, R(0)), A);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < 5; ++k) sum[wave][k] = acc[k];
+        }
+        __syncthreads();
+        if (threadIdx.x < 5) {
+            double *to = (part == 0 ? D.P : D.S) + threadIdx.x * nc + c;
+            double v = sum[0][threadIdx.x];
+            for (int w = 1; w < kSortWaves; ++w) v += sum[w][threadIdx.x];
+            *to = part == 0 ? *to + v : *to - v;
+        }
+        __syncthreads();  // (the list and the sums are read before the next part's are written)
+    }
 }
 
 // the particles between two steps in their order (arrivals, stayers, cell by cell), one after
@@ -3777,6 +3919,15 @@ void count_new(const Dev &D, int buf, hipStream_t s, Prof *pr) {
 
 }  // namespace
 
+bool long_cells(long long cells, long long per_cell) { return per_cell >= kLongRef && cells <= kLongCells; }
+int list_split(long long nc, bool sparse, long long per_cell) {
+    // some 30% of a cell's particles meet a face; 4,096 waves fill the chip (64 boxes of 10,000
+    // particles: k_track 326 us with one row, 26 with 94, k_scatter 51 and 11)
+    const int g = sparse ? kListCellsSparse : kListCellsDense;
+    const long long waves = (nc + g - 1) / g, runs = (3 * per_cell * g / 10 + kWave - 1) / kWave;
+    return (int)std::max(1LL, std::min({runs, 4096 / waves, 256LL}));
+}
+
 long long scan_partials_needed(long long n) { return (n + kScanTile - 1) / kScanTile + 1; }
 long long count_partials_needed(long long nc, long long nff) {
     return (nc + kCountBS - 1) / kCountBS + (nff + kCountBS - 1) / kCountBS;
@@ -3811,19 +3962,33 @@ void launch_stream_i(const Dev &D, int buf, int bs, hipStream_t s) {
         k_stream<R, 256, MULTI, ILP><<<g, 256, 0, s>>>(D, buf);
 }
 
+// the transport of the cells that k_stream leaves to blocks
+template <typename R, bool MULTI>
+void launch_stream_long(const Dev &D, int buf, hipStream_t s) {
+    if (!D.long_any) return;
+    const unsigned g = (unsigned)D.nc;
+    if (D.K > 0)
+        k_stream_long<R, MULTI, true><<<g, kLongWaves * kWave, 0, s>>>(D, buf);
+    else
+        k_stream_long<R, MULTI, false><<<g, kLongWaves * kWave, 0, s>>>(D, buf);
+}
+
 // blocks of the kernels that take several cells per wave
 unsigned list_grid(const Dev &D, int waves = 4) {
     const int per = waves * (D.list_sparse ? kListCellsSparse : kListCellsDense);
     return (unsigned)((D.nc + per - 1) / per);
 }
+// The same over the lists, whose runs of 64 entries are independent of one another: D.list_split
+// rows of waves take them in turn (one unless a few cells hold long lists).
+dim3 list_grid_runs(const Dev &D) { return dim3(list_grid(D), (unsigned)D.list_split); }
 
 template <typename R, bool KE, int MESH>
 void launch_track_m(const Dev &D, int buf, hipStream_t s) {
     if (D.nff > 0) k_stream_in<R, KE, MESH><<<256, 256, 0, s>>>(D, buf);
     if (D.list_sparse)
-        k_track<R, KE, MESH, kListCellsSparse><<<list_grid(D), 256, 0, s>>>(D, buf);
+        k_track<R, KE, MESH, kListCellsSparse><<<list_grid_runs(D), 256, 0, s>>>(D, buf);
     else
-        k_track<R, KE, MESH, kListCellsDense><<<list_grid(D), 256, 0, s>>>(D, buf);
+        k_track<R, KE, MESH, kListCellsDense><<<list_grid_runs(D), 256, 0, s>>>(D, buf);
 }
 
 template <typename R, bool KE>
@@ -3847,17 +4012,30 @@ void launch_stream(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
         launch_stream_i<R, false, 2>(D, buf, cfg.stream_bs, s);
     else
         launch_stream_i<R, false, 1>(D, buf, cfg.stream_bs, s);
+    if (D.n_inst > 1)
+        launch_stream_long<R, true>(D, buf, s);
+    else
+        launch_stream_long<R, false>(D, buf, s);
     if (D.K > 0)
         launch_track<R, true>(D, buf, s);
     else
         launch_track<R, false>(D, buf, s);
 }
 
+template <typename R>
+void launch_gather_long(const Dev &D, int buf, hipStream_t s) {
+    if (!D.long_any) return;
+    if (D.K > 0)
+        k_gather_long<R, true><<<(unsigned)D.nc, kSortWaves * kWave, 0, s>>>(D, buf);
+    else
+        k_gather_long<R, false><<<(unsigned)D.nc, kSortWaves * kWave, 0, s>>>(D, buf);
+}
+
 void launch_scatter(const Dev &D, hipStream_t s) {
     if (D.list_sparse)
-        k_scatter<kListCellsSparse><<<list_grid(D), 256, 0, s>>>(D);
+        k_scatter<kListCellsSparse><<<list_grid_runs(D), 256, 0, s>>>(D);
     else
-        k_scatter<kListCellsDense><<<list_grid(D), 256, 0, s>>>(D);
+        k_scatter<kListCellsDense><<<list_grid_runs(D), 256, 0, s>>>(D);
     if (D.nff > 0) k_scatter_in<<<256, 256, 0, s>>>(D);
 }
 
@@ -4008,6 +4186,10 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
         else
             k_gather<double, WPB, false><<<g, WPB * 64, 0, s>>>(D, buf);
     }
+    if (f32)
+        launch_gather_long<float>(D, buf, s);
+    else
+        launch_gather_long<double>(D, buf, s);
     k_update<<<gc + 1, 256, 0, s>>>(D);
     launch_heat(D, buf ^ 1, s);
     pr->end(kSlotGather);

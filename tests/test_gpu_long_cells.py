@@ -1,0 +1,143 @@
+"""Few cells with many particles each: cells of more than 512 particles in an instance of at most 512
+cells and at least 640 reference particles, whose transport (and buckets of more than 256) the
+waves of a block share.
+
+* Against the oracle: cells on both sides of 512, buckets on both sides of 256 and of 4,096 (the
+  sort's local memory), boxes, tetrahedra, entering particles, internal energies.  The bar is that
+  of tests/parity.py and the rounding of the oracle's running sum over a cell's n particles,
+  n 2^-53; the masses of the sampled particles, which come from rho - rho^p, are left out.
+* Bit for bit the same with any launch shape, in a batch, and at the tightest capacity.
+* A move takes no more than a few times as long as with the same particles in many cells.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2007_13091_amd import workloads as wl
+from parity import RTOL, compare_fields, compare_particles, compare_stats
+
+pytestmark = pytest.mark.gpu
+
+
+def _solver(w, precision=0, capacity=0):
+    from paper_2007_13091_amd.ugkwp import Solver
+
+    s = Solver(w.mesh, w.params, precision=precision, capacity=capacity)
+    s.init_state(w.W0)
+    return s
+
+
+def _case(name):
+    if name == "boxes":
+        return wl.closed_box(n=(3, 2, 2), n_ref=640, kn=0.3, bc=wl.BC_DIFFUSE)
+    if name == "tets-inflow":
+        return wl.free_stream_box(n=(2, 2, 1), U=(1.5, 0.4, -0.3), n_ref=700, kn=0.5, tets=True, jitter=0.1,
+                                  walls={"zlo": wl.BC(wl.BC_DIFFUSE, Tw=1.0)})
+    if name == "diatomic":
+        return wl.closed_box(n=(3, 2, 1), n_ref=900, kn=0.5, bc=wl.BC_DIFFUSE, gamma=1.4)
+    if name == "thousands-of-arrivals":
+        return wl.closed_box(n=(2, 1, 1), n_ref=20000, kn=5.0)
+    if name == "thinned":
+        return wl.closed_box(n=(4, 3, 2), n_ref=900, kn=1e5)
+    return wl.closed_box(n=(2, 2, 1), n_ref=4000, kn=1.0, tets=True)  # "tets"
+
+
+def _thinned(w, o):
+    """A state of particles alone in which every other cell holds 2 of 5 (particles leave no room
+    for new ones, so its cells stay below 512)."""
+    o.step()
+    st = o.export_state()
+    p = st["particles"]
+    keep = (p["cell"] % 2 == 0) | (np.arange(p["uid"].size) % 5 < 2)
+    p = {k: v[keep] for k, v in p.items()}
+    p = {k: v[np.argsort(p["cell"], kind="stable")] for k, v in p.items()}
+    phi = np.concatenate([np.ones((p["m"].size, 1)), p["u"], 0.5 * (p["u"] ** 2).sum(1, keepdims=True)], 1) * p["m"][:, None]
+    P = np.stack([np.bincount(p["cell"], phi[:, k], w.mesh.n_cells) for k in range(5)], 1)
+    vol, _, _ = o.geometry()
+    return dict(st, W=P / vol[:, None], P=P, particles=p)
+
+
+@pytest.mark.parametrize("name", ["boxes", "tets-inflow", "diatomic", "thousands-of-arrivals", "tets", "thinned"])
+def test_long_cells_against_the_oracle(name):
+    w = _case(name)
+    s, o = _solver(w), oracle.Oracle(w.mesh, w.params)
+    o.set_state(w.W0)
+    vol, _, _ = o.geometry()
+    if name == "thinned":
+        st = _thinned(w, o)
+        o.import_state(st)
+        s.import_state(st)
+    least, most = 1 << 30, 0
+    for n in range(4):
+        st = s.step(1)
+        o.step()
+        pg, po = s.particles(), o.particles()
+        held = np.bincount(pg["cell"], minlength=w.mesh.n_cells)
+        least, most = min(least, int(held.min())), max(most, int(held.max()))
+        rtol = RTOL + 2.0 ** -53 * 3 * most
+        what = f"{name} step {n}"
+        print(f"[gpu-long-cells] {what}: {held.min()} to {held.max()} particles a cell", flush=True)
+        compare_stats(st, o.stats(), what=what)
+        Wo, Po, _ = o.state()
+        compare_fields(s.moments(0), Wo, s.moments(1) * vol[:, None], Po, vol, rtol=rtol, what=what)
+        compare_particles(dict(pg, m=np.ones_like(pg["m"])), dict(po, m=np.ones_like(po["m"])), vscale=4.0, rtol=rtol,
+                          what=what)
+    assert most > 512 and (name != "thinned" or least < 512)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("name", ["boxes", "diatomic", "tets-inflow"])
+def test_long_cells_are_the_same_bits_in_any_surroundings(name, precision):
+    from paper_2007_13091_amd.ugkwp import Solver
+
+    w = _case(name)
+    # (a K > 0 instance has to share its K with the batch)
+    other = wl.closed_box(n=(4, 3, 2), n_ref=50, gamma=w.params.gamma)
+    a = _solver(w, precision, capacity=200000)
+    b = _solver(w, precision, capacity=200000)
+    b.launch_config((512, 2, 8, 64))
+    batch = Solver([w.mesh, other.mesh], [w.params, other.params], precision=precision)
+    batch.init_state(np.concatenate([w.W0, other.W0]))
+    lo, hi = batch.instance_cells(0)
+    most, steps = 0, []
+    for n in range(5):
+        st = a.step(1)
+        most = max(most, st["n_moved"])
+        assert b.step(1) == st
+        batch.step(1)
+        W, Wp = a.moments(0), a.moments(1)
+        np.testing.assert_array_equal(b.moments(0), W)
+        np.testing.assert_array_equal(b.moments(1), Wp)
+        np.testing.assert_array_equal(batch.moments(0)[lo:hi], W)
+        np.testing.assert_array_equal(batch.moments(1)[lo:hi], Wp)
+        steps.append((st, W, Wp, a.particles()))
+    tight = _solver(w, precision, capacity=most)
+    for n, (st, W, Wp, p) in enumerate(steps):
+        assert tight.step(1) == st
+        np.testing.assert_array_equal(tight.moments(0), W)
+        np.testing.assert_array_equal(tight.moments(1), Wp)
+        q = tight.particles()
+        for k in p:
+            np.testing.assert_array_equal(q[k], p[k], err_msg=f"step {n} {k}")
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_a_move_costs_about_the_same_in_few_cells(precision):
+    def per_move(n, n_ref):
+        w = wl.closed_box(n=(n, n, n), n_ref=n_ref, bc=wl.BC_DIFFUSE)
+        w.params.sampling = 1
+        s = _solver(w, precision, capacity=4 * n_ref * n ** 3)
+        s.step(5)
+        s.profile(True, slots=["stream", "gather"])
+        best = np.inf
+        for _ in range(5):
+            s.profile_read()
+            st = s.step(4)
+            p = s.profile_read()
+            best = min(best, sum(p[k][0] for k in ("stream", "gather")) / (4 * st["n_moved"]))
+        s.close()
+        return best
+
+    many, few = per_move(16, 156), per_move(4, 10000)
+    print(f"[gpu-long-cells] ns a move: {1e6 * many:.3f} in 4,096 cells, {1e6 * few:.3f} in 64", flush=True)
+    assert few < 5.0 * many

@@ -1164,14 +1164,23 @@ int32_t ugkwp_autotune(ugkwp_ctx *ctx, int32_t steps_per_trial, int32_t *cfg_out
 
 namespace {
 
-// The workload signature that keys the autotuner's cache: the device, the precision, K, the
-// sizes and every instance's reconstruction, sampling mode and collision model.
+// The kernels that the launch shapes belong to: raised when a shape comes to mean another split of the
+// work or its kernel is another one, so that a cache written by another build's kernels misses
+// (2: a wave per cell in the transport).
+constexpr int kShapesVersion = 2;
+
+// The workload signature that keys the autotuner's cache: the device, the kernels, the precision, K,
+// the sizes, what picks between kernels of one shape (cell types, lists, shared cells) and every
+// instance's reconstruction, sampling mode and collision model.
 std::string tune_key(const ugkwp_ctx *ctx) {
     int dev = 0;
     hipDeviceProp_t prop{};
     std::string arch = "?";
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) arch = prop.gcnArchName;
-    std::string k = arch + " prec=" + std::to_string(ctx->D.prec) + " K=" + std::to_string(ctx->D.K) +
+    const ugkwp::Dev &D = ctx->D;
+    std::string k = arch + " shapes=" + std::to_string(kShapesVersion) +
+                    " mesh=" + (D.all_box ? "box" : (D.all_tet ? "tet" : "any")) +
+                    " sparse=" + std::to_string(D.list_sparse) + " long=" + std::to_string(D.long_any) + " prec=" + std::to_string(ctx->D.prec) + " K=" + std::to_string(ctx->D.K) +
                     " inst=" + std::to_string(ctx->D.n_inst) + " cells=" + std::to_string(ctx->D.nc) +
                     " faces=" + std::to_string(ctx->D.nf) + " cap=" + std::to_string(ctx->D.cap) + " modes=";
     for (const ugkwp_params &p : ctx->ps) {

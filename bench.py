@@ -28,12 +28,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, vendor figure
-# algorithmic bytes of one particle move: the particle state read once and written once
-# (FP64: x 24 + u 24 + m 8 + cell 4 + uid 8 = 68 B; FP32 form: 12 + 12 + 4 + 4 + 8 = 40 B)
+# a particle's record as it lies in memory (FP64: x 24 + u 24 + m 8 + uid 8; FP32 form: 12 + 12 + 8
+# in the record and the mass beside it, 4); its cell follows from its place
+RECORD_BYTES = {"double": 64, "float": 36}
+# the charges of kernel_roofline and whole_step where the survivors are not known: a record with a
+# cell index of 4 B, read once and written once; in a gather that moves every survivor a
+# survivor's record and bucket key, a collided particle's velocity, mass and key
 BYTES_PER_MOVE = {"double": 136, "float": 80}
-# algorithmic bytes of the gather (S6): a survivor's record read and written with its cell,
-# plus its bucket key read (FP64: 64 + 64 + 4 + 4 = 136 B; FP32: 36 + 40 + 4 = 80 B); a
-# collided particle's velocity and mass read with its key (FP64: 48 + 4 = 52 B; FP32: 36 + 4)
 BYTES_PER_SURVIVOR = {"double": 136, "float": 80}
 BYTES_PER_COLLIDED = {"double": 52, "float": 40}
 # algorithmic bytes of a first-order cell-step: W and P read and written, volume and the
@@ -142,22 +143,36 @@ def kernel_roofline(kms, moves_per_step, last, rtype, names, workload):
     return dom, out
 
 
-def charge_transport_alone(kr):
-    """The transport writes the particles that stay in their cell itself, so the gather moves only
-    arrivals and collided particles, whose number the statistics do not hold: a rate from all
-    survivors would not be one of bytes that it moves.  Its time stays; the move is charged to
-    the transport."""
+def transport_bytes(rtype, moves, survivors):
+    """Algorithmic bytes of a step's particles: every record read once, a survivor's written once
+    (one that collides or leaves the domain is read, summed and dropped)."""
+    return RECORD_BYTES[rtype] * (moves + survivors)
+
+
+def _rate(nbytes, ms):
+    ach = nbytes / (ms * 1e-3) / 1e9
+    return {"achieved": round(ach, 1), "frac": round(ach / HBM_PEAK_GBS, 4)}
+
+
+def charge_transport_alone(kr, rtype, moves, survivors):
+    """The transport reads every particle and writes the survivors, most of them at once to where
+    the next step reads them; the gather moves only arrivals and collided particles, whose number
+    the statistics do not hold: a rate from all survivors would not be one of bytes that it moves.
+    Its time stays; the particles are charged to the transport."""
+    n = transport_bytes(rtype, moves, survivors)
+    kr["stream"].update(_rate(n, kr["stream"]["kernel_avg_ms"]), algorithmic_bytes_per_launch=int(n))
     kr["gather"].update(achieved=None, frac=None, algorithmic_bytes_per_launch=None)
     return kr
 
 
-def whole_step(ms_per_step, moves_per_step, cells, rtype, recon=0):
-    """The whole step against HBM: the particle moves' and the cells' algorithmic bytes over
-    the wall time of a step."""
-    algo = BYTES_PER_MOVE[rtype] * moves_per_step + BYTES_PER_CELL[("hex", rtype, recon)] * cells
-    ach = algo / (ms_per_step * 1e-3) / 1e9
-    return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(ach / HBM_PEAK_GBS, 4), "algorithmic_bytes_per_step": int(algo)}
+def whole_step(ms_per_step, moves_per_step, cells, rtype, recon=0, survivors=None):
+    """The whole step against HBM: the particles' and the cells' algorithmic bytes over the wall
+    time of a step."""
+    part = (BYTES_PER_MOVE[rtype] * moves_per_step if survivors is None
+            else transport_bytes(rtype, moves_per_step, survivors))
+    algo = part + BYTES_PER_CELL[("hex", rtype, recon)] * cells
+    return {"bound": "hbm", **_rate(algo, ms_per_step), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "algorithmic_bytes_per_step": int(algo)}
 
 
 def _prim(W):
@@ -259,7 +274,7 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
     names = kernel_names("float", cfg, True, sparse=True)
     workload = "batch64"
     dom, kr = kernel_roofline(kms, moves / steps, st1, "float", names, workload)
-    charge_transport_alone(kr)
+    charge_transport_alone(kr, "float", moves / steps, st1["n_alive"])
     faces = sum((6 * w.mesh.n_cells + int(w.mesh.bface_nodes.shape[0])) // 2 for w in ws)
     flux_ms = fl[0] / max(fl[1], 1)
     flux_name = f"k_flux<float, {cfg[3]}>"
@@ -282,11 +297,11 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
     out = {"value": moves / el, "ms_per_step": ms, "cell_steps_per_s": nc * steps / el,
            "particles_per_step": int(moves / steps), "steps": steps, "timed_after_step": done_steps - steps,
            "launch_config": {"stream_bs": cfg[0], "stream_ilp": cfg[1], "sample_wpb": cfg[2], "flux_bs": cfg[3]},
-           "dominant": dom, "kernels": kr, "whole_step": whole_step(ms, moves / steps, nc, "float"),
+           "dominant": dom, "kernels": kr, "whole_step": whole_step(ms, moves / steps, nc, "float", survivors=st1["n_alive"]),
            "flux": flux_roof,
            "graph_replay_ms_per_step": round(tg, 4), "cells": nc, "instances": len(ws)}
     # FP64 plain, one instance after the other (eager launches), then the one-step error
-    pm, pt, pc = 0, 0.0, 0
+    pm, pt, pc, pa = 0, 0.0, 0, 0
     kt = {"stream": 0.0, "gather": 0.0}
     errs = []
     flips = 0
@@ -299,6 +314,7 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
         pm += mv
         pt += e
         pc += w.mesh.n_cells * steps
+        pa += b["n_alive"]
         for q in kt:
             kt[q] += km[q] * steps
         st = g.export_state()
@@ -321,13 +337,10 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
     out["fp64_plain_one_by_one"] = {
         "value": pm / pt, "unit": "particle moves/s", "cell_steps_per_s": pc / pt, "ms_per_step": p_ms,
         "kernel_ms_per_step_sum": {q: round(kt[q] / steps, 4) for q in kt},
-        "whole_step": whole_step(p_ms, pm / steps, nc, "double"),
-        "kernels": {q: {"kernel_avg_ms_mean_over_instances": round(kms64[q], 4),
-                        "achieved": round(BYTES_PER_MOVE["double"] * pm / steps / (kt[q] / steps * 1e-3) / 1e9, 1)
-                        if q == "stream" else None, "unit": "GB/s", "peak": HBM_PEAK_GBS} for q in kt}}
-    for q in kt:
-        ach = out["fp64_plain_one_by_one"]["kernels"][q]["achieved"]
-        out["fp64_plain_one_by_one"]["kernels"][q]["frac"] = None if ach is None else round(ach / HBM_PEAK_GBS, 4)
+        "whole_step": whole_step(p_ms, pm / steps, nc, "double", survivors=pa),
+        "kernels": {q: {"kernel_avg_ms_mean_over_instances": round(kms64[q], 4), "unit": "GB/s", "peak": HBM_PEAK_GBS,
+                        **(_rate(transport_bytes("double", pm / steps, pa), kt[q] / steps) if q == "stream"
+                           else {"achieved": None, "frac": None})} for q in kt}}
     out["speedup_vs_fp64_plain_one_by_one"] = out["value"] / (pm / pt)
     worst = {v: max(e[v]["L1"] for e in errs) for v in ("rho", "U", "T")}
     worst_inf = {v: max(e[v]["Linf"] for e in errs) for v in ("rho", "U", "T")}
@@ -365,14 +378,14 @@ def cavity_leg(precision, steps, warmup, start, sampling=0, recon=2, prandtl=1.0
     names = kernel_names(rtype, cfg, False)
     workload = f"cavity32_recon{recon}" + ("_gp" if sampling == 2 else "") + ("_shakhov" if prandtl != 1.0 else "")
     dom, kr = kernel_roofline(kms, moves / steps, st1, rtype, names, workload)
-    charge_transport_alone(kr)
+    charge_transport_alone(kr, rtype, moves / steps, st1["n_alive"])
     ms = el / steps * 1e3
     s.close()
     del s
     torch.cuda.empty_cache()
     leg = {"value": moves / el, "unit": "particle moves/s", "ms_per_step": ms, "cell_steps_per_s": nc * steps / el,
            "particles_per_step": int(moves / steps), "steps": steps, "timed_after_step": int(st1["step"]) - steps,
-           "dominant": dom, "kernels": kr, "whole_step": whole_step(ms, moves / steps, nc, rtype, recon)}
+           "dominant": dom, "kernels": kr, "whole_step": whole_step(ms, moves / steps, nc, rtype, recon, survivors=st1["n_alive"])}
     return leg
 
 

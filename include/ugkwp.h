@@ -277,9 +277,10 @@ int32_t ugkwp_geometry(ugkwp_ctx *ctx, double *vol, double *xc, double *dS);
 int32_t ugkwp_graph_enable(ugkwp_ctx *ctx, int32_t on);
 
 /* Launch shapes of the tunable kernels, cfg[4] = {k_stream block size (128, 256, 512; a
- * wave per cell), k_stream runs of 64 particles loaded together (1, 2), k_sample waves per block (1, 2, 4, 8; a wave takes 8
- * cells), k_flux block size (64, 128, 256)}.  Every shape gives bit-identical results.
- * Defaults: {256, 1, 4, 128}. */
+ * wave per cell), k_stream runs of 64 particles loaded together (1, 2), k_sample waves per
+ * block (1, 2, 4, 8; a wave takes 8 cells on 32,768 cells or more, else one), flux block size
+ * (64, 128, 256; second order on at most 21,845 faces has one shape of its own)}.  Every shape
+ * gives bit-identical results.  Defaults: {256, 1, 4, 128}. */
 int32_t ugkwp_set_launch(ugkwp_ctx *ctx, const int32_t *cfg);
 int32_t ugkwp_get_launch(const ugkwp_ctx *ctx, int32_t *cfg);
 
@@ -294,8 +295,9 @@ int32_t ugkwp_autotune(ugkwp_ctx *ctx, int32_t steps_per_trial, int32_t *cfg_out
 
 /* The autotuner with a result cache, for callers that run the same workload again.  The cache
  * is a text file of JSON lines {"key": "<workload signature>", "launch": [a, b, c, d]}; the
- * signature names the device architecture, the precision, K, the instance count, the cells,
- * faces and capacity, and every instance's reconstruction, sampling mode and collision model.
+ * signature names the device architecture, the kernels that the shapes belong to, the
+ * precision, K, the instance count, the cells, faces and capacity, and every instance's
+ * reconstruction, sampling mode and collision model.
  * A hit (the last line with the signature, its shapes in range) sets those shapes with no trial
  * step: the state does not advance.  A miss runs ugkwp_autotune (the state advances as there)
  * and appends its result.  cache_path must name a readable and appendable file (created if
@@ -307,8 +309,10 @@ int32_t ugkwp_autotune_cached(ugkwp_ctx *ctx, int32_t steps_per_trial, const cha
 /* Measurement support.  While enabled, each group of kernel launches of ugkwp_step is
  * bracketed by hip events recorded on the library's stream.  ugkwp_profile_read waits for
  * the stream, writes the summed elapsed milliseconds and the number of timed groups for the
- * first n_slots slots (see ugkwp_profile_slot_name; slot 5 is the free transport, slots 6
- * and 7 time no kernels and keep their numbers), and clears the sums.  Either output pointer may be NULL. */
+ * first n_slots slots (see ugkwp_profile_slot_name), and clears the sums.  Slot 5, "stream", is
+ * the free transport with the flights that meet walls and the bucket counts; slots 6 and 7,
+ * "stream_wall" and "count", have no kernels of their own: they keep their numbers and read 0.
+ * Either output pointer may be NULL. */
 int32_t ugkwp_profile_enable(ugkwp_ctx *ctx, int32_t on);
 int32_t ugkwp_profile_read(ugkwp_ctx *ctx, int32_t n_slots, double *total_ms, int64_t *launches);
 /* Record only the slots whose bit is set in mask (default: all); fewer events, less overhead. */

@@ -490,8 +490,6 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
         D.gp_any = D.gp_any || p[k].sampling >= 2;
         D.sh_any = D.sh_any || prandtl_of(p[k]) != 1.0;
     }
-    D.any_diffuse = 0;
-    for (const auto &bc : ctx->H.bcs) D.any_diffuse |= bc.type == 1 ? 1 : 0;
     D.all_box = D.nfar != nullptr ? 1 : 0;
     D.all_tet = 1;
     for (uint8_t t : H.ctype) D.all_tet = D.all_tet && t == 4;
@@ -525,7 +523,6 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
         q.c2 = p[k].c2;
         q.n_ref = p[k].n_ref;
         q.n_min = p[k].n_min;
-        q.long_cells = ugkwp::long_cells(r.cell1 - r.cell0, std::max(q.n_ref, q.n_min)) ? 1 : 0;
         q.max_cross = p[k].max_crossings;
         q.recon = p[k].recon;
         q.venkat_k = p[k].venkat_k;

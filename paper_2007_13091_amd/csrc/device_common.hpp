@@ -54,7 +54,6 @@ struct InstP {
     int32_t gks_steps;     // steps n < gks_steps of the instance are wave-only (no particles)
     long long bf0;         // its first input boundary face in the concatenated list
     double pr;             // Prandtl number: 1 the BGK model, otherwise the Shakhov model
-    int32_t long_cells;    // cells of many particles are shared by a block's waves (k_stream_long)
 };
 
 constexpr int kDtSlots = 8;  // words for the minimum of Omega / Lambda of an instance of many blocks
@@ -177,9 +176,8 @@ struct Dev {
     int32_t all_tet;        // every cell is a tetrahedron
     int32_t list_sparse;    // the kernels over the cells' lists take more cells per wave
     int32_t list_split;     // rows of waves over the lists (more than one if a few cells hold long lists)
-    int32_t long_any;       // some instance has long_cells
+    int32_t long_any;       // in some instance a block's waves share the cells of many particles
     int32_t recon_any, recon_all;  // some / every instance reconstructs to second order
-    int32_t any_diffuse;           // the mesh has a diffuse wall (the wall kernel runs)
     const InstP *ip;        // [n_inst]
     InstS *is;              // [n_inst]
     const int32_t *cinst;   // [nc] instance of each cell (n_inst > 1 only)

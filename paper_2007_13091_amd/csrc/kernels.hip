@@ -1431,25 +1431,20 @@ __device__ __forceinline__ R internal_energy(uint64_t seed, uint64_t uid, long l
 }
 __device__ __forceinline__ void store_e(const Particles &pa, long long i, double e) { pa.e64[i] = e; }
 __device__ __forceinline__ void store_e(const Particles &pa, long long i, float e) { pa.e32[i] = e; }
-__device__ __forceinline__ double load_e(const Particles &pa, long long i, double) { return pa.e64[i]; }
-__device__ __forceinline__ float load_e(const Particles &pa, long long i, float) { return pa.e32[i]; }
 
 // Shakhov model: raw moments sum m u_i |u|^2 and sum m u_i u_j of a cell's particles, from which
 // the cell's heat flux q = (1/Omega) sum m c |c|^2 / 2 with c = u - U follows by expanding c
-template <bool SH>
 __device__ __forceinline__ void add_heat(double m, double u0, double u1, double u2, double H[9]) {
-    if constexpr (SH) {
-        const double w = m * (u0 * u0 + u1 * u1 + u2 * u2);
-        H[0] += w * u0;
-        H[1] += w * u1;
-        H[2] += w * u2;
-        H[3] += m * u0 * u0;
-        H[4] += m * u0 * u1;
-        H[5] += m * u0 * u2;
-        H[6] += m * u1 * u1;
-        H[7] += m * u1 * u2;
-        H[8] += m * u2 * u2;
-    }
+    const double w = m * (u0 * u0 + u1 * u1 + u2 * u2);
+    H[0] += w * u0;
+    H[1] += w * u1;
+    H[2] += w * u2;
+    H[3] += m * u0 * u0;
+    H[4] += m * u0 * u1;
+    H[5] += m * u0 * u2;
+    H[6] += m * u1 * u1;
+    H[7] += m * u1 * u2;
+    H[8] += m * u2 * u2;
 }
 // q of one cell from its survivors' raw moments H (summed as above, then over the wave), its
 // P^{n+1} and W^{n+1}: lane i < 3 returns component i,
@@ -1515,7 +1510,7 @@ __global__ void __launch_bounds__(256) k_heat(Dev D, int buf) {
         for (int k = lane; k < n; k += kWave) {
             double u[3], m;
             load_um(pa, k < nm ? slot_of(D, buf, span, m0 + k) : v0 + (k - nm), u, m, R(0));
-            add_heat<true>(m, u[0], u[1], u[2], H);
+            add_heat(m, u[0], u[1], u[2], H);
         }
 #pragma unroll
         for (int k = 0; k < 9; ++k) H[k] = wave_sum(H[k]);
@@ -2516,36 +2511,13 @@ __device__ int track(const Dev &D, R x[3], R u[3], int &cell, R &ts, int &entry,
     }
 }
 
-// load / store of the transported state of particle i: position and velocity change in
-// place, mass and id (the last 16 bytes of an FP64 record, the last 8 of an FP32 one) are
-// read for the id and never rewritten
-__device__ __forceinline__ void load_state(const Particles &pa, long long i, double x[3], double u[3], uint64_t &uid) {
-    const double2 *rp = reinterpret_cast<const double2 *>(pa.rec + i);
-    const double2 r0 = rp[0], r1 = rp[1], r2 = rp[2];
-    uid = (uint64_t)__double_as_longlong(reinterpret_cast<const double *>(rp + 3)[1]);
-    x[0] = r0.x;
-    x[1] = r0.y;
-    x[2] = r1.x;
-    u[0] = r1.y;
-    u[1] = r2.x;
-    u[2] = r2.y;
-}
+// store of the transported state of particle i: position and velocity; mass and id (the last 16 bytes
+// of an FP64 record, the last 8 of an FP32 one) stay
 __device__ __forceinline__ void store_state(const Particles &pa, long long i, const double x[3], const double u[3]) {
     double2 *rp = reinterpret_cast<double2 *>(pa.rec + i);
     rp[0] = make_double2(x[0], x[1]);
     rp[1] = make_double2(x[2], u[0]);
     rp[2] = make_double2(u[1], u[2]);
-}
-__device__ __forceinline__ void load_state(const Particles &pa, long long i, float x[3], float u[3], uint64_t &uid) {
-    const float4 *rp = reinterpret_cast<const float4 *>(pa.rec32 + i);
-    const float4 a = rp[0], b = rp[1];
-    x[0] = a.x;
-    x[1] = a.y;
-    x[2] = a.z;
-    u[0] = a.w;
-    u[1] = b.x;
-    u[2] = b.y;
-    uid = (uint64_t)__float_as_uint(b.z) | ((uint64_t)__float_as_uint(b.w) << 32);
 }
 __device__ __forceinline__ void store_state(const Particles &pa, long long i, const float x[3], const float u[3]) {
     float4 *rp = reinterpret_cast<float4 *>(pa.rec32 + i);
@@ -2698,6 +2670,10 @@ __device__ __forceinline__ void block_counts(const Dev &D, unsigned long long nx
 // 1.157 (0.845 and 0.827); eight waves took 0.722 (0.525) there, most of them idle in the last round.
 constexpr int kLongRef = 640, kLongCell = 512, kLongWaves = 4;
 constexpr long long kLongCells = 512;
+__host__ __device__ constexpr bool long_rule(long long cells, long long per_cell) {
+    return per_cell >= kLongRef && cells <= kLongCells;
+}
+__device__ __forceinline__ bool long_instance(const InstP &P) { return long_rule(P.cell1 - P.cell0, max(P.n_ref, P.n_min)); }
 template <int W>
 struct LongShared {
     int2 cnt[2][W];       // stayers and listed particles of the waves' runs, two rounds
@@ -2722,7 +2698,7 @@ __device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w,
     const int n = nold + ns;
     if (D.long_any || W > 1) {
         // (no list of these cells: a store before the loads below would take them off the scalar unit)
-        const bool many = n > kLongCell && D.ip[MULTI ? D.cinst[c] : 0].long_cells;
+        const bool many = n > kLongCell && long_instance(D.ip[MULTI ? D.cinst[c] : 0]);
         if (many != (W > 1)) return;
     }
     const int v0 = hi32(o0) + (int)so;  // this cell's region of the next buffer
@@ -2961,12 +2937,17 @@ struct Runs {
         return l;
     }
 };
-// Cells per wave of the kernels over the lists and buckets (host: list_cells).  A list holds
-// some 15% of a box cell's particles and some 30% of a tetrahedron's, so with tens of particles
-// per cell eight lists fill the lanes that one leaves idle (tetrahedra, N_ref 50: 178 against
-// 742 us in k_track, 106 against 291 us in the gather), while with hundreds two lists are
-// enough and eight leave too few waves (box cells, N_ref 400: 216 against 261 us).  A small mesh
-// has few waves anyway and takes two.
+// Cells per wave of the kernels over the lists and buckets: eight where Dev::list_sparse says so (16,384
+// cells or more of fewer than 320 particles each), else two.  A list holds some 15% of a box
+// cell's particles and some 30% of a tetrahedron's, so with tens of particles per cell eight
+// lists fill the lanes that one leaves idle (tetrahedra, N_ref 50: 178 against 742 us in k_track,
+// 106 against 291 us in the gather), while with hundreds two lists are enough and eight leave
+// too few waves (box cells, N_ref 400: 216 against 261 us).  A small mesh has few waves anyway.
+// Around the limits, microseconds a step with two and with eight, FP64 (FP32):
+//   cells, N_ref 50    4,096: 98, 102 (88, 91)       13,824: 172, 160 (146, 139)   19,683: 213, 192 (182, 165)
+//   cells, N_ref 150   13,824: 212, 218 (168, 177)   19,683: 272, 272 (213, 216)   32,768: 321, 318 (244, 239)
+//   N_ref, 32,768 cells    300: 522, 521 (384, 385)      350: 580, 591 (429, 426)      400: 637, 658 (468, 474)
+//   tetrahedra, N_ref 150  13,182: 207, 209 (168, 174)   16,464: 244, 243 (193, 196)   34,992: 345, 328 (261, 258)
 constexpr int kListCellsSparse = 8, kListCellsDense = 2;
 
 // S5: the flights that meet a face: the moved state goes back to the particle's slot, its end
@@ -3347,7 +3328,7 @@ __device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
                     for (int k = 0; k < 5; ++k) to[k * nc + c] = part == 0 ? pv[k] + acc[k] : pv[k] - acc[k];
                 }
                 wave_sync();
-            } else if (nr > kGatherLds && D.long_any && D.ip[inst_of(D, c0 + g)].long_cells) {
+            } else if (nr > kGatherLds && D.long_any && long_instance(D.ip[inst_of(D, c0 + g)])) {
                 // k_gather_long's
             } else if (nr > 0) {
                 // one bucket of more than 64
@@ -3413,7 +3394,7 @@ __global__ void __launch_bounds__(kSortWaves * kWave) k_gather_long(Dev D, int b
     __shared__ double sum[kSortWaves][5];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
     const int c = (int)blockIdx.x, nc = D.nc;
-    if (D.sc->none || !D.ip[inst_of(D, c)].long_cells) return;
+    if (D.sc->none || !long_instance(D.ip[inst_of(D, c)])) return;
     const Particles src = D.pa[buf], dst = D.pa[buf ^ 1];
     const long long span = D.sc->span[buf ^ 1];
     for (int part = 0; part < 2; ++part) {
@@ -3919,7 +3900,7 @@ void count_new(const Dev &D, int buf, hipStream_t s, Prof *pr) {
 
 }  // namespace
 
-bool long_cells(long long cells, long long per_cell) { return per_cell >= kLongRef && cells <= kLongCells; }
+bool long_cells(long long cells, long long per_cell) { return long_rule(cells, per_cell); }
 int list_split(long long nc, bool sparse, long long per_cell) {
     // some 30% of a cell's particles meet a face; 4,096 waves fill the chip (64 boxes of 10,000
     // particles: k_track 326 us with one row, 26 with 94, k_scatter 51 and 11)
@@ -4052,7 +4033,7 @@ void launch_sample_g(const Dev &D, int buf, int w, hipStream_t s) {
         k_sample<R, 4, KE, G><<<g, 256, 0, s>>>(D, buf);
 }
 
-// the cells of at most 64 new particles, then those with more
+// the cells of at most 64 new pairs, then those with more
 template <typename R, bool KE>
 void launch_sample_k(const Dev &D, int buf, int w, hipStream_t s) {
     if (D.nc >= kSampleCellsMin)
@@ -4203,7 +4184,7 @@ void launch_step(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Pro
 
 // A wave-only step when no particle exists: no particle is sampled or let in (e = 0 in the
 // wave-only phase), so the particle kernels would find nothing to do; the bucket counts (zeroed
-// by k_prim_dt) are still scanned so that the offsets are those of empty cells.
+// by k_cell_prep) are still scanned so that the offsets are those of empty cells.
 void launch_step_wave_only(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s, Prof *pr) {
     const int nc = D.nc, nf = D.nf;
     const unsigned gc = (unsigned)((nc + 255) / 256);

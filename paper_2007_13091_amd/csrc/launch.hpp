@@ -23,12 +23,12 @@ enum ProfSlot : int {
     kSlotScan,          // k_offsets
     kSlotFlux,          // k_flux
     kSlotSample,        // k_sample
-    kSlotStream,        // k_stream, k_stream_in, k_track
+    kSlotStream,        // k_stream, k_stream_long, k_stream_in, k_track
     kSlotStreamWall,    // (no kernels: k_track re-emits at walls)
     kSlotCount,         // (no kernels: k_track counts)
     kSlotScan2,         // scan of the bucket counts
     kSlotScatter,       // k_scatter
-    kSlotGather,        // k_gather, k_update
+    kSlotGather,        // k_gather, k_gather_long, k_update, k_heat
     kSlotFinal,         // (the averaging kernels when averaging is on)
     kNumSlots
 };
@@ -42,8 +42,8 @@ struct Prof {
 struct LaunchCfg {
     int stream_bs = 256;  // k_stream block size: 128, 256 or 512 (a wave per cell)
     int stream_ilp = 1;   // k_stream runs of 64 particles loaded together: 1 or 2
-    int sample_wpb = 4;   // k_sample waves (cells) per block: 1, 2, 4 or 8
-    int flux_bs = 128;    // k_flux block size: 64, 128 or 256
+    int sample_wpb = 4;   // k_sample waves per block: 1, 2, 4 or 8
+    int flux_bs = 128;    // k_flux and k_flux2 block size: 64, 128 or 256 (k_flux2_axes has one shape)
 };
 bool launch_cfg_valid(const LaunchCfg &c);
 

@@ -106,10 +106,17 @@ def kernel_names(rtype, cfg, multi, ke=False, sparse=False):
             "gather": f"k_gather{'_sparse' if sparse else ''}<{rtype}, 1, {'true' if ke else 'false'}>"}
 
 
+def track_name(rtype, sparse=False):
+    """The kernel that follows the flights that meet a face, timed with the transport (box meshes,
+    no internal degrees of freedom)."""
+    return f"k_track<{rtype}, false, 1, {8 if sparse else 2}>"
+
+
 def timed_steps(s, steps):
     """K steps, eager launches, bracketed by device synchronisation, with hip events on the
-    library's stream around the two particle kernels (transport and gather) in every step.
-    Returns wall seconds, particle moves, the two kernels' average launch times (ms) and the
+    library's stream around the two groups of particle kernels (transport: k_stream and k_track;
+    gather: k_gather and k_update) in every step.
+    Returns wall seconds, particle moves, the two groups' average times (ms) and the
     statistics before and after."""
     import torch
 
@@ -155,12 +162,16 @@ def _rate(nbytes, ms):
     return {"achieved": round(ach, 1), "frac": round(ach / HBM_PEAK_GBS, 4)}
 
 
-def charge_transport_alone(kr, rtype, moves, survivors):
+def charge_transport_alone(kr, rtype, moves, survivors, track=None, workload=None):
     """The transport reads every particle and writes the survivors, most of them at once to where
     the next step reads them; the gather moves only arrivals and collided particles, whose number
     the statistics do not hold: a rate from all survivors would not be one of bytes that it moves.
-    Its time stays; the particles are charged to the transport."""
+    Its time stays; the particles are charged to the transport.  track: the name of the kernel
+    timed with it, whose measured traffic belongs to the group's."""
     n = transport_bytes(rtype, moves, survivors)
+    if track:
+        t = [kr["stream"]["traffic"], measured_traffic(track, workload)]
+        kr["stream"].update(kernel=kr["stream"]["kernel"] + " + " + track, traffic=None if None in t else sum(t))
     kr["stream"].update(_rate(n, kr["stream"]["kernel_avg_ms"]), algorithmic_bytes_per_launch=int(n))
     kr["gather"].update(achieved=None, frac=None, algorithmic_bytes_per_launch=None)
     return kr
@@ -275,7 +286,7 @@ def batched_run(steps, warmup, start, sampling, cpu_sample_moves=0):
     names = kernel_names("float", cfg, True, sparse=True)
     workload = "batch64"
     dom, kr = kernel_roofline(kms, moves / steps, st1, "float", names, workload)
-    charge_transport_alone(kr, "float", moves / steps, st1["n_alive"])
+    charge_transport_alone(kr, "float", moves / steps, st1["n_alive"], track_name("float", sparse=True), workload)
     faces = sum((6 * w.mesh.n_cells + int(w.mesh.bface_nodes.shape[0])) // 2 for w in ws)
     flux_ms = fl[0] / max(fl[1], 1)
     flux_name = f"k_flux<float, {cfg[3]}>"
@@ -379,7 +390,7 @@ def cavity_leg(precision, steps, warmup, start, sampling=0, recon=2, prandtl=1.0
     names = kernel_names(rtype, cfg, False)
     workload = f"cavity32_recon{recon}" + ("_gp" if sampling == 2 else "") + ("_shakhov" if prandtl != 1.0 else "")
     dom, kr = kernel_roofline(kms, moves / steps, st1, rtype, names, workload)
-    charge_transport_alone(kr, rtype, moves / steps, st1["n_alive"])
+    charge_transport_alone(kr, rtype, moves / steps, st1["n_alive"], track_name(rtype), workload)
     ms = el / steps * 1e3
     s.close()
     del s

@@ -34,3 +34,17 @@ def test_a_dropped_particle_is_read_and_not_written(rtype, rec):
     assert kr["gather"]["achieved"] is None and kr["gather"]["kernel_avg_ms"] == 0.01
     ws = b.whole_step(1.0, moves, 1000, rtype, survivors=alive)
     assert ws["algorithmic_bytes_per_step"] == n + 1000 * b.BYTES_PER_CELL[("hex", rtype, 0)]
+
+
+def test_measured_traffic_is_that_of_the_timed_group(monkeypatch):
+    b = _bench()
+    held = {"k_stream<float, 256, true, 1>": 5, "k_track<float, false, 1, 8>": 7}
+    monkeypatch.setattr(b, "measured_traffic", lambda k, w: held.get(k) if w == "here" else None)
+    names = {"stream": "k_stream<float, 256, true, 1>", "gather": "k_gather"}
+    for workload, want in (("here", 12), ("elsewhere", None)):
+        _, kr = b.kernel_roofline({"stream": 1.0, "gather": 1.0}, 10, {"n_alive": 9, "n_collided": 1}, "float", names, workload)
+        kr = b.charge_transport_alone(kr, "float", 10, 9, b.track_name("float", sparse=True), workload)
+        assert kr["stream"]["traffic"] == want and kr["stream"]["kernel"].endswith("+ k_track<float, false, 1, 8>")
+    src = open(os.path.join(ROOT, "paper_2007_13091_amd", "csrc", "kernels.hip")).read()
+    assert "kListCellsSparse = 8, kListCellsDense = 2" in src
+    assert "k_track<R, KE, MESH, kListCellsSparse><<<" in src

@@ -977,14 +977,22 @@ __device__ void flux2_pair(const Side2<R> &L, const Side2<R> &Rs, R dt, R mu_ref
 // (roundoff of an empty hydro part, which the limiter can pin to a neighbour's zero).
 // Bound by the latency of dependent loads and by its FP64 divisions (two a face and component in
 // the limiter), not by its bytes.  Five waves have 64 cells, each one component of W and of the hydro
-// state; the values and gradients meet in local memory for the face states, a face a wave.  One
-// thread per cell held ten components and their gradients in registers, one wave per SIMD:
-// 32,768 cells 30 us, now 19.5; the 2,709 cells of a 301 x 3 x 3 tube 26 us, now 12.7.  Ten waves of one component each:
-// 32 and 11.3 us, the neighbours' centres and densities read twice as often.
+// state; what is a face's (the centres, the neighbour's hydro part, a ghost's state) a wave forms for
+// one face and leaves in local memory for all, as the gradients for the face states.  With a thread
+// per cell (ten components and their gradients in registers, one wave per SIMD) 32,768 boxes took
+// 28.7 us, now 17.7; the 2,709 of a 301 x 3 x 3 tube 26 and 12.6; 262,144 boxes 120 and 109;
+// 34,992 tetrahedra 27.7 and 20; 511,104 tetrahedra, which fill the chip either way, 180 and 184 (208
+// when every wave formed every face's data).  Ten waves of one component each: 32 us on 32,768 boxes.
 constexpr int kGradCells = kWave;
 
+// NF: the faces of a cell at most (4: every cell a tetrahedron).
+template <int NF>
 __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
-    __shared__ double sv[10][4][kGradCells];  // cell value and limited gradient by component (W, hydro)
+    __shared__ double sv[10][3][kGradCells];  // limited gradient by component (W, hydro)
+    // by face: the neighbour's centre and the face's centre from the cell's, the neighbour's rho^h / rho
+    // (a ghost: its state)
+    __shared__ double sf[NF][11][kGradCells];
+    __shared__ double se[kGradCells];  // eps^2
     __shared__ int sok[kGradCells];
     const int cl = lane_id(), kk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int nc = D.nc, c0 = blockIdx.x * kGradCells + cl;
@@ -996,6 +1004,13 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
     const int nfc = D.nfc[c];
     const double *lfx = D.lfx + (long long)c * 18;
     double Wc[5], g[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+    int nb[NF];
+    double vj[NF][2];
+    // every neighbour's load before the first use
+#pragma unroll
+    for (int lf = 0; lf < NF; ++lf) nb[lf] = lf < nfc ? D.nbl[c * 6 + lf].x : c;
+#pragma unroll
+    for (int lf = 0; lf < NF; ++lf) vj[lf][0] = D.W[kk * nc + (nb[lf] >= 0 ? nb[lf] : c)];
 #pragma unroll
     for (int i = 0; i < 5; ++i) Wc[i] = D.W[i * nc + c];
     const double fc = D.rhoh[c] / Wc[0];
@@ -1007,36 +1022,29 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
     double vc[2];
     vc[0] = comp(Wc);
     vc[1] = fc * vc[0];
-    if (live) {
-        int nb[6];
-        double xj[6][3], vj[6][2];
+    // the faces' data: a face a wave, the last of six to the first wave
+    for (int lf = kk; lf < nfc && live; lf += 5) {
+        const int j = D.nbl[c * 6 + lf].x;
+        double xj[3];
+        if (j >= 0) {
 #pragma unroll
-        for (int lf = 0; lf < 6; ++lf) nb[lf] = lf < nfc ? D.nbl[c * 6 + lf].x : c;
-        // every neighbour's loads before the first use
-#pragma unroll
-        for (int lf = 0; lf < 6; ++lf) {
-            const int j = nb[lf] >= 0 ? nb[lf] : c;
-            vj[lf][0] = D.W[kk * nc + j];
-            vj[lf][1] = D.rhoh[j] / D.W[j] * vj[lf][0];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xj[lf][d] = D.xc[d * nc + j];
-        }
-#pragma unroll
-        for (int lf = 0; lf < 6; ++lf) {
-            if (nb[lf] >= 0) continue;
+            for (int d = 0; d < 3; ++d) xj[d] = D.xc[d * nc + j];
+            sf[lf][6][cl] = D.rhoh[j] / D.W[j];
+        } else {
             const double4 pl = D.plane[c * 6 + lf];
             const double nn[3] = {pl.x, pl.y, pl.z};
             const double dist = pl.w - (nn[0] * xc[0] + nn[1] * xc[1] + nn[2] * xc[2]);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) xj[lf][d] = xc[d] + 2.0 * dist * nn[d];
-            const DevBC &b = D.bc[-1 - nb[lf]];
+            for (int d = 0; d < 3; ++d) xj[d] = xc[d] + 2.0 * dist * nn[d];
+            const DevBC &b = D.bc[-1 - j];
             if (b.type == 2) {
-                vj[lf][0] = vj[lf][1] = b.Winf[kk];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) sf[lf][6 + i][cl] = b.Winf[i];
             } else {
                 const double rho = Wc[0];
                 const double U[3] = {Wc[1] / rho, Wc[2] / rho, Wc[3] / rho};
                 const double T = temp_k(Wc, D.K);
-                double Ug[3], vg[5];
+                double Ug[3];
                 if (b.type == 0) {
                     const double un = U[0] * nn[0] + U[1] * nn[1] + U[2] * nn[2];
 #pragma unroll
@@ -1045,20 +1053,41 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
 #pragma unroll
                     for (int d = 0; d < 3; ++d) Ug[d] = 2.0 * b.Uw[d] - U[d];
                 }
-                vg[0] = rho;
+                sf[lf][6][cl] = rho;
 #pragma unroll
-                for (int d = 0; d < 3; ++d) vg[1 + d] = rho * Ug[d];
-                vg[4] = 0.5 * rho * (Ug[0] * Ug[0] + Ug[1] * Ug[1] + Ug[2] * Ug[2]) + 0.5 * (3.0 + D.K) * rho * T;
-                vj[lf][0] = comp(vg);
-                vj[lf][1] = fc * vj[lf][0];
+                for (int d = 0; d < 3; ++d) sf[lf][7 + d][cl] = rho * Ug[d];
+                sf[lf][10][cl] =
+                    0.5 * rho * (Ug[0] * Ug[0] + Ug[1] * Ug[1] + Ug[2] * Ug[2]) + 0.5 * (3.0 + D.K) * rho * T;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            sf[lf][d][cl] = xj[d] - xc[d];
+            sf[lf][3 + d][cl] = lfx[3 * lf + d] - xc[d];
+        }
+    }
+    if (kk == 4 && live && P.recon != 1) {
+        const double kh = P.venkat_k * cbrt(D.vol[c]);
+        se[cl] = kh * kh * kh;
+    }
+    __syncthreads();
+    if (live) {
+#pragma unroll
+        for (int lf = 0; lf < NF; ++lf) {
+            if (lf >= nfc) break;
+            if (nb[lf] >= 0) {
+                vj[lf][1] = sf[lf][6][cl] * vj[lf][0];
+            } else {
+                vj[lf][0] = sf[lf][6 + kk][cl];
+                vj[lf][1] = D.bc[-1 - nb[lf]].type == 2 ? vj[lf][0] : fc * vj[lf][0];
             }
         }
         double A00 = 0, A01 = 0, A02 = 0, A11 = 0, A12 = 0, A22 = 0;
         double r[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, vmax[2] = {vc[0], vc[1]}, vmin[2] = {vc[0], vc[1]};
 #pragma unroll
-        for (int lf = 0; lf < 6; ++lf) {
+        for (int lf = 0; lf < NF; ++lf) {
             if (lf >= nfc) break;
-            const double dx[3] = {xj[lf][0] - xc[0], xj[lf][1] - xc[1], xj[lf][2] - xc[2]};
+            const double dx[3] = {sf[lf][0][cl], sf[lf][1][cl], sf[lf][2][cl]};
             A00 += dx[0] * dx[0];
             A01 += dx[0] * dx[1];
             A02 += dx[0] * dx[2];
@@ -1079,8 +1108,7 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
         const double C00 = A11 * A22 - A12 * A12, C01 = A02 * A12 - A01 * A22, C02 = A01 * A12 - A02 * A11;
         const double C11 = A00 * A22 - A02 * A02, C12 = A02 * A01 - A00 * A12, C22 = A00 * A11 - A01 * A01;
         const double det = A00 * C00 + A01 * C01 + A02 * C02;
-        const double kh = P.venkat_k * cbrt(D.vol[c]);
-        const double eps2 = kh * kh * kh;
+        const double eps2 = P.recon != 1 ? se[cl] : 0.0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             g[h][0] = (C00 * r[h][0] + C01 * r[h][1] + C02 * r[h][2]) / det;
@@ -1089,7 +1117,7 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
         }
         double phi[2] = {1.0, 1.0};
         for (int lf = 0; lf < nfc; ++lf) {
-            const double dx[3] = {lfx[3 * lf] - xc[0], lfx[3 * lf + 1] - xc[1], lfx[3 * lf + 2] - xc[2]};
+            const double dx[3] = {sf[lf][3][cl], sf[lf][4][cl], sf[lf][5][cl]};
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const double Dk = g[h][0] * dx[0] + g[h][1] * dx[1] + g[h][2] * dx[2];
@@ -1111,19 +1139,17 @@ __global__ void __launch_bounds__(5 * kGradCells) k_grad(Dev D) {
             for (int d = 0; d < 3; ++d) g[h][d] *= phi[h];
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        sv[5 * h + kk][0][cl] = vc[h];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) sv[5 * h + kk][1 + d][cl] = g[h][d];
-    }
+        for (int d = 0; d < 3; ++d) sv[5 * h + kk][d][cl] = g[h][d];
     __syncthreads();
     // the states extrapolated to the faces: one face a wave, the last of six to the first wave
     for (int lf = kk; lf < nfc && live; lf += 5) {
-        const double dx[3] = {lfx[3 * lf] - xc[0], lfx[3 * lf + 1] - xc[1], lfx[3 * lf + 2] - xc[2]};
+        const double dx[3] = {sf[lf][3][cl], sf[lf][4][cl], sf[lf][5][cl]};
         double wf[10];
 #pragma unroll
         for (int i = 0; i < 10; ++i)
-            wf[i] = sv[i][0][cl] + sv[i][1][cl] * dx[0] + sv[i][2][cl] * dx[1] + sv[i][3][cl] * dx[2];
+            wf[i] = (i < 5 ? Wc[i] : fc * Wc[i - 5]) + sv[i][0][cl] * dx[0] + sv[i][1][cl] * dx[1] + sv[i][2][cl] * dx[2];
         bool ok = wf[0] > 0.0 && temp_k(wf, D.K) > 0.0 && wf[5] >= -1e-12 * wf[0];
         if (wf[5] > 1e-12 * wf[0] && !(temp_k(wf + 5, D.K) > 0.0)) ok = false;
         if (!ok) atomicAnd(&sok[cl], 0);
@@ -1163,7 +1189,23 @@ struct Face2 {
     Side2<R> L, Rs;
     double Whl0, Wl0;
 };
+// the outer side's derivatives at a boundary (specular walls mirror the inner ones: along n and the
+// normal momentum flip; the free stream has none)
 template <typename R>
+__device__ __forceinline__ void mirror_derivs(Face2<R> &F) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const R sg = ((d == 0) != (k == 1)) ? (R)-1 : (R)1;
+            F.Rs.dW[d][k] = F.type == 0 ? sg * F.L.dW[d][k] : (R)0;
+            F.Rs.dWh[d][k] = F.type == 0 ? sg * F.L.dWh[d][k] : (R)0;
+        }
+}
+// DERIVS: with both sides' derivatives, each side's loaded with its state.  A thread that has a face
+// to itself runs at one wave per SIMD, where a second round of loads after the states is not hidden:
+// 101,376 faces FP64 53 us with it, 47 without; 1,033,824 faces of tetrahedra 509 and 421.
+template <typename R, bool DERIVS>
 __device__ __forceinline__ bool open_face(const Dev &D, int f, Face2<R> &F) {
     const int nf = D.nf;
     F.f = f;
@@ -1187,10 +1229,12 @@ __device__ __forceinline__ bool open_face(const Dev &D, int f, Face2<R> &F) {
         w0 = W[0];
         wh0 = Wh[0];
         S.g = to_frame<R>(W, F.n, F.t1, F.t2, D.K);
+        if (DERIVS) frame_derivs<R>(D.gW, D.nc, c, F.n, F.t1, F.t2, S.dW);
         // a face hydro density at or below 1e-12 of the face density is roundoff of an empty hydro
         // part (the limiter can pin it exactly to a neighbour's zero): no hydro wave on that side
         if (Wh[0] > 1e-12 * W[0]) {
             S.h = to_frame<R>(Wh, F.n, F.t1, F.t2, D.K);
+            if (DERIVS) frame_derivs<R>(D.gH, D.nc, c, F.n, F.t1, F.t2, S.dWh);
         } else {
             S.h.rho = (R)0;
             S.h.K = D.K;
@@ -1209,10 +1253,10 @@ __device__ __forceinline__ bool open_face(const Dev &D, int f, Face2<R> &F) {
         F.Rs.g = to_frame<R>(D.bc[-1 - F.nb].Winf, F.n, F.t1, F.t2, D.K);
         F.Rs.h = F.Rs.g;
     }
+    if (DERIVS && F.nb < 0) mirror_derivs<R>(F);
     return true;
 }
-// both sides' derivatives along the frame's axes (specular walls mirror them: along n and the normal
-// momentum flip; the free stream has none)
+// both sides' derivatives along the frame's axes
 template <typename R>
 __device__ __forceinline__ void face_derivs(const Dev &D, Face2<R> &F) {
     frame_derivs<R>(D.gW, D.nc, F.c, F.n, F.t1, F.t2, F.L.dW);
@@ -1220,16 +1264,9 @@ __device__ __forceinline__ void face_derivs(const Dev &D, Face2<R> &F) {
     if (F.nb >= 0) {
         frame_derivs<R>(D.gW, D.nc, F.nb, F.n, F.t1, F.t2, F.Rs.dW);
         if (F.Rs.h.rho > (R)0) frame_derivs<R>(D.gH, D.nc, F.nb, F.n, F.t1, F.t2, F.Rs.dWh);
-        return;
+    } else {
+        mirror_derivs<R>(F);
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            const R sg = ((d == 0) != (k == 1)) ? (R)-1 : (R)1;
-            F.Rs.dW[d][k] = F.type == 0 ? sg * F.L.dW[d][k] : (R)0;
-            F.Rs.dWh[d][k] = F.type == 0 ? sg * F.L.dWh[d][k] : (R)0;
-        }
 }
 // the face's flux, times its area, oriented owner -> neighbour
 template <typename R>
@@ -1263,11 +1300,10 @@ __global__ void __launch_bounds__(BS) k_flux2(Dev D) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= D.nf) return;
     Face2<R> F;
-    if (!open_face<R>(D, f, F)) return;
+    if (!open_face<R, true>(D, f, F)) return;
     const InstP &P = D.ip[inst_of(D, F.c)];
     R Ff[5];
     if (F.pair) {
-        face_derivs<R>(D, F);
         const R qsh = F.type == 0 ? (R)0 : (R)shakhov_qsh(D, P, f, F.c, F.nb);
         flux2_pair<R>(F.L, F.Rs, F.dt, (R)P.mu_ref, (R)P.omega, (R)P.c2, F.gks, qsh, Ff);
     } else {
@@ -1316,7 +1352,7 @@ __global__ void __launch_bounds__(3 * kWave) k_flux2_axes(Dev D) {
     Prim<R> z;
     Mom3<R> M0;
     AxisPart<R> p;
-    const bool live = f < D.nf && open_face<R>(D, f, F);
+    const bool live = f < D.nf && open_face<R, false>(D, f, F);
     if (live && F.pair) {
         Mom3<R> ML, MR;
         mom3<R>(1, F.L.g, ML);
@@ -4068,7 +4104,11 @@ void launch_flux(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
     if (D.recon_any) {
         // second order: gradients, then the faces of reconstructing instances; the first-order
         // kernel takes the others
-        k_grad<<<(unsigned)((D.nc + kGradCells - 1) / kGradCells), 5 * kGradCells, 0, s>>>(D);
+        const unsigned gg = (unsigned)((D.nc + kGradCells - 1) / kGradCells);
+        if (D.all_tet)
+            k_grad<4><<<gg, 5 * kGradCells, 0, s>>>(D);
+        else
+            k_grad<6><<<gg, 5 * kGradCells, 0, s>>>(D);
         if (nf <= kFluxSplitMax)
             k_flux2_axes<R><<<(unsigned)((nf + kWave - 1) / kWave), 3 * kWave, 0, s>>>(D);
         else if (bs == 64)

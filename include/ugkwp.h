@@ -279,7 +279,7 @@ int32_t ugkwp_graph_enable(ugkwp_ctx *ctx, int32_t on);
 /* Launch shapes of the tunable kernels, cfg[4] = {k_stream block size (128, 256, 512; a
  * wave per cell), k_stream runs of 64 particles loaded together (1, 2), k_sample waves per
  * block (1, 2, 4, 8; a wave takes 8 cells on 32,768 cells or more, else one), flux block size
- * (64, 128, 256; second order on at most 21,845 faces has one shape of its own)}.  Every shape
+ * (64, 128, 256; second order on at most 10,240 faces has one shape of its own)}.  Every shape
  * gives bit-identical results.  Defaults: {256, 1, 4, 128}. */
 int32_t ugkwp_set_launch(ugkwp_ctx *ctx, const int32_t *cfg);
 int32_t ugkwp_get_launch(const ugkwp_ctx *ctx, int32_t *cfg);

@@ -1316,9 +1316,12 @@ __global__ void __launch_bounds__(BS) k_flux2(Dev D) {
 // 7,000 dependent operations, so three waves share 64 faces, one per axis of the face frame.  Each
 // forms the states and the sums of its axis and hands them over in local memory; the second also
 // has the time coefficients, the first joins the axes in the order of flux2_pair (the same bits).
-// 9,331 faces of a 301 x 3 x 3 tube: 21 us against 32; the 101,376 of a 32^3 cavity, which fill
-// the chip anyway: 100 us against 52.  The limit is one round of such waves, one to a SIMD.
-constexpr int kFluxSplitMax = 64 * 1024 / 3;
+// It saves a microsecond or two while a block has a CU to itself and a SIMD to each wave, and costs a
+// second round beyond.  Microseconds for gradients and fluxes with it and without, FP64 (FP32): 3,300
+// faces of boxes 36.2, 37.2 (29.5, 32.7); 9,331 of a 301 x 3 x 3 tube 35.5, 36.0 (30.6, 32.0); 13,056:
+// 35.2, 34.7 (30.0, 31.3), where a step with particles is no longer shorter (140, 140; 127, 125);
+// 18,468: 51.8, 37.4 (38.9, 33.0).
+constexpr int kFluxSplitMax = 10240;
 template <typename R>
 struct AxisPart {
     R T[5], X[5], Y[2][5];

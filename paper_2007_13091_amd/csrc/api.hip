@@ -498,14 +498,10 @@ int32_t ugkwp_init_mesh(ugkwp_ctx **out, const ugkwp_mesh *m, int32_t n_inst, co
         for (int k = 0; k < n_inst; ++k)
             per_cell += (double)(ctx->ranges[k].cell1 - ctx->ranges[k].cell0) * std::max(p[k].n_ref, p[k].n_min);
         D.list_sparse = H.nc >= 16384 && per_cell < 320.0 * (double)H.nc ? 1 : 0;
-        D.long_any = 0;
-        D.list_split = 1;
-        for (int k = 0; k < n_inst; ++k) {
-            const int ref = std::max(p[k].n_ref, p[k].n_min);
-            if (!ugkwp::long_cells(ctx->ranges[k].cell1 - ctx->ranges[k].cell0, ref)) continue;
-            D.long_any = 1;
-            D.list_split = std::max(D.list_split, ugkwp::list_split(H.nc, D.list_sparse != 0, ref));
-        }
+        int most = 0;
+        for (int k = 0; k < n_inst; ++k) most = std::max(most, std::max(p[k].n_ref, p[k].n_min));
+        D.long_from = ugkwp::long_from(H.nc, most);
+        D.list_split = D.long_from == ugkwp::kNoLong ? 1 : ugkwp::list_split(H.nc, D.list_sparse != 0, most);
     }
     D.cap = cap;
     D.prec = p[0].precision;
@@ -1177,7 +1173,7 @@ std::string tune_key(const ugkwp_ctx *ctx) {
     const ugkwp::Dev &D = ctx->D;
     std::string k = arch + " shapes=" + std::to_string(kShapesVersion) +
                     " mesh=" + (D.all_box ? "box" : (D.all_tet ? "tet" : "any")) +
-                    " sparse=" + std::to_string(D.list_sparse) + " long=" + std::to_string(D.long_any) + " prec=" + std::to_string(ctx->D.prec) + " K=" + std::to_string(ctx->D.K) +
+                    " sparse=" + std::to_string(D.list_sparse) + " long=" + std::to_string(D.long_from != ugkwp::kNoLong ? 1 : 0) + " prec=" + std::to_string(ctx->D.prec) + " K=" + std::to_string(ctx->D.K) +
                     " inst=" + std::to_string(ctx->D.n_inst) + " cells=" + std::to_string(ctx->D.nc) +
                     " faces=" + std::to_string(ctx->D.nf) + " cap=" + std::to_string(ctx->D.cap) + " modes=";
     for (const ugkwp_params &p : ctx->ps) {

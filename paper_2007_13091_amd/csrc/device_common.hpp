@@ -56,6 +56,8 @@ struct InstP {
     double pr;             // Prandtl number: 1 the BGK model, otherwise the Shakhov model
 };
 
+constexpr int kNoLong = 0x7FFFFFFF;
+
 constexpr int kDtSlots = 8;  // words for the minimum of Omega / Lambda of an instance of many blocks
 
 // Step state of one instance: its own time step, time and step counter, and the counts of
@@ -176,7 +178,7 @@ struct Dev {
     int32_t all_tet;        // every cell is a tetrahedron
     int32_t list_sparse;    // the kernels over the cells' lists take more cells per wave
     int32_t list_split;     // rows of waves over the lists (more than one if a few cells hold long lists)
-    int32_t long_any;       // in some instance a block's waves share the cells of many particles
+    int32_t long_from;      // a block's waves share the cells of more particles than this (kNoLong: none)
     int32_t recon_any, recon_all;  // some / every instance reconstructs to second order
     const InstP *ip;        // [n_inst]
     InstS *is;              // [n_inst]

@@ -2694,30 +2694,24 @@ __device__ __forceinline__ void block_counts(const Dev &D, unsigned long long nx
 }
 
 // Cells with many particles.  A wave per cell goes through its cell's runs of 64 one after the other, so a few
-// cells of thousands of particles leave the chip idle: in an instance of at most kLongCells cells and
-// kLongRef or more reference particles a cell of more than kLongCell particles is left to
-// k_stream_long.  There the kLongWaves waves of a block take the runs in turn, with the same
-// places for every particle (the runs' counts meet in local memory); the sums are those of the
-// waves in their order.  The rule looks at the instance and the cell alone, so a cell's bits do
-// not depend on the batch around it.
-// 64 boxes of 10,000 particles, FP64: 331 us with a wave per cell, 105 with four (a step, with the
-// lists split as well and k_gather_long, 1.03 ms and 0.30; a thread per particle 0.70).  The
-// limits: 64 boxes of 700 particles 0.116 and 0.090 ms a step, of 500 particles 0.102 with a wave
-// (0.117 a thread per particle); 1,000 boxes of 700 particles are 0.133 ms with a wave per cell
-// and 0.153 with a thread per particle.  A batch of 32 x 512 boxes, whose cells would fill the chip
-// either way: 700 particles 0.604 and 0.601 ms (FP32 0.438 and 0.453), 1,500 particles 1.175 and
-// 1.157 (0.845 and 0.827); eight waves took 0.722 (0.525) there, most of them idle in the last round.
-constexpr int kLongRef = 640, kLongCell = 512, kLongWaves = 4;
-constexpr long long kLongCells = 512;
-__host__ __device__ constexpr bool long_rule(long long cells, long long per_cell) {
-    return per_cell >= kLongRef && cells <= kLongCells;
-}
-__device__ __forceinline__ bool long_instance(const InstP &P) { return long_rule(P.cell1 - P.cell0, max(P.n_ref, P.n_min)); }
+// cells of hundreds of particles leave the chip idle: on a small mesh (long_from) a cell of more than
+// Dev::long_from particles is left to k_stream_long.  There the kLongWaves waves of a block take the
+// runs in turn, with the same places for every particle (the runs' counts meet in local memory).
+// Every run's terms of the sums go through local memory too and are added lane by lane in the
+// order of the runs, as one wave adds them, so the bits do not depend on who takes a cell.
+// 64 boxes of 10,000 particles, FP64: k_stream 331 us by waves, 132 by blocks.  Where the line lies
+// (long_from), microseconds a step of a cavity by waves and by blocks, FP64 (FP32):
+//   64 cells     400 particles: 117, 92 (102, 83)       2,500: 449, 166 (379, 145)
+//   1,000 cells  400: 128, 109 (114, 97)                2,500: 547, 277 (466, 228)
+//   1,728 cells  1,000: 233, 186 (190, 154)             2,500: 597, 405 (506, 319)
+//   4,096 cells  1,000: 344, 335 (268, 257)             8 instances of 512 cells: 385, 387 (293, 297)
+// Beyond, blocks cost up to 6% at 600 particles (8,000 cells FP32).  With fewer particles waves are no slower than
+// a thread per particle was (64 cells of 300: 103 and 115); with 400 and more they were, by up to a third.
+constexpr int kLongCell = 256, kLongWaves = 4;
 template <int W>
 struct LongShared {
-    int2 cnt[2][W];       // stayers and listed particles of the waves' runs, two rounds
-    double sum[W][10];    // P and collided sums of the waves
-    int own[W];
+    int4 cnt[W];                 // stayers, listed and collided particles of the waves' runs
+    double part[W][10][kWave];   // the runs' terms of P and of the collided particles' sums
 };
 
 // One cell's free flight by the W waves of a block (W = 1: by one wave, without a barrier), ILP runs of 64
@@ -2735,11 +2729,8 @@ __device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w,
     const int ns = n_new > 0 ? (int)(D.samoff[c + 1] - so) : 0;
     const int nold = hi32(o1) - hi32(o0), nm = lo32(o1) - lo32(o0);
     const int n = nold + ns;
-    if (D.long_any || W > 1) {
-        // (no list of these cells: a store before the loads below would take them off the scalar unit)
-        const bool many = n > kLongCell && long_instance(D.ip[MULTI ? D.cinst[c] : 0]);
-        if (many != (W > 1)) return;
-    }
+    // (no list of these cells: a store before the loads below would take them off the scalar unit)
+    if ((n > D.long_from) != (W > 1)) return;
     const int v0 = hi32(o0) + (int)so;  // this cell's region of the next buffer
     const int vs = D.v0[buf][c] - nm;   // slot of an old particle k >= nm: vs + k
     // places of its arrivals and of its new particles in the second part of this buffer: am + k
@@ -2767,7 +2758,7 @@ __device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w,
     const unsigned long long below = lane == 0 ? 0ULL : (~0ULL >> (64 - lane));
     double Pn[5] = {0, 0, 0, 0, 0}, Cn[5] = {0, 0, 0, 0, 0};
     int nst = 0, nlv = 0, nco = 0;  // stayers, particles that meet a face, collided here
-    int round = 0;
+    double mine[3] = {0, 0, 0};     // (W > 1) the sums that this wave keeps: w, w + W, ...
     for (int r0 = 0; r0 < n; r0 += W * ILP * kWave) {
         const int k0 = r0 + w * kWave;
         Part<R> q[ILP];
@@ -2822,34 +2813,44 @@ __device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w,
             const bool stay = k < n && !meets && !collided, own = k < n && !meets && collided;
             const unsigned long long ms = __ballot(stay), ml = __ballot(meets), mo = __ballot(own);
             const int cs = (int)__popcll(ms);
-            int ps = nst, pl = nlv, as = cs, al = (int)__popcll(ml);  // first places, and the round's counts
+            const int rs = (int)__popcll(ms & below);
+            double tP[5] = {0, 0, 0, 0, 0}, tC[5] = {0, 0, 0, 0, 0};
+            if (stay) {
+                // the transport's last move of a flight that meets no face
+#pragma unroll
+                for (int d = 0; d < 3; ++d) q[j].x[d] = q[j].x[d] + q[j].u[d] * dt;
+                add_phi<R>(W > 1 ? tP : Pn, q[j].m, q[j].u, q[j].e);
+                stage_part(st + rs * CPR, q[j]);
+            }
+            if (mo && own) add_phi<R>(W > 1 ? tC : Cn, q[j].m, q[j].u, q[j].e);
+            int ps = nst, pl = nlv, as = cs, al = (int)__popcll(ml), ao = (int)__popcll(mo);  // first places, the round's counts
             if (W > 1) {
-                int2 *cnt = sh->cnt[round & 1];
-                ++round;
-                if (lane == 0) cnt[w] = make_int2(as, al);
-                __syncthreads();  // (the next but one round writes these again: one barrier a round is enough)
-                as = al = 0;
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    sh->part[w][i][lane] = tP[i];
+                    if (mo) sh->part[w][5 + i][lane] = tC[i];
+                }
+                if (lane == 0) sh->cnt[w] = make_int4(as, al, ao, 0);
+                __syncthreads();
+                as = al = ao = 0;
 #pragma unroll
                 for (int i = 0; i < W; ++i) {
-                    const int2 v = cnt[i];
+                    const int4 v = sh->cnt[i];
                     if (i < w) {
                         ps += v.x;
                         pl += v.y;
                     }
                     as += v.x;
                     al += v.y;
+                    ao += v.z;
+#pragma unroll
+                    for (int h = 0; h < 3; ++h) {
+                        const int t = w + h * W;
+                        if (t < 5 || (t < 10 && v.z)) mine[h] += sh->part[i][t][lane];
+                    }
                 }
             }
-            if (stay) {
-                // the transport's last move of a flight that meets no face
-#pragma unroll
-                for (int d = 0; d < 3; ++d) q[j].x[d] = q[j].x[d] + q[j].u[d] * dt;
-                add_phi<R>(Pn, q[j].m, q[j].u, q[j].e);
-                const int rs = (int)__popcll(ms & below);
-                stage_part(st + rs * CPR, q[j]);
-                store_side<KE>(pb, v0 + ps + rs, q[j]);
-            }
-            if (mo && own) add_phi<R>(Cn, q[j].m, q[j].u, q[j].e);
+            if (stay) store_side<KE>(pb, v0 + ps + rs, q[j]);
             if (meets) {
                 const int li = v0 + pl + (int)__popcll(ml & below);
                 D.lsrc[li] = (uint32_t)slot[j] | (k < nold ? 0u : kNewBit);
@@ -2862,30 +2863,26 @@ __device__ __forceinline__ void stream_cell(const Dev &D, int buf, int c, int w,
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             nst += as;
             nlv += al;
-            nco += (int)__popcll(mo);
+            nco += ao;
+            if (W > 1) __syncthreads();  // (the counts and terms are read before the next round's are written)
+        }
+    }
+    if (W > 1) {
+#pragma unroll
+        for (int h = 0; h < 3; ++h)
+            if (w + h * W < 10) sh->part[0][w + h * W][lane] = mine[h];
+        __syncthreads();
+        if (w != 0) return;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            Pn[i] = sh->part[0][i][lane];
+            Cn[i] = sh->part[0][5 + i][lane];
         }
     }
     // the stayers' part of P^{n+1}; the gather's E - S is P^{n+1} + (collided elsewhere) - S, so
     // what collided here comes off S
     double Pk, Ck;
     wave_sum_pc(Pn, Cn, Pk, Ck);
-    if (W > 1) {
-        if (lane < 5) {
-            sh->sum[w][lane] = Pk;
-            sh->sum[w][5 + lane] = Ck;
-        }
-        if (lane == 0) sh->own[w] = nco;
-        __syncthreads();
-        if (w != 0) return;
-        nco = 0;
-        for (int i = 0; i < W; ++i) nco += sh->own[i];
-        if (lane < 5) {
-            for (int i = 1; i < W; ++i) {
-                Pk += sh->sum[i][lane];
-                Ck += sh->sum[i][5 + lane];
-            }
-        }
-    }
     if (lane < 5) {
         if (nco) D.S[lane * nc + c] = D.S[lane * nc + c] - Ck;
         D.P[lane * nc + c] = Pk;
@@ -3367,7 +3364,7 @@ __device__ __forceinline__ void gather_cells(const Dev &D, int buf) {
                     for (int k = 0; k < 5; ++k) to[k * nc + c] = part == 0 ? pv[k] + acc[k] : pv[k] - acc[k];
                 }
                 wave_sync();
-            } else if (nr > kGatherLds && D.long_any && long_instance(D.ip[inst_of(D, c0 + g)])) {
+            } else if (nr > kGatherLds && D.long_from < kNoLong) {
                 // k_gather_long's
             } else if (nr > 0) {
                 // one bucket of more than 64
@@ -3422,18 +3419,19 @@ __global__ void __launch_bounds__(WPB * 64) k_gather_sparse(Dev D, int buf) {
     gather_cells<R, WPB, KE, kListCellsSparse>(D, buf);
 }
 
-// The buckets of more than kGatherLds entries in the cells whose transport a block may share
-// (k_stream_long): a block each, its waves taking the runs of 64 in turn.  What bounds a wave alone
-// there is the sort (78 passes over 4,096 entries in global memory); here up to kLongSort entries
-// are sorted in local memory.  64 boxes of 10,000 particles: 330 us in k_gather, 33 here.
+// The buckets of more than kGatherLds entries where a block may share a cell's transport (k_stream_long): a
+// block each, its waves taking the runs of 64 in turn, the terms of the sums added lane by lane in
+// the runs' order as one wave adds them.  What bounds a wave alone there is the sort (78 passes
+// over 4,096 entries in global memory); here up to kLongSort entries are sorted in local memory.
+// 64 boxes of 10,000 particles: 330 us in k_gather, 33 here.
 constexpr int kLongSort = 4096, kSortWaves = 8;
 template <typename R, bool KE>
 __global__ void __launch_bounds__(kSortWaves * kWave) k_gather_long(Dev D, int buf) {
     __shared__ unsigned long long lds[kLongSort];
-    __shared__ double sum[kSortWaves][5];
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+    __shared__ double terms[kSortWaves][5][kWave];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
     const int c = (int)blockIdx.x, nc = D.nc;
-    if (D.sc->none || !long_instance(D.ip[inst_of(D, c)])) return;
+    if (D.sc->none) return;
     const Particles src = D.pa[buf], dst = D.pa[buf ^ 1];
     const long long span = D.sc->span[buf ^ 1];
     for (int part = 0; part < 2; ++part) {
@@ -3447,31 +3445,34 @@ __global__ void __launch_bounds__(kSortWaves * kWave) k_gather_long(Dev D, int b
             list = lds;
         }
         sort_list<kSortWaves>(list, nr, (int)threadIdx.x);
-        double acc[5] = {0, 0, 0, 0, 0};
-        for (int k = wave * kWave + lane; k < nr; k += kSortWaves * kWave) {
-            Part<R> A;
-            load_part<KE>(src, (long long)(lo32(list[k]) & ~kHeadBit), A);
-            add_phi<R>(acc, A.m, A.u, A.e);
-            if (part == 0) {
-                const int o = slot_of(D, buf ^ 1, span, first + k);
-                store_side<KE>(dst, o, A);
-                stage_part(rec_chunks(dst, o, R(0)), A);
+        double mine = 0.0;  // the sum that this wave keeps: component w
+        for (int k0 = 0; k0 < nr; k0 += kSortWaves * kWave) {
+            const int k = k0 + w * kWave + lane;
+            double t[5] = {0, 0, 0, 0, 0};
+            if (k < nr) {
+                Part<R> A;
+                load_part<KE>(src, (long long)(lo32(list[k]) & ~kHeadBit), A);
+                add_phi<R>(t, A.m, A.u, A.e);
+                if (part == 0) {
+                    const int o = slot_of(D, buf ^ 1, span, first + k);
+                    store_side<KE>(dst, o, A);
+                    stage_part(rec_chunks(dst, o, R(0)), A);
+                }
             }
-        }
 #pragma unroll
-        for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
-        if (lane == 0) {
+            for (int i = 0; i < 5; ++i) terms[w][i][lane] = t[i];
+            __syncthreads();
+            if (w < 5) {
 #pragma unroll
-            for (int k = 0; k < 5; ++k) sum[wave][k] = acc[k];
+                for (int i = 0; i < kSortWaves; ++i) mine += terms[i][w][lane];
+            }
+            __syncthreads();  // (read before the next round's are written)
         }
-        __syncthreads();
-        if (threadIdx.x < 5) {
-            double *to = (part == 0 ? D.P : D.S) + threadIdx.x * nc + c;
-            double v = sum[0][threadIdx.x];
-            for (int w = 1; w < kSortWaves; ++w) v += sum[w][threadIdx.x];
-            *to = part == 0 ? *to + v : *to - v;
+        if (w < 5) {
+            mine = wave_sum(mine);
+            double *to = (part == 0 ? D.P : D.S) + w * nc + c;
+            if (lane == 0) *to = part == 0 ? *to + mine : *to - mine;
         }
-        __syncthreads();  // (the list and the sums are read before the next part's are written)
     }
 }
 
@@ -3939,7 +3940,10 @@ void count_new(const Dev &D, int buf, hipStream_t s, Prof *pr) {
 
 }  // namespace
 
-bool long_cells(long long cells, long long per_cell) { return long_rule(cells, per_cell); }
+int long_from(long long nc, long long per_cell) {
+    const bool few = nc <= 1024 ? per_cell >= 400 : nc <= 4096 && per_cell >= 1000;
+    return few ? kLongCell : kNoLong;
+}
 int list_split(long long nc, bool sparse, long long per_cell) {
     // some 30% of a cell's particles meet a face; 4,096 waves fill the chip (64 boxes of 10,000
     // particles: k_track 326 us with one row, 26 with 94, k_scatter 51 and 11)
@@ -3985,7 +3989,7 @@ void launch_stream_i(const Dev &D, int buf, int bs, hipStream_t s) {
 // the transport of the cells that k_stream leaves to blocks
 template <typename R, bool MULTI>
 void launch_stream_long(const Dev &D, int buf, hipStream_t s) {
-    if (!D.long_any) return;
+    if (D.long_from == kNoLong) return;
     const unsigned g = (unsigned)D.nc;
     if (D.K > 0)
         k_stream_long<R, MULTI, true><<<g, kLongWaves * kWave, 0, s>>>(D, buf);
@@ -4044,7 +4048,7 @@ void launch_stream(const Dev &D, int buf, const LaunchCfg &cfg, hipStream_t s) {
 
 template <typename R>
 void launch_gather_long(const Dev &D, int buf, hipStream_t s) {
-    if (!D.long_any) return;
+    if (D.long_from == kNoLong) return;
     if (D.K > 0)
         k_gather_long<R, true><<<(unsigned)D.nc, kSortWaves * kWave, 0, s>>>(D, buf);
     else

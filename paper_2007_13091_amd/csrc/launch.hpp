@@ -10,10 +10,10 @@ namespace ugkwp {
 long long scan_partials_needed(long long n);
 long long count_partials_needed(long long nc, long long nff);
 
-// whether a block shares the transport of an instance's cells of many particles: it has `cells` cells and
-// per_cell reference particles (the larger of n_ref and n_min)
-bool long_cells(long long cells, long long per_cell);
-// rows of waves over which the lists of such a batch of nc cells are spread
+// Dev::long_from of a batch of nc cells whose instances have at most per_cell reference particles (the
+// larger of n_ref and n_min)
+int long_from(long long nc, long long per_cell);
+// rows of waves over which the lists of such a batch are spread
 int list_split(long long nc, bool sparse, long long per_cell);
 
 // measurement hook: called around each group of launches of a step (no-op by default)

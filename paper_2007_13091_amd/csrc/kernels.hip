@@ -13,11 +13,13 @@
 //   k_stream         S4+S5 free-flight times and the flights that meet no face, cell by cell:
 //                  stayers are written to their cell's region of the next buffer and summed,
 //                  the others listed
+//   k_stream_long    S4+S5 the same by a block per cell of many particles (small meshes)
 //   k_stream_in      S5  flights of the particles entering through far-field faces
 //   k_track        S5  the listed flights, face to face; bucket sizes
 //   scan           exclusive prefix of the bucket sizes
 //   k_scatter      the leavers by end cell
-//   k_gather       S6  arrivals in a fixed order, sums E and W^p
+//   k_gather       S6  arrivals in a fixed order, sums E and W^p (k_gather_long: long buckets
+//                  by a block)
 //   k_update       S6  update of W; step bookkeeping
 //   k_avg_cells,   time averaging for steady states, when turned on        (Sec. 2.4(c))
 //   k_avg_fin

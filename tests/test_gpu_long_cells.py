@@ -124,8 +124,8 @@ def test_long_cells_are_the_same_bits_in_any_surroundings(name, precision):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("n,n_ref", [(4, 10000), (9, 2500)])
-def test_a_move_costs_about_the_same_in_few_cells(n, n_ref, precision):
+@pytest.mark.parametrize("n,n_ref,most", [(4, 10000, 8.0), (9, 2500, 2.0)])  # (16 and 3 with a wave per cell)
+def test_a_move_costs_about_the_same_in_few_cells(n, n_ref, most, precision):
     def per_move(n, n_ref):
         w = wl.cavity(n=n, n_ref=n_ref)
         w.params.sampling = 1
@@ -145,4 +145,4 @@ def test_a_move_costs_about_the_same_in_few_cells(n, n_ref, precision):
     many = per_move(16, 156) if n == 4 else per_move(32, 56)
     few = per_move(n, n_ref)
     print(f"[gpu-long-cells] ns a move: {1e6 * many:.3f} in many cells, {1e6 * few:.3f} in {n ** 3}", flush=True)
-    assert few < 5.0 * many
+    assert few < most * many

@@ -124,7 +124,7 @@ def test_long_cells_are_the_same_bits_in_any_surroundings(name, precision):
 
 
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("n,n_ref,most", [(4, 10000, 8.0), (9, 2500, 2.0)])  # (16 and 3 with a wave per cell)
+@pytest.mark.parametrize("n,n_ref,most", [(4, 10000, 8.0), (9, 2500, 2.0)])  # (21 and 3.4 with a wave per cell)
 def test_a_move_costs_about_the_same_in_few_cells(n, n_ref, most, precision):
     def per_move(n, n_ref):
         w = wl.cavity(n=n, n_ref=n_ref)
